@@ -13,13 +13,10 @@
 //   anneal_small<P>   persistent: one workgroup owns 16 replicas and all N <= 256 spins for the
 //                     whole anneal. J sits in LDS, the operand copy of S is double-buffered in
 //                     LDS, the master state lives in registers; one barrier per iteration.
-//   anneal_step<P>    one iteration for large N (FP32; FP64 only for shapes the tiled FP64
-//                     kernel does not take): each wave owns 16 rows x 64 replicas, reads J and S
-//                     straight from global memory (L2), updates the master state in HBM and
-//                     writes the next operand copy of S.
-//   anneal_step_tiled, anneal_step_tiled_f64
-//                     the same iteration as tiled matrix products through LDS (BF16 operands on
-//                     256 x 128 workgroup tiles, FP64 on 128 x 64), with the fused epilogue.
+//   anneal_step_tiled, anneal_step_tiled_f
+//                     one iteration for large N as a tiled matrix product through LDS (BF16
+//                     operands on 256 x 128 workgroup tiles; FP64 and FP32 on 128 x 64, 64 x 64 or
+//                     32 x 32), with the fused epilogue.
 //   anneal_sparse*    degree-d graphs with J in ELL rows (see their own comments).
 //   readout_kernel    s~ = sign(s) (s = 0 reads +1).
 //   energy_kernel     exact integer energies for integral J (int8) and integral h, or an
@@ -239,98 +236,6 @@ __global__ __launch_bounds__(1024) void anneal_small_batched(const AnnealArgs* _
   const int2 tk = tasks[blockIdx.x];
   const AnnealArgs a = jobs[tk.x];
   anneal_small_body<P, J8>(a, tk.y);
-}
-
-// ------------------------------------------------------------------------------------------
-// anneal_step<P>: one iteration t for large N. Block = 256 threads (4 waves); workgroup
-// (bx, by) owns rows [64 bx, 64 bx + 64) and replicas [64 by, 64 by + 64); wave w owns the 16
-// rows [64 bx + 16 w, +16) for all 64 replicas (four 16x16 MFMA tiles sharing one A fragment).
-// Operands come straight from global memory: J as [Mp][Kp] op_t, S_cur as [Rp][Kp] op_t
-// (replica-major, k contiguous). Writes S_next and the master state (in place).
-// ------------------------------------------------------------------------------------------
-template <int P>
-__global__ __launch_bounds__(256) void anneal_step(AnnealArgs a, const void* S_cur_v, void* S_next_v,
-                                                   int t) {
-  using Tr = Traits<P>;
-  using op_t = typename Tr::op_t;
-  using acc_t = typename Tr::acc_t;
-  using frag_t = typename Tr::frag_t;
-  using acc4_t = typename Tr::acc4_t;
-  constexpr int KW = Tr::KW;
-  constexpr int VEC = 16 / (KW * (int)sizeof(op_t));
-  const op_t* J = reinterpret_cast<const op_t*>(a.J);
-  const op_t* S_cur = reinterpret_cast<const op_t*>(S_cur_v);
-  op_t* S_next = reinterpret_cast<op_t*>(S_next_v);
-  const int N = a.N, Kp = a.Kp, Kq = Kp >> 2;
-
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const int g = lane >> 4;
-  const int c = lane & 15;
-  const int rowbase = blockIdx.x * 64 + wave * 16;
-  const int arow = rowbase + Tr::a_row(c);
-  const int row0 = rowbase + 4 * g;
-  const int rbase = blockIdx.y * 64;
-
-  acc4_t acc[4];
-#pragma unroll
-  for (int ct = 0; ct < 4; ++ct)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) acc[ct][v] = (acc_t)0;
-
-  const op_t* Arow = J + (size_t)arow * Kp + g * Kq;
-  const op_t* B0 = S_cur + (size_t)(rbase + c) * Kp + g * Kq;
-  for (int m = 0; m < Kq; m += VEC * KW) {
-    const uint4 av = *reinterpret_cast<const uint4*>(Arow + m);
-    const frag_t* af = reinterpret_cast<const frag_t*>(&av);
-#pragma unroll
-    for (int ct = 0; ct < 4; ++ct) {
-      const uint4 bv = *reinterpret_cast<const uint4*>(B0 + (size_t)ct * 16 * Kp + m);
-      const frag_t* bf = reinterpret_cast<const frag_t*>(&bv);
-#pragma unroll
-      for (int u = 0; u < VEC; ++u) acc[ct] = Tr::mfma(af[u], bf[u], acc[ct]);
-    }
-  }
-
-  const acc_t* inv_g = reinterpret_cast<const acc_t*>(a.inv_norm);
-  const acc_t* h_g = reinterpret_cast<const acc_t*>(a.hterm);
-  acc_t* state = reinterpret_cast<acc_t*>(a.state);
-  acc_t* traj = reinterpret_cast<acc_t*>(a.traj);
-  const acc_t coef_t = reinterpret_cast<const acc_t*>(a.coef)[t - 1];
-  acc_t inv[4], hv[4];
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    inv[v] = inv_g[row0 + v];
-    hv[v] = h_g[row0 + v];
-  }
-  const int k_rec = t - a.t_begin;
-#pragma unroll
-  for (int ct = 0; ct < 4; ++ct) {
-    const int r = rbase + ct * 16 + c;
-    const bool live_r = r < a.R;
-    acc_t s[4], fld[4];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      fld[v] = acc[ct][v];
-      s[v] = (live_r && row0 + v < N) ? state[(size_t)r * N + row0 + v] : (acc_t)0;
-    }
-    Epilogue<P>::apply(fld, inv, hv, s, a, coef_t, (uint32_t)(row0 >> 2), (uint32_t)r, (uint32_t)t);
-#pragma unroll
-    for (int v = 0; v < 4; ++v)
-      if (row0 + v >= N || !live_r) s[v] = (acc_t)0;
-    op_t* dst = S_next + (size_t)r * Kp + row0;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) dst[v] = (op_t)s[v];
-    if (live_r) {
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        if (row0 + v < N) {
-          state[(size_t)r * N + row0 + v] = s[v];
-          if (traj && k_rec < a.record) traj[((size_t)k_rec * a.R + r) * N + row0 + v] = s[v];
-        }
-      }
-    }
-  }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1199,151 +1104,209 @@ __global__ __launch_bounds__(512, 1) void anneal_step_tiled(AnnealArgs a, const 
 }
 
 // ------------------------------------------------------------------------------------------
-// anneal_step_tiled_f64: one FP64 iteration as a tiled matrix product with the fused FP64
-// epilogue (the validation path for large N). Workgroup (bx, by) owns rows [128 bx, +128) x
-// replicas [64 by, +64); wave w owns rows 32 w .. +31 (two 16-row tiles) for all 64 replicas
-// (four 16-column tiles): eight v_mfma_f64_16x16x4f64 accumulators. J [Mp][Kp] and S_cur
-// [Rp][Kp] (FP64, k contiguous) stream through a 3-stage LDS ring of 32-k blocks (32 KB of J and
-// 16 KB of S per stage), filled by direct-to-LDS loads issued two blocks ahead. A block is four
-// 8-k windows of two MFMA steps; in window i, step s, lane group g carries k = 8 i + 2 g + s for
-// A and B alike (a dot product does not depend on the order of its terms), so every lane reads
-// both steps' operands with one ds_read_b128. The 16-byte unit u of tile row q is stored at
-// u ^ (q & 15) of its 256-byte row, so the 8 lanes one LDS cycle serves hit 8 distinct bank
-// groups (the A rows of a 16-row tile are permuted as the FP64 instruction's output needs, which
-// keeps them distinct modulo 16). Needs Mp % 128 == 0, Kp % 32 == 0 and S buffers of Rp rows
-// (padding rows zero).
+// anneal_step_tiled_f<P, RT, CT, WM, WR>: one FP64 or FP32 iteration for large N as a tiled matrix
+// product with the fused epilogue. A workgroup of WM x WR waves owns 16 RT WM rows x 16 CT WR
+// replicas, RT x CT accumulators of 16 x 16 per wave. J [Mp][Kp] and S_cur [Rp][Kp] (k contiguous)
+// stream through an LDS ring of NS stages, 256 bytes of k per row and stage, filled by
+// direct-to-LDS loads issued NS - 1 blocks ahead. The 16-byte unit u of tile row q is stored at
+// u ^ (q & 15) of its 256-byte row, so the lanes one LDS cycle serves hit distinct bank groups (the
+// A rows of a 16-row FP64 tile are permuted as that instruction's output needs, which keeps them
+// distinct modulo 16). Which k a unit holds:
+//   FP64  a block is 32 consecutive k, four 8-k windows of two MFMA steps; in window i, step s, lane
+//         group g carries k = 8 i + 2 g + s, so unit 4 i + g holds both steps' operands.
+//   FP32  lane group g owns the k range [g Kp/4, (g+1) Kp/4); a block is 16 consecutive k of each of
+//         the four ranges, and in window i lane group g carries k = g Kp/4 + 16 kb + 4 i + s in
+//         step s = 0..3: unit 4 g + i holds the four steps' operands.
+// Each wave loads its master states before the k loop, so that their latency hides under the
+// matrix work. The order of each output's sum does not depend on the tile, so every tile size gives
+// the same results bit for bit.
+// What bounds it: the matrix cores (64 cycles per 16x16x4 FP64 instruction and SIMD, 32 in FP32),
+// and beside them the block boundaries (about 330 cycles, and 50 per load that a wave issues),
+// which a second wave per SIMD covers in part: hence eight waves per large tile, or two workgroups
+// per CU. Where the tiles do not cover the chip, the serial k loop and the FP64 epilogue of one tile
+// (32 x libm log, sincos and tanh per lane take 40 us) are the time, hence the smaller tiles
+// (launch_step_f_pick). Measured per iteration, N = 2000, against the former kernels (FP64 always
+// 128 x 64 with four waves; FP32 without LDS, operands straight from L2): FP64 R = 1024 226 -> 178
+// us (46.0 TFLOP/s), R = 256 212 -> 55, R = 64 214 -> 34; FP32 R = 1024 270 -> 94 us, R = 256
+// 107 -> 31, N = 777 R = 256 45 -> 12. Padding the operand rows to spread them over the L2 channels
+// changed nothing.
+// Needs Mp % 128 == 0, Kp % 64 == 0, and S buffers of roundup(R, 64) rows (padding rows finite).
 // ------------------------------------------------------------------------------------------
-constexpr int SF_M = 128;                     // rows per workgroup
-constexpr int SF_R = 64;                      // replicas per workgroup
-constexpr int SF_K = 32;                      // k per block
-constexpr int SF_STAGES = 3;
-constexpr int SF_JT = SF_M * SF_K * 8;        // bytes of the J tile of one block (32 KB)
-constexpr int SF_STAGE = SF_JT + SF_R * SF_K * 8;  // J tile + S tile (48 KB)
-constexpr int SF_LPW = SF_STAGE / 1024 / 4;   // 1 KB direct-to-LDS loads per wave and block (12)
+template <int P, int RT, int CT, int WM, int WR>
+struct SfTile {
+  static constexpr int TM = 16 * RT * WM;               // rows per workgroup
+  static constexpr int TR = 16 * CT * WR;               // replicas per workgroup
+  static constexpr int W = WM * WR;                     // waves
+  static constexpr int STAGE = (TM + TR) * 256;         // J tile + S tile of one block
+  static constexpr int LPW = STAGE / 1024 / W;          // 1 KB direct-to-LDS loads per wave and block
+  static constexpr int NS = STAGE > 40 * 1024 ? 3 : (STAGE > 24 * 1024 ? 4 : 5);  // stages of the ring
+  static constexpr int BLK = P == PREC_FP64 ? 32 : 64;  // k per block
+  static_assert(LPW * 1024 * W == STAGE && NS * STAGE <= 160 * 1024, "whole loads per wave; the ring fits in LDS");
+  static_assert((NS - 2) * LPW <= 63, "wait counts fit the vmcnt field");
+};
 
-__global__ __launch_bounds__(256, 1) void anneal_step_tiled_f64(AnnealArgs a, const double* __restrict__ S_cur,
-                                                                double* __restrict__ S_next, int t) {
-  using Tr = Traits<PREC_FP64>;
-  extern __shared__ __align__(16) unsigned char smem_sf[];  // SF_STAGES x (J tile, S tile)
+template <int P, int RT, int CT, int WM, int WR>
+__device__ __forceinline__ void step_tiled_f_body(const AnnealArgs& a, const void* __restrict__ S_cur,
+                                                  void* __restrict__ S_next_v, int t) {
+  using Tr = Traits<P>;
+  using T = SfTile<P, RT, CT, WM, WR>;
+  using acc_t = typename Tr::acc_t;  // the operand type too (FP64 or FP32)
+  using acc4_t = typename Tr::acc4_t;
+  acc_t* S_next = reinterpret_cast<acc_t*>(S_next_v);
+  constexpr int ES = sizeof(acc_t), SPU = 16 / ES;  // element bytes; MFMA steps per 16-byte unit
+  constexpr int LPW = T::LPW, NS = T::NS, LA = NS - 1;
+  typedef acc_t unit_t __attribute__((ext_vector_type(SPU)));
+  extern __shared__ __align__(16) unsigned char smem_sf[];  // NS x (J tile, S tile)
   const int N = a.N, Kp = a.Kp;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: scalar registers
   const int g = lane >> 4, c = lane & 15;
-  const int m0 = blockIdx.x * SF_M, r0 = blockIdx.y * SF_R;
+  const int m0 = blockIdx.x * T::TM, r0 = blockIdx.y * T::TR;
+  const int wm = 16 * RT * (wave / WR), wr = 16 * CT * (wave % WR);
 
-  // direct-to-LDS loads: 48 blocks of 1 KB per stage (blocks 0..31 the J tile, 32..47 the S
-  // tile, four tile rows each); wave w issues blocks 12 w .. 12 w + 11. Lane l fills position
-  // l % 16 of tile row 4 (b % 32) + l / 16 with the global unit the swizzle puts there.
-  size_t goff[SF_LPW];
+  // direct-to-LDS loads: 1 KB blocks of four tile rows, first the J tile's, then the S tile's; wave
+  // w issues blocks LPW w .. LPW w + LPW - 1. Lane l fills position l % 16 of tile row 4 b' + l / 16
+  // (b' the block within its tile) with the global unit the swizzle puts there.
+  size_t goff[LPW];
 #pragma unroll
-  for (int u = 0; u < SF_LPW; ++u) {
-    const int b = SF_LPW * wave + u;
-    const bool is_j = b < 32;
-    const int q = 4 * (is_j ? b : b - 32) + (lane >> 4);
+  for (int u = 0; u < LPW; ++u) {
+    const int b = LPW * wave + u;
+    const bool is_j = 4 * b < T::TM;
+    const int q = 4 * (is_j ? b : b - T::TM / 4) + (lane >> 4);
     const int unit = (lane & 15) ^ (q & 15);
-    goff[u] = is_j ? ((size_t)(m0 + q) * Kp + 2 * unit) * 8 : ((size_t)(r0 + q) * Kp + 2 * unit) * 8;
+    const size_t row = is_j ? m0 + q : r0 + q;
+    const size_t k = P == PREC_FP64 ? 2 * unit : (unit >> 2) * (Kp >> 2) + 4 * (unit & 3);
+    goff[u] = (row * Kp + k) * ES;
   }
   const unsigned char* Jb = reinterpret_cast<const unsigned char*>(a.J);
   const unsigned char* Sb = reinterpret_cast<const unsigned char*>(S_cur);
   unsigned char* ring = smem_sf;
   auto issue = [&](int kb, int stage) {
 #pragma unroll
-    for (int u = 0; u < SF_LPW; ++u) {
-      const int b = SF_LPW * wave + u;
-      const unsigned char* src = (b < 32 ? Jb : Sb) + goff[u] + (size_t)kb * SF_K * 8;
-      __builtin_amdgcn_global_load_lds(reinterpret_cast<const uint32_t*>(src), ring + stage * SF_STAGE + b * 1024,
+    for (int u = 0; u < LPW; ++u) {
+      const int b = LPW * wave + u;
+      const unsigned char* src = (4 * b < T::TM ? Jb : Sb) + goff[u] + (size_t)kb * (T::BLK / (P == PREC_FP64 ? 1 : 4)) * ES;
+      __builtin_amdgcn_global_load_lds(reinterpret_cast<const uint32_t*>(src), ring + stage * T::STAGE + b * 1024,
                                        16, 0, 0);
     }
   };
-  // fragment offsets within a stage: A row 32 wave + 16 rt + a_row(c), B replica 16 ct + c; window
-  // i reads unit 4 i + g of its row
-  int aoff[2][4], boff[4][4];
+  // fragment offsets within a stage
+  int aoff[RT][4], boff[CT][4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
+    const int unit = P == PREC_FP64 ? 4 * i + g : 4 * g + i;
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt) {
-      const int q = 32 * wave + 16 * rt + Tr::a_row(c);
-      aoff[rt][i] = q * 256 + (((4 * i + g) ^ (q & 15)) * 16);
+    for (int rt = 0; rt < RT; ++rt) {
+      const int q = wm + 16 * rt + Tr::a_row(c);
+      aoff[rt][i] = q * 256 + ((unit ^ (q & 15)) * 16);
     }
 #pragma unroll
-    for (int ct = 0; ct < 4; ++ct) {
-      const int q = 16 * ct + c;
-      boff[ct][i] = SF_JT + q * 256 + (((4 * i + g) ^ (q & 15)) * 16);
+    for (int ct = 0; ct < CT; ++ct) {
+      const int q = wr + 16 * ct + c;
+      boff[ct][i] = T::TM * 256 + q * 256 + ((unit ^ (q & 15)) * 16);
     }
   }
 
-  f64x4 acc[2][4];
+  // this wave's master states (issued ahead of the first blocks, so the first wait covers them)
+  acc_t* state = reinterpret_cast<acc_t*>(a.state);
+  acc_t st[RT][CT][4];
 #pragma unroll
-  for (int rt = 0; rt < 2; ++rt)
+  for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-    for (int ct = 0; ct < 4; ++ct)
+    for (int ct = 0; ct < CT; ++ct) {
+      const int row0 = m0 + wm + 16 * rt + 4 * g, r = r0 + wr + 16 * ct + c;
 #pragma unroll
-      for (int v = 0; v < 4; ++v) acc[rt][ct][v] = 0.0;
+      for (int v = 0; v < 4; ++v)
+        st[rt][ct][v] = (r < a.R && row0 + v < N) ? state[(size_t)r * N + row0 + v] : (acc_t)0;
+    }
 
-  const int nkb = Kp / SF_K;
-  issue(0, 0);
-  if (nkb > 1) issue(1, 1);
+  acc4_t acc[RT][CT];
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) acc[rt][ct][v] = (acc_t)0;
+
+  const int nkb = Kp / T::BLK;
+  // The fragments of a window are read into one register set while the MFMAs of the window before
+  // it run on the other, across the block boundaries too: the barrier that makes block kb + 1
+  // visible stands before the last window of block kb.
+  unit_t af[2][RT], bfr[2][CT];
+  auto load = [&](int set, int stage, int i) {
+    const unsigned char* base = ring + stage * T::STAGE;
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) af[set][rt] = *reinterpret_cast<const unit_t*>(base + aoff[rt][i]);
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) bfr[set][ct] = *reinterpret_cast<const unit_t*>(base + boff[ct][i]);
+  };
+#pragma unroll
+  for (int p = 0; p < LA; ++p)
+    if (p < nkb) issue(p, p);
+  if (nkb >= LA) step_wait_vm<LPW * (LA - 1)>();
+  else step_wait_vm<0>();
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+  load(0, 0, 0);
+  int cur = 0;  // stage of block kb
   for (int kb = 0; kb < nkb; ++kb) {
-    // this wave's part of block kb has landed (block kb + 1 may still be in flight)
-    if (kb + 1 < nkb) step_wait_vm<SF_LPW>();
-    else step_wait_vm<0>();
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_barrier();  // every wave's part landed; every wave is done with block kb - 1
-    __builtin_amdgcn_sched_barrier(0);
-    if (kb + 2 < nkb) issue(kb + 2, (kb + 2) % SF_STAGES);
-    const unsigned char* base = ring + (kb % SF_STAGES) * SF_STAGE;
+    const int nxt = cur + 1 == NS ? 0 : cur + 1;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      double2 af[2], bfr[4];
+      if (i < 3) {
+        load((i + 1) & 1, cur, i + 1);
+      } else if (kb + 1 < nkb) {
+        // this wave's part of block kb + 1 has landed (up to LA - 2 blocks after it may still be in flight)
+        if (kb + LA <= nkb) step_wait_vm<LPW * (LA - 2)>();
+        else step_wait_vm<0>();
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_barrier();  // every wave's part landed; every wave is done with block kb - 1
+        __builtin_amdgcn_sched_barrier(0);
+        if (kb + LA < nkb) issue(kb + LA, cur == 0 ? NS - 1 : cur - 1);
+        load(0, nxt, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);  // the reads go out ahead of the MFMAs
 #pragma unroll
-      for (int rt = 0; rt < 2; ++rt) af[rt] = *reinterpret_cast<const double2*>(base + aoff[rt][i]);
+      for (int s = 0; s < SPU; ++s)
 #pragma unroll
-      for (int ct = 0; ct < 4; ++ct) bfr[ct] = *reinterpret_cast<const double2*>(base + boff[ct][i]);
+        for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-      for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-        for (int ct = 0; ct < 4; ++ct) {
-          acc[rt][ct] = Tr::mfma(af[rt].x, bfr[ct].x, acc[rt][ct]);
-          acc[rt][ct] = Tr::mfma(af[rt].y, bfr[ct].y, acc[rt][ct]);
-        }
+          for (int ct = 0; ct < CT; ++ct) acc[rt][ct] = Tr::mfma(af[i & 1][rt][s], bfr[i & 1][ct][s], acc[rt][ct]);
+      __builtin_amdgcn_sched_barrier(0);
     }
-    // the reads of this block are complete before the next barrier frees its buffer
-    __builtin_amdgcn_s_waitcnt(0xC07F);
-    __builtin_amdgcn_sched_barrier(0);
+    cur = nxt;
   }
 
-  // ---- fused FP64 epilogue (the one every FP64 kernel shares) ----------------------------------
-  const double* inv_g = reinterpret_cast<const double*>(a.inv_norm);
-  const double* h_g = reinterpret_cast<const double*>(a.hterm);
-  double* state = reinterpret_cast<double*>(a.state);
-  double* traj = reinterpret_cast<double*>(a.traj);
-  const double coef_t = reinterpret_cast<const double*>(a.coef)[t - 1];
+  // ---- fused epilogue (the one every kernel of the precision shares) ----------------------------
+  const acc_t* inv_g = reinterpret_cast<const acc_t*>(a.inv_norm);
+  const acc_t* h_g = reinterpret_cast<const acc_t*>(a.hterm);
+  acc_t* traj = reinterpret_cast<acc_t*>(a.traj);
+  const acc_t coef_t = reinterpret_cast<const acc_t*>(a.coef)[t - 1];
   const int k_rec = t - a.t_begin;
 #pragma unroll
-  for (int rt = 0; rt < 2; ++rt) {
-    const int row0 = m0 + 32 * wave + 16 * rt + 4 * g;
-    double inv[4], hv[4];
+  for (int rt = 0; rt < RT; ++rt) {
+    const int row0 = m0 + wm + 16 * rt + 4 * g;
+    acc_t inv[4], hv[4];
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       inv[v] = inv_g[row0 + v];
       hv[v] = h_g[row0 + v];
     }
 #pragma unroll
-    for (int ct = 0; ct < 4; ++ct) {
-      const int r = r0 + 16 * ct + c;
+    for (int ct = 0; ct < CT; ++ct) {
+      const int r = r0 + wr + 16 * ct + c;
       const bool live_r = r < a.R;
-      double s[4], fld[4];
+      acc_t fld[4];
+      acc_t* s = st[rt][ct];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        fld[v] = acc[rt][ct][v];
-        s[v] = (live_r && row0 + v < N) ? state[(size_t)r * N + row0 + v] : 0.0;
-      }
-      Epilogue<PREC_FP64>::apply(fld, inv, hv, s, a, coef_t, (uint32_t)(row0 >> 2), (uint32_t)r, (uint32_t)t);
+      for (int v = 0; v < 4; ++v) fld[v] = acc[rt][ct][v];
+      Epilogue<P>::apply(fld, inv, hv, s, a, coef_t, (uint32_t)(row0 >> 2), (uint32_t)r, (uint32_t)t);
 #pragma unroll
       for (int v = 0; v < 4; ++v)
-        if (row0 + v >= N || !live_r) s[v] = 0.0;
-      double* dst = S_next + (size_t)r * Kp + row0;
-#pragma unroll
-      for (int v = 0; v < 4; ++v) dst[v] = s[v];
+        if (row0 + v >= N || !live_r) s[v] = (acc_t)0;
+      acc4_t* dst = reinterpret_cast<acc4_t*>(S_next + (size_t)r * Kp + row0);
+      *dst = acc4_t{s[0], s[1], s[2], s[3]};
       if (live_r) {
 #pragma unroll
         for (int v = 0; v < 4; ++v)
@@ -1354,6 +1317,12 @@ __global__ __launch_bounds__(256, 1) void anneal_step_tiled_f64(AnnealArgs a, co
       }
     }
   }
+}
+
+template <int P, int RT, int CT, int WM, int WR>
+__global__ __launch_bounds__(64 * WM * WR, 2) void anneal_step_tiled_f(AnnealArgs a, const void* __restrict__ S_cur,
+                                                                       void* __restrict__ S_next, int t) {
+  step_tiled_f_body<P, RT, CT, WM, WR>(a, S_cur, S_next, t);
 }
 
 template <int JFMT>
@@ -1367,40 +1336,52 @@ static hipError_t launch_step_tiled(const AnnealArgs& a, const void* S_cur, void
   return hipGetLastError();
 }
 
+template <int P, int RT, int CT, int WM, int WR>
+static hipError_t launch_step_f(const AnnealArgs& a, const void* S_cur, void* S_next, int t, hipStream_t st) {
+  using T = SfTile<P, RT, CT, WM, WR>;
+  const size_t lds = (size_t)T::NS * T::STAGE;
+  hipError_t e = hipFuncSetAttribute((const void*)anneal_step_tiled_f<P, RT, CT, WM, WR>,
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  const dim3 grid(a.Mp / T::TM, (a.R + T::TR - 1) / T::TR);
+  hipLaunchKernelGGL((anneal_step_tiled_f<P, RT, CT, WM, WR>), grid, dim3(64 * T::W), lds, st, a, S_cur, S_next, t);
+  return hipGetLastError();
+}
+
+// Tile of the FP64 / FP32 iteration: 128 x 64 or 64 x 64 with eight waves, one workgroup per CU, or
+// 32 x 32 with four waves and two workgroups per CU. The measured time of one round of tiles over
+// the CUs is 155 / 87 us (FP64, N = 2000; FP32 84 / 46), and 9 + 25.5 us (FP32 4.5 + 14) per 32 x 32
+// tile that a CU gets, i.e. in both precisions 6.2 : 3.3 : 1/3 + 1 per tile; the cheapest by this
+// count is taken. (N = 2000: 128 x 64 from R = 1024, where it takes 178 us in FP64 against 192 with
+// 64 x 64 and 213 with 32 x 32; 64 x 64 at R = 512; 32 x 32 at R = 256, 55 us against 89 and 158.)
+template <int P>
+static hipError_t launch_step_f_pick(const AnnealArgs& a, const void* S_cur, void* S_next, int t, hipStream_t st) {
+  int dev = 0, cus = 256;
+  if (hipGetDevice(&dev) == hipSuccess)
+    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  auto rounds = [&](int tm, int tr) {
+    const long tiles = (long)(a.Mp / tm) * ((a.R + tr - 1) / tr);
+    return (double)((tiles + cus - 1) / cus);
+  };
+  const double big = 6.2 * rounds(128, 64), mid = 3.3 * rounds(64, 64), small = 1.0 / 3 + rounds(32, 32);
+  if (big <= mid && big <= small) return launch_step_f<P, 2, 2, 4, 2>(a, S_cur, S_next, t, st);
+  if (mid <= small) return launch_step_f<P, 1, 2, 4, 2>(a, S_cur, S_next, t, st);
+  return launch_step_f<P, 1, 1, 2, 2>(a, S_cur, S_next, t, st);
+}
+
 hipError_t launch_anneal_step(int prec, int jfmt, const AnnealArgs& a, const void* S_cur, void* S_next, int t,
                               hipStream_t st) {
-  if (prec == PREC_BF16 || prec == PREC_FP8J_BF16S) {
-    if (a.Mp % ST_M == 0 && a.Kp % ST_K == 0) {
+  if (a.Mp % 256 != 0 || a.Kp != a.Mp) return hipErrorInvalidValue;
+  switch (prec) {
+    case PREC_FP64: return launch_step_f_pick<PREC_FP64>(a, S_cur, S_next, t, st);
+    case PREC_FP32: return launch_step_f_pick<PREC_FP32>(a, S_cur, S_next, t, st);
+    case PREC_BF16:
+    case PREC_FP8J_BF16S:
       if (jfmt == 2) return launch_step_tiled<2>(a, S_cur, S_next, t, st);
       if (jfmt == 1) return launch_step_tiled<1>(a, S_cur, S_next, t, st);
       return launch_step_tiled<0>(a, S_cur, S_next, t, st);
-    }
-    if (jfmt != 0) return hipErrorInvalidValue;  // the direct kernel below reads BF16 J
   }
-  if (prec == PREC_FP64 && a.Mp % SF_M == 0 && a.Kp % SF_K == 0 && a.Rp % SF_R == 0) {
-    const size_t lds = (size_t)SF_STAGES * SF_STAGE;
-    hipError_t e = hipFuncSetAttribute((const void*)anneal_step_tiled_f64,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    const dim3 grid(a.Mp / SF_M, a.Rp / SF_R);
-    hipLaunchKernelGGL(anneal_step_tiled_f64, grid, dim3(256), lds, st, a, (const double*)S_cur, (double*)S_next, t);
-    return hipGetLastError();
-  }
-  const dim3 grid(a.Mp / 64, a.Rp / 64);
-  switch (prec) {
-    case PREC_FP64:
-      hipLaunchKernelGGL((anneal_step<PREC_FP64>), grid, dim3(256), 0, st, a, S_cur, S_next, t);
-      break;
-    case PREC_FP32:
-      hipLaunchKernelGGL((anneal_step<PREC_FP32>), grid, dim3(256), 0, st, a, S_cur, S_next, t);
-      break;
-    case PREC_BF16:
-    case PREC_FP8J_BF16S:
-      hipLaunchKernelGGL((anneal_step<PREC_BF16>), grid, dim3(256), 0, st, a, S_cur, S_next, t);
-      break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
+  return hipErrorInvalidValue;
 }
 
 size_t sparse_lds_bytes(int prec, int N, int RB) {
