@@ -191,11 +191,11 @@ int nmfa_set_state(nmfa_ctx *c, int32_t R, const double *in);
 int nmfa_trajectory(nmfa_ctx *c, double *out);
 
 /* Information about a context: writes n, the precision and the kernel path (0 = persistent
- * small-N kernel with J in LDS; 1 = per-iteration kernel; 2 = persistent XCD-group kernel with
- * J rows in LDS whose groups exchanged spins through one XCD's L2; 3 = the same kernel with
- * device-scope fences, used when a group's workgroups were not all placed on one XCD; 4 and 5 =
- * the XCD-group kernel with J rows held in registers (FP4-exact couplings, n <= 2048), exchange
- * as for 2 and 3; 6 = the sparse kernel, J as nonzeros per row (chosen for n > 256 when every
+ * small-N kernel with J in LDS; 1 = per-iteration kernel; 2 = persistent XCD-group kernel
+ * (J rows in registers as FP8 or BF16, n <= 2048, or in LDS) whose groups exchanged spins through
+ * one XCD's L2; 3 = the same with device-scope fences, used when a group's workgroups were not all
+ * placed on one XCD; 4 and 5 = the XCD-group kernel with J rows held in registers as FP4
+ * (FP4-exact couplings, n <= 2048), exchange as for 2 and 3; 6 = the sparse kernel, J as nonzeros per row (chosen for n > 256 when every
  * row has at most min(64, n/8) couplings and either the register variant below applies or no
  * XCD-group kernel does, or with NMFA_FLAG_FORCE_SPARSE); 7 = the sparse kernel with each
  * thread's rows of J held in registers (at most 16 couplings per row, n <= 4096, fewer

@@ -13,7 +13,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libnmfa.so")
-HIP_SOURCES = ["nmfa_kernels.hip", "nmfa_xcd.hip", "nmfa_fill.hip", "nmfa_noalloc.hip"]
+HIP_SOURCES = ["nmfa_kernels.hip", "nmfa_xcd.hip", "nmfa_xrs.hip", "nmfa_fill.hip", "nmfa_noalloc.hip"]
 CXX_SOURCES = ["nmfa_api.cpp", "nmfa_server.cpp"]
 
 ARCH = os.environ.get("NMFA_OFFLOAD_ARCH", "gfx950")
@@ -34,21 +34,21 @@ def build(verbose: bool = False) -> str:
     cc = hipcc()
     objdir = os.path.join(PKG, "_build")
     os.makedirs(objdir, exist_ok=True)
-    objs = []
-    for src in HIP_SOURCES:
+    objs, running = [], []
+    for src in HIP_SOURCES + CXX_SOURCES:  # one compiler process per source
         obj = os.path.join(objdir, src + ".o")
-        cmd = [cc, *COMMON, *DEVICE, "-c", os.path.join(CSRC, src), "-o", obj]
+        if src in HIP_SOURCES:
+            cmd = [cc, *COMMON, *DEVICE, "-c", os.path.join(CSRC, src), "-o", obj]
+        else:
+            cmd = [cc, *COMMON, "-x", "c++", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-c",
+                   os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
-        subprocess.check_call(cmd)
+        running.append((cmd, subprocess.Popen(cmd)))
         objs.append(obj)
-    for src in CXX_SOURCES:
-        obj = os.path.join(objdir, src + ".o")
-        cmd = [cc, *COMMON, "-x", "c++", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-c", os.path.join(CSRC, src), "-o", obj]
-        if verbose:
-            print(" ".join(cmd), flush=True)
-        subprocess.check_call(cmd)
-        objs.append(obj)
+    failed = [cmd for cmd, proc in running if proc.wait() != 0]
+    if failed:
+        raise subprocess.CalledProcessError(1, failed[0])
     tmp = LIB + ".tmp"
     cmd = [cc, "--offload-arch=" + ARCH, "-shared", "-fPIC", *objs, "-o", tmp, "-lpthread"]
     if verbose:

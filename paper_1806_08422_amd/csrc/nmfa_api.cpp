@@ -413,6 +413,8 @@ extern "C" int nmfa_create(int32_t n, const double* J, const double* h, const nm
   const bool x_ok = bf && Mp_x / xcd_rows() <= 32 && x_nbuf >= 2;
   // register-resident-J variant of the XCD-group kernel: FP4-exact couplings, n <= 2048
   const bool x_rj = x_ok && x_jfmt == 2 && xrj_fits(n) && !(p->flags & NMFA_FLAG_FORCE_LDS_J);
+  // couplings that FP4 does not hold exactly: the small tiles keep them in registers as FP8 or BF16
+  const bool x_rs = bf && !fp8s && x_jfmt != 2 && xrj_fits(n) && !(p->flags & NMFA_FLAG_FORCE_LDS_J);
   // sparse (ELL) kernel: maximum degree D <= 64 and the workgroup's state fits in LDS
   int deg_max = 0;
   for (int i = 0; i < n; ++i) deg_max = std::max(deg_max, rows[i].deg);
@@ -453,7 +455,7 @@ extern "C" int nmfa_create(int32_t n, const double* J, const double* h, const nm
     c->path = 0;
   } else if (sp_auto) {
     c->path = 3;
-  } else if (x_ok) {
+  } else if (x_ok || x_rs) {
     c->path = 2;
   } else {
     c->path = 1;
@@ -471,6 +473,12 @@ extern "C" int nmfa_create(int32_t n, const double* J, const double* h, const nm
   } else if (c->path == 2 && x_rj) {
     c->xvar = fp8s ? 2 : 1;
     c->Mp = (int)round_up(n, xrj_rows(fp8s ? 1 : 0));
+    c->Kp = xrj_kp(n);
+    c->lds_stride = 0;
+    c->jfmt = x_jfmt;
+  } else if (c->path == 2 && x_rs) {
+    c->xvar = 3;
+    c->Mp = (int)round_up(n, 128);
     c->Kp = xrj_kp(n);
     c->lds_stride = 0;
     c->jfmt = x_jfmt;
@@ -777,11 +785,54 @@ extern "C" int nmfa_anneal_range(nmfa_ctx* c, int32_t R, int32_t t_f, int32_t t_
   return ctx_launch_run(c, R, t_f, t_begin, t_end, seed, (hipStream_t)hip_stream, true);
 }
 
-bool ctx_group_shape(const nmfa_ctx* c, int32_t R, int* P, int* G) {
+// The tile of a group-kernel run: the large tile of the context's kernel (tile -1) or, with J in
+// registers and BF16 spins, one of the small tiles. Small tiles put more CUs on a replica (a group of
+// few replicas spreads over more workgroups) and read the spins more often per update, so the
+// choice is by the time of one iteration of all R replicas: launches (groups over the groups that
+// fit in width workgroups) times the measured time of one iteration of a launch, a + b Kp / 1024 us:
+//                      Kp =  512   1024   2048 (us)      N = 2000: R = 100   256   512   1024
+//   64 x 16 (tile 0)        1.3    1.7    2.4                      2.5   5.0  10.2   20.1
+//   128 x 16 (tile 1)       1.6    2.2    3.4                      3.5   3.6   7.0   13.8
+//   128 x 32 (tile 2)       2.2    3.1    4.8                      4.7   4.8   5.0    9.6
+//   256 x 32 (anneal_xrj)   3.4    4.7    7.3                      7.3   7.3   7.4    8.2
+// Launches in which every XCD holds whole groups need groups in multiples of eight; the others pay
+// for device-scope fences, most with the smallest tile (N = 2000, R = 100: 2.6 -> 7.0, 3.6 -> 5.3,
+// 4.9 -> 6.7 and 7.3 -> 8.8 us). Two workgroups per CU gained nothing (128 x 16, R = 512: 7.0 us for
+// one launch of 512 workgroups, 2 x 3.5 for two of 256), so width counts one per CU.
+bool ctx_group_plan(const nmfa_ctx* c, int32_t R, int width, GroupPlan* out) {
   if (c->path != 2) return false;
-  const int Rg = c->xvar ? xrj_group_replicas(c->xvar == 2) : xcd_group_replicas();
-  *G = (R + Rg - 1) / Rg;
-  *P = c->Mp / (c->xvar ? xrj_rows(c->xvar == 2) : xcd_rows());
+  width = std::min(width, GROUP_MAX_WGS);
+  static const double kTime[3][3] = {{0.9, 0.75, 4.0}, {1.0, 1.2, 1.8}, {1.4, 1.7, 1.8}};  // a, b, fences
+  bool any = false;
+  auto consider = [&](int tile, int rows, int rg, double a, double b, double fences) {
+    const int P = c->Mp / rows, G = (R + rg - 1) / rg;
+    const double t = a + b * c->Kp / 1024.0;
+    const int local = width / (8 * P) * 8, fenced = width / P;
+    for (const int per : {local, fenced}) {
+      if (per < 1) continue;
+      const double us = (double)((G + per - 1) / per) * (per == local ? t : t + fences);
+      if (any && us >= out->us) continue;
+      *out = GroupPlan{tile, P, rg, G, per, us};
+      any = true;
+    }
+    return P;
+  };
+  if (c->xvar == 1 || c->xvar == 3)
+    for (int tile : {2, 1, 0})
+      if (xrs_applies(c->jfmt, tile, c->Kp))
+        consider(tile, xrs_rows(tile), xrs_group_replicas(tile), kTime[tile][0], kTime[tile][1], kTime[tile][2]);
+  if (c->xvar == 0) consider(-1, xcd_rows(), xcd_group_replicas(), 2.0, 5.6, 1.0);
+  if (c->xvar == 1) consider(-1, xrj_rows(0), xrj_group_replicas(0), 2.1, 2.6, 0.8);
+  if (c->xvar == 2) consider(-1, xrj_rows(1), xrj_group_replicas(1), 1.8, 1.6, 0.8);
+  if (!any) {  // not even one group fits in width: one group per launch
+    width = 1 << 20;
+    if (c->xvar == 0) consider(-1, xcd_rows(), xcd_group_replicas(), 2.0, 5.6, 1.0);
+    else if (c->xvar == 3) consider(0, xrs_rows(0), xrs_group_replicas(0), 0.9, 0.75, 4.0);
+    else consider(-1, xrj_rows(c->xvar == 2), xrj_group_replicas(c->xvar == 2), 2.1, 2.6, 0.8);
+    out->per_launch = 1;
+    out->us = 1e9;
+    return false;
+  }
   return true;
 }
 
@@ -802,14 +853,12 @@ int ctx_launch_run(nmfa_ctx* c, int32_t R, int32_t t_f, int32_t t_begin, int32_t
     c->launches = 1;
     HIP_TRY(hipEventRecord(c->evm, st));
   } else if (c->path == 2) {
-    const int Rg = c->xvar ? xrj_group_replicas(c->xvar == 2) : xcd_group_replicas();
-    const int G = (R + Rg - 1) / Rg;
-    const int P = c->Mp / (c->xvar ? xrj_rows(c->xvar == 2) : xcd_rows());
-    int cus = 0;
-    HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device));
-    int width = std::min(cus, 256);  // the control block serves 256 workgroups
+    int width = 0;
+    HIP_TRY(hipDeviceGetAttribute(&width, hipDeviceAttributeMultiprocessorCount, c->device));
     if (max_workgroups > 0) width = std::min(width, max_workgroups);
-    const int per_launch = std::max(1, width / P);
+    GroupPlan gp;
+    ctx_group_plan(c, R, width, &gp);
+    const int Rg = gp.rg, G = gp.G, P = gp.P, per_launch = gp.per_launch;
     HIP_TRY(launch_pack_state(c->prec, c->d_state, c->d_S[t_begin & 1], c->n, R, c->Kp, c->Ks, G * Rg,
                               t_begin == 1 ? 1 : 0, st));
     // A new run clears the whole control block; a continued one (and every launch after the
@@ -822,6 +871,10 @@ int ctx_launch_run(nmfa_ctx* c, int32_t R, int32_t t_f, int32_t t_begin, int32_t
     c->launches = 0;
     for (int gb = 0; gb < G; gb += per_launch) {
       const int ng = std::min(per_launch, G - gb);
+      // workgroups are dispatched round robin over the eight XCDs: a multiple of 8 P of them, where
+      // that many fit, gives every XCD a multiple of P, so that every group exchanges through one L2
+      const int even = (ng + 7) / 8 * 8 * P;
+      const int grid = even <= width ? even : ng * P;
       if (gb > 0 || t_begin > 1) {  // fresh registration and barrier counters; abort and mode persist
         HIP_TRY(launch_zero_words(ctl, 0, 17, 64, ctl_words, st));
       }
@@ -832,11 +885,13 @@ int ctx_launch_run(nmfa_ctx* c, int32_t R, int32_t t_f, int32_t t_begin, int32_t
       x.ctl = c->d_ctl;
       x.P = P;
       x.group_base = gb;
+      x.groups = ng;
       x.force_fenced = (c->flags & NMFA_FLAG_FORCE_FENCED) ? 1 : 0;
       x.nbuf = c->nbuf;
-      if (c->xvar == 2) HIP_TRY(launch_anneal_xrj8(a, x, ng, st));
-      else if (c->xvar) HIP_TRY(launch_anneal_xrj(a, x, ng, st));
-      else HIP_TRY(launch_anneal_xcd(c->jfmt, a, x, ng, st));
+      if (gp.tile >= 0) HIP_TRY(launch_anneal_xrs(c->jfmt, gp.tile, a, x, grid, st));
+      else if (c->xvar == 2) HIP_TRY(launch_anneal_xrj8(a, x, grid, st));
+      else if (c->xvar) HIP_TRY(launch_anneal_xrj(a, x, grid, st));
+      else HIP_TRY(launch_anneal_xcd(c->jfmt, a, x, grid, st));
       ++c->launches;
     }
     HIP_TRY(hipEventRecord(c->evm, st));
@@ -1055,7 +1110,7 @@ extern "C" int nmfa_info(nmfa_ctx* c, int32_t* n, int32_t* precision, int32_t* p
         int rc = sync_ctx(c);
         if (rc) return rc;
       }
-      *path = ((c->exchange_mode == 2) ? 3 : 2) + (c->xvar ? 2 : 0);
+      *path = ((c->exchange_mode == 2) ? 3 : 2) + (c->xvar == 1 || c->xvar == 2 ? 2 : 0);
     } else {
       *path = (c->path == 3) ? 6 + c->sp_rq : c->path;
     }

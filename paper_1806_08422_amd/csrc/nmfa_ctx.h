@@ -16,7 +16,8 @@ struct nmfa_ctx {
   int path = 0;  // 0 = persistent small-N kernel, 1 = per-iteration kernel, 2 = XCD-group kernel
   int jfmt = 1;              // path 2: J format in LDS (0 BF16, 1 FP8 E4M3, 2 FP4 E2M1)
   int nbuf = 2;              // path 2: spin chunk buffers in LDS (2, 3, 4 or 6)
-  int xvar = 0;              // path 2: 0 = J rows in LDS, 1 = J rows in registers (FP4)
+  int xvar = 0;              // path 2: 0 = J rows in LDS; in registers: 1 = FP4, 2 = FP4 with FP8 spins,
+                             // 3 = FP8 or BF16 (small tiles only)
   unsigned* d_ctl = nullptr; // path 2: control block
   bool ctl_pending = false;  // path 2: abort/mode flags not yet read back
   int exchange_mode = 0;     // path 2: 1 = XCD-local, 2 = device-scope fences
@@ -81,9 +82,16 @@ struct nmfa_ctx {
 int ctx_prepare_run(nmfa_ctx* c, int32_t R, int32_t t_f, int32_t t_begin, int32_t t_end, uint64_t seed,
                     hipStream_t st, nmfa::AnnealArgs* out);
 // For the persistent XCD-group path (whose workgroups wait for each other, so that all of one
-// launch must be resident at once): P workgroups per replica group and G groups for R replicas.
-// Returns false for the other paths.
-bool ctx_group_shape(const nmfa_ctx* c, int32_t R, int* P, int* G);
+// launch must be resident at once): the tile for R replicas when one launch may hold width
+// workgroups. Returns false for the other paths, and where not even one replica group fits.
+struct GroupPlan {
+  int tile = -1;       // small tile (launch_anneal_xrs), or -1 for the large tile of the context's kernel
+  int P = 1, rg = 1;   // workgroups and replicas per group
+  int G = 1;           // groups
+  int per_launch = 1;  // groups per launch
+  double us = 0;       // estimated time of one iteration of all groups
+};
+bool ctx_group_plan(const nmfa_ctx* c, int32_t R, int width, GroupPlan* out);
 // Enqueue iterations t_begin..t_end on the context's kernel path; with finish, also the energies.
 // max_workgroups > 0 caps the workgroups of one group-kernel launch (more launches, one after the
 // other on st, cover the remaining groups); results do not depend on it.

@@ -26,6 +26,8 @@ struct AnnealArgs {
   int negate_noise;      // test hook: z -> -z
 };
 
+constexpr int GROUP_MAX_WGS = 256;  // workgroups of one group-kernel launch (control block size)
+
 // Persistent large-N kernel (XCD groups): extra arguments.
 struct XcdArgs {
   void* S[2];        // operand copies of the spins, BF16 [Rp][ks], double-buffered by parity of t
@@ -33,6 +35,7 @@ struct XcdArgs {
   unsigned* ctl;     // control block (xcd_ctl_words() words, zeroed before every launch)
   int P;             // workgroups per replica group = Mp / xcd_rows()
   int group_base;    // first replica group of this launch
+  int groups;        // replica groups of this launch (workgroups of further ones leave at once)
   int force_fenced;  // test hook: use device-scope fences even when the groups are XCD-local
   int nbuf;          // spin chunk buffers in LDS: 2, 3, 4 or 6
 };
@@ -42,12 +45,21 @@ hipError_t launch_anneal_small(int prec, const AnnealArgs& a, hipStream_t st);
 hipError_t launch_anneal_small_batched(int prec, const AnnealArgs* jobs, const int2* tasks, int n_tasks,
                                        int max_Mp, size_t lds, hipStream_t st);
 // jfmt: format of J in global memory and LDS: 0 = BF16, 1 = FP8 E4M3, 2 = FP4 E2M1
-hipError_t launch_anneal_xcd(int jfmt, const AnnealArgs& a, const XcdArgs& x, int groups, hipStream_t st);
+hipError_t launch_anneal_xcd(int jfmt, const AnnealArgs& a, const XcdArgs& x, int grid, hipStream_t st);
 // Register-resident-J variant (FP4 J), Kp = xrj_kp(n): BF16 spins with 256 rows per workgroup and
 // groups of 32 replicas; FP8 spins (launch_anneal_xrj8) with 128 rows and groups of 64 replicas.
-hipError_t launch_anneal_xrj(const AnnealArgs& a, const XcdArgs& x, int groups, hipStream_t st);
+hipError_t launch_anneal_xrj(const AnnealArgs& a, const XcdArgs& x, int grid, hipStream_t st);
 // The same decomposition with FP8 E4M3 spin operands (FP4 x FP8 scaled MFMA); S holds bytes.
-hipError_t launch_anneal_xrj8(const AnnealArgs& a, const XcdArgs& x, int groups, hipStream_t st);
+hipError_t launch_anneal_xrj8(const AnnealArgs& a, const XcdArgs& x, int grid, hipStream_t st);
+// Small tiles of the register-J kernel, BF16 spins, J of format jfmt in rows of Kp = xrj_kp(n)
+// couplings: 64 x 16, 128 x 16 and 128 x 32 (tiles 0, 1, 2; rows x replicas per workgroup). grid:
+// workgroups launched (>= x.groups * x.P).
+hipError_t launch_anneal_xrs(int jfmt, int tile, const AnnealArgs& a, const XcdArgs& x, int grid, hipStream_t st);
+int xrs_rows(int tile);
+int xrs_group_replicas(int tile);
+bool xrs_applies(int jfmt, int tile, int Kp);
+hipError_t launch_group_resident(const void* fn, int grid, int block, size_t lds, const AnnealArgs& a,
+                                 const XcdArgs& x, hipStream_t st);
 int xrj_rows(int fp8_spins);
 int xrj_group_replicas(int fp8_spins);
 int xrj_kp(int n);

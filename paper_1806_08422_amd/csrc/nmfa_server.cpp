@@ -31,6 +31,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <chrono>
 #include <cmath>
 #include <condition_variable>
@@ -181,32 +182,35 @@ void finish_job(nmfa_server* s, Job* j, int status) {
 // others). Budgets: lane 0 half of the CUs, lanes 1 and 2 a quarter each, rounded down to a
 // multiple of the 8 XCDs so that the round-robin placement of a launch's workgroups over the XCDs
 // also fits. A request goes to the lane on which, after the work already given to it, it would
-// finish first, with per-launch time taken as proportional to Mp (the k length) and the number
-// of launches as its groups over the groups that fit the budget.
+// finish first, by the time estimate of its tile under that lane's budget.
 void plan_group_lanes(const nmfa_server* s, const std::vector<Job*>& jobs, const std::vector<int>& t_end,
                       std::vector<int>* lane, std::vector<int>* cap) {
   lane->assign(jobs.size(), -1);
   cap->assign(jobs.size(), 0);
-  std::vector<int> idx, P(jobs.size()), G(jobs.size());
+  std::vector<int> idx;
   for (size_t k = 0; k < jobs.size(); ++k)
-    if (jobs[k]->ctx && ctx_group_shape(jobs[k]->ctx, jobs[k]->R, &P[k], &G[k])) idx.push_back((int)k);
+    if (jobs[k]->ctx && jobs[k]->ctx->path == 2) idx.push_back((int)k);
   for (int k : idx) (*lane)[k] = 0;  // default: one stream, whole chip
   const int budget[SERVER_LANES] = {s->cus / 2 / 8 * 8, s->cus / 4 / 8 * 8, s->cus / 4 / 8 * 8};
   if (idx.size() < 2 || budget[1] < 8) return;
-  for (int k : idx)
-    if (P[k] > budget[0]) return;
-  auto iters = [&](int k) { return (double)(t_end[k] - jobs[k]->t_sched); };
-  std::sort(idx.begin(), idx.end(), [&](int x, int y) {
-    return (double)G[x] * P[x] * jobs[x]->ctx->Mp * iters(x) > (double)G[y] * P[y] * jobs[y]->ctx->Mp * iters(y);
-  });
+  // time of each request's chunk on each lane (infinite where not one of its groups fits)
+  std::vector<std::array<double, SERVER_LANES>> cost(jobs.size());
+  for (int k : idx) {
+    const double iters = t_end[k] - jobs[k]->t_sched;
+    for (int L = 0; L < SERVER_LANES; ++L) {
+      GroupPlan gp;
+      cost[k][L] = ctx_group_plan(jobs[k]->ctx, jobs[k]->R, budget[L], &gp) ? gp.us * iters : HUGE_VAL;
+    }
+    if (cost[k][0] == HUGE_VAL) return;
+  }
+  std::sort(idx.begin(), idx.end(), [&](int x, int y) { return cost[x][0] > cost[y][0]; });
   double load[SERVER_LANES] = {0, 0, 0};
   for (int k : idx) {
     int best = -1;
     double best_end = 0, best_t = 0;
     for (int L = 0; L < SERVER_LANES; ++L) {
-      if (P[k] > budget[L]) continue;
-      const int per = budget[L] / P[k];
-      const double t = (double)((G[k] + per - 1) / per) * jobs[k]->ctx->Mp * iters(k);
+      const double t = cost[k][L];
+      if (t == HUGE_VAL) continue;
       if (best < 0 || load[L] + t < best_end) {
         best = L;
         best_end = load[L] + t;

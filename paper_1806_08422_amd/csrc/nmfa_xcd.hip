@@ -23,216 +23,21 @@
 //   * Barrier: the P workgroups of a group count arrivals with a device-scope atomic and poll it
 //     with device-scope loads. When every group sits inside one XCD (checked at start-up from
 //     the XCC_ID hardware register) the new spins are exchanged through that XCD's L2: stores
-//     complete before the arrival, and readers invalidate their L1 after the barrier. Otherwise
+//     complete before the arrival, and readers load past their L1. Otherwise
 //     the workgroups fall back to device-scope release/acquire fences.
 //   * Every wait is bounded; a timeout raises an abort flag that ends every workgroup's loop and
 //     is reported to the host as an error.
 #include <hip/hip_runtime.h>
 
-#include <utility>
-
 #include "nmfa_device.h"
+#include "nmfa_group.h"
 #include "nmfa_internal.h"
 
 namespace nmfa {
 
-// control block layout (uint32 words)
-enum : int {
-  CTL_REG = 0,        // [16] workgroups registered per XCD
-  CTL_TOTAL = 16,     // workgroups registered
-  CTL_ABORT = 17,     // barrier timeout
-  CTL_MODE = 18,      // 1 = XCD-local exchange, 2 = device-scope fences (written by workgroup 0)
-  CTL_BAR = 64,       // group barrier counters, one per 16 words
-  CTL_WG = 64 + 16 * 256,  // per workgroup: group, row block, exchange mode (4 words each)
-  CTL_WORDS = 64 + 16 * 256 + 4 * 256,
-};
-
 constexpr int XCD_ROWS = 64;   // rows of J per workgroup
 constexpr int XCD_RG = 128;    // replicas per group
 constexpr int XCD_KC = 64;     // k per streamed spin chunk
-
-constexpr unsigned SPIN_LIMIT = 1u << 22;  // about a second of polling
-
-__device__ __forceinline__ unsigned ld_dev(const unsigned* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Widen 8 FP8 E4M3 values (two 32-bit words) to 8 BF16 (exact for every FP8 value).
-__device__ __forceinline__ bf16x8 fp8x8_to_bf16x8(uint32_t lo, uint32_t hi) {
-  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-  const bf16x2 p0 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, 1.0f, false);
-  const bf16x2 p1 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, 1.0f, true);
-  const bf16x2 p2 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, 1.0f, false);
-  const bf16x2 p3 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, 1.0f, true);
-  bf16x8 r;
-  r[0] = p0[0]; r[1] = p0[1]; r[2] = p1[0]; r[3] = p1[1];
-  r[4] = p2[0]; r[5] = p2[1]; r[6] = p3[0]; r[7] = p3[1];
-  return r;
-}
-
-// Widen 8 FP4 E2M1 values (one 32-bit word, value 2b in the low nibble of byte b) to 8 BF16.
-__device__ __forceinline__ bf16x8 fp4x8_to_bf16x8(uint32_t w) {
-  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-  const bf16x2 p0 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(w, 1.0f, 0);
-  const bf16x2 p1 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(w, 1.0f, 1);
-  const bf16x2 p2 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(w, 1.0f, 2);
-  const bf16x2 p3 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(w, 1.0f, 3);
-  bf16x8 r;
-  r[0] = p0[0]; r[1] = p0[1]; r[2] = p1[0]; r[3] = p1[1];
-  r[4] = p2[0]; r[5] = p2[1]; r[6] = p3[0]; r[7] = p3[1];
-  return r;
-}
-
-// Wait until at most N of this wave's vector-memory operations are outstanding (N <= 63: the
-// counter's low four bits sit in bits 3:0 of the immediate, the high two in bits 15:14; LDS and
-// export counters are not waited on).
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-  static_assert(N >= 0 && N <= 63, "vmcnt immediate");
-  __builtin_amdgcn_s_waitcnt(0xF70 | (N & 15) | ((N >> 4) << 14));
-}
-
-// Wait until this wave's LDS reads (and scalar loads) are complete; vector-memory counters are
-// left alone.
-__device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(0xC07F); }
-
-// Workgroup barrier without the memory fence of __syncthreads (which would also wait for the
-// chunks still in flight); the asm statements keep the compiler from moving LDS accesses across.
-__device__ __forceinline__ void bare_barrier() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
-// Where a workgroup sits: its replica group, its row block and the exchange mode.
-struct XcdSlot {
-  unsigned my_group;  // group index within this launch
-  int rb;             // row block
-  bool xcd_mode;      // spins exchanged through the XCD's L2 (no device-scope fences)
-  bool aborted;
-};
-
-// Registration: every workgroup reports its XCD (HW_REG_XCC_ID); when each XCD holds a multiple
-// of P workgroups, groups are formed inside XCDs, else by launch order with device-scope fences.
-// Thread 0 does the work; the result is broadcast through this workgroup's control words.
-__device__ XcdSlot xcd_register(const XcdArgs& x, int tid) {
-  unsigned* ctl = x.ctl;
-  const unsigned P = (unsigned)x.P;
-  if (tid == 0) {
-    const unsigned xcc = __builtin_amdgcn_s_getreg((20) | (0 << 6) | (15 << 11)) & 0xfu;
-    const unsigned slot = atomicAdd(&ctl[CTL_REG + xcc], 1u);
-    atomicAdd(&ctl[CTL_TOTAL], 1u);
-    unsigned spins = 0;
-    while (ld_dev(&ctl[CTL_TOTAL]) < gridDim.x) {
-      if (++spins > SPIN_LIMIT) {
-        atomicExch(&ctl[CTL_ABORT], 1u);
-        break;
-      }
-    }
-    // XCD-local exchange needs every XCD's workgroup count to be a multiple of P.
-    unsigned base = 0, ok = 1;
-    for (unsigned k = 0; k < 16; ++k) {
-      const unsigned cnt = ld_dev(&ctl[CTL_REG + k]);
-      if (cnt % P) ok = 0;
-      if (k < xcc) base += cnt;
-    }
-    unsigned* info = &ctl[CTL_WG + 4 * blockIdx.x];
-    info[0] = ok ? (base + slot) / P : blockIdx.x / P;
-    info[1] = ok ? slot % P : blockIdx.x % P;
-    info[2] = (ok && !x.force_fenced) ? 1u : 0u;
-    if (blockIdx.x == 0) atomicMax(&ctl[CTL_MODE], (ok && !x.force_fenced) ? 1u : 2u);
-    __builtin_amdgcn_s_waitcnt(0);
-  }
-  __syncthreads();
-  XcdSlot r;
-  r.my_group = __builtin_amdgcn_readfirstlane(ld_dev(&ctl[CTL_WG + 4 * blockIdx.x]));
-  r.rb = (int)__builtin_amdgcn_readfirstlane(ld_dev(&ctl[CTL_WG + 4 * blockIdx.x + 1]));
-  r.xcd_mode = ld_dev(&ctl[CTL_WG + 4 * blockIdx.x + 2]) != 0;
-  r.aborted = ld_dev(&ctl[CTL_ABORT]) != 0;
-  return r;
-}
-
-// Group barrier after the new spins are stored, in two halves so that work which does not
-// depend on the other workgroups can run in between. Arrive: this workgroup's stores are
-// complete (and released to the device when the group spans XCDs); one thread adds to the
-// group's counter.
-__device__ __forceinline__ void xcd_group_arrive(unsigned* bar, bool xcd_mode, int tid) {
-  __builtin_amdgcn_s_waitcnt(0);  // this wave's stores of the new spins are complete
-  __syncthreads();
-  if (tid == 0) {
-    if (!xcd_mode) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    __hip_atomic_fetch_add(bar, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-}
-
-// Wait: one thread polls until all P workgroups have arrived for this epoch (bounded), then the
-// other workgroups' spins are made visible. Returns whether the anneal was aborted (a wait timed
-// out somewhere).
-__device__ __forceinline__ bool xcd_group_wait(const XcdArgs& x, unsigned* bar, unsigned epoch, bool xcd_mode,
-                                               int tid) {
-  unsigned* ctl = x.ctl;
-  if (tid == 0) {
-    const unsigned target = (unsigned)x.P * epoch;
-    unsigned spins = 0;
-    while (ld_dev(bar) < target) {
-      if (++spins > SPIN_LIMIT || ld_dev(&ctl[CTL_ABORT])) {
-        atomicExch(&ctl[CTL_ABORT], 1u);
-        break;
-      }
-    }
-    if (!xcd_mode) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-  }
-  __syncthreads();
-  if (xcd_mode) asm volatile("buffer_inv sc0" ::: "memory");  // drop stale L1 lines
-  return ld_dev(&ctl[CTL_ABORT]) != 0;
-}
-
-// Wait of the register-J kernel, which keeps the round trips to L2 off its critical path: the
-// caller polls the counter once ahead (seen, read while it draws the next noise), the polling
-// thread reads the abort word only every 64 polls, and its decision reaches the other waves
-// through an LDS word (abort_word) rather than a load of the control block by every thread.
-// Every wave of the workgroup therefore sees the same decision.
-__device__ __forceinline__ bool xrj_group_wait(const XcdArgs& x, unsigned* bar, unsigned epoch, bool xcd_mode,
-                                               int tid, unsigned seen, unsigned* abort_word) {
-  unsigned* ctl = x.ctl;
-  if (tid == 0) {
-    const unsigned target = (unsigned)x.P * epoch;
-    unsigned ab = 0;
-    if (seen < target) {
-      unsigned spins = 0;
-      while (ld_dev(bar) < target) {
-        if ((++spins & 63u) == 0 && (spins > SPIN_LIMIT || ld_dev(&ctl[CTL_ABORT]))) {
-          atomicExch(&ctl[CTL_ABORT], 1u);
-          ab = 1;
-          break;
-        }
-      }
-    }
-    if (!xcd_mode) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    *abort_word = ab;
-  }
-  __syncthreads();
-  if (xcd_mode) asm volatile("buffer_inv sc0" ::: "memory");  // drop stale L1 lines
-  return *abort_word != 0;
-}
-
-__device__ __forceinline__ bool xcd_group_barrier(const XcdArgs& x, unsigned* bar, unsigned epoch,
-                                                  bool xcd_mode, int tid) {
-  xcd_group_arrive(bar, xcd_mode, tid);
-  return xcd_group_wait(x, bar, epoch, xcd_mode, tid);
-}
-
-// Raw J fragment of one lane for one k-step: 8 values as 16 (BF16), 8 (FP8) or 4 (FP4) bytes.
-template <int JFMT> struct JRaw;
-template <> struct JRaw<0> { typedef bf16x8 T; };
-template <> struct JRaw<1> { typedef uint2 T; };
-template <> struct JRaw<2> { typedef uint32_t T; };
-
-template <int JFMT>
-__device__ __forceinline__ bf16x8 widen(const typename JRaw<JFMT>::T& v);
-template <> __device__ __forceinline__ bf16x8 widen<0>(const bf16x8& v) { return v; }
-template <> __device__ __forceinline__ bf16x8 widen<1>(const uint2& v) { return fp8x8_to_bf16x8(v.x, v.y); }
-template <> __device__ __forceinline__ bf16x8 widen<2>(const uint32_t& v) { return fp4x8_to_bf16x8(v); }
 
 // JFMT: 0 = BF16, 1 = FP8 E4M3, 2 = FP4 E2M1 (format of J in global memory and in LDS);
 // NB: spin chunk buffers in LDS.
@@ -257,6 +62,7 @@ __global__ __launch_bounds__(512, 1) void anneal_xcd(AnnealArgs a, XcdArgs x) {
   // ---- registration: find the XCD of every workgroup, then agree on the mapping -------------
   const XcdSlot slot = xcd_register(x, tid);
   const unsigned my_group = slot.my_group;
+  if (my_group >= (unsigned)x.groups) return;  // beyond the launch's groups
   const int group = (int)my_group + x.group_base;
   const int rb = slot.rb;
   const bool xcd_mode = slot.xcd_mode;
@@ -374,7 +180,7 @@ __global__ __launch_bounds__(512, 1) void anneal_xcd(AnnealArgs a, XcdArgs x) {
 #pragma unroll
       for (int u = 0; u < DPW; ++u)
         __builtin_amdgcn_raw_ptr_buffer_load_lds(srs, Sl + (size_t)buf * CHUNK_BYTES + dma_dst[u], 16,
-                                                 (unsigned)dma_src[u] * 2u, ch * KC * 2, 0, 0);
+                                                 (unsigned)dma_src[u] * 2u, ch * KC * 2, 0, AUX_SC1);
     };
     // this lane's fragments of chunk ch (in buffer buf) into registers
     auto load_frags = [&](AT (&fa)[KSTEPS][2], bf16x8 (&fb)[KSTEPS][2], int ch, int buf) {
@@ -533,13 +339,6 @@ constexpr int XRB_NB = 16;                     // spin chunk buffers in LDS (one
 constexpr int XRB_GB = 3;                      // loaded chunks per workgroup barrier (and per batch of loads)
 constexpr int XRB_CHB = XRB_RG * XRB_KC * 2;   // bytes of one chunk: 32 replicas x 128 k, BF16
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-
-template <class F, int... I>
-__device__ __forceinline__ void static_for(F&& f, std::integer_sequence<int, I...>) {
-  (f(std::integral_constant<int, I>{}), ...);
-}
-
 // Output layout of v_mfma_f32_32x32x16_bf16: lane l holds column l % 32 and, in accumulator
 // element i, row 8 (i / 4) + 4 (l / 32) + i % 4: four quads of consecutive rows, each the four
 // Gaussians of one Philox call.
@@ -564,6 +363,7 @@ __global__ __launch_bounds__(256, 1) void anneal_xrj(AnnealArgs a, XcdArgs x) {
 
   const XcdSlot slot = xcd_register(x, tid);
   const unsigned my_group = slot.my_group;
+  if (my_group >= (unsigned)x.groups) return;  // beyond the launch's groups
   const int group = (int)my_group + x.group_base;
   const int rb = slot.rb;
   const bool xcd_mode = slot.xcd_mode;
@@ -708,7 +508,7 @@ __global__ __launch_bounds__(256, 1) void anneal_xrj(AnnealArgs a, XcdArgs x) {
 #pragma unroll
       for (int u = 0; u < DPW; ++u)
         __builtin_amdgcn_raw_ptr_buffer_load_lds(srs, ring + wb + buf * CHB + u * 1024, 16, dma_off[u],
-                                                 ch * 2 * XRB_KC, 0, 0);
+                                                 ch * 2 * XRB_KC, 0, AUX_SC1);
     };
     bf16x8 fb[D + 1];  // [register set]: the spins of one 16-k step
     auto load = [&](int sidx) {
@@ -903,6 +703,7 @@ __global__ __launch_bounds__(256, 1) void anneal_xrj8(AnnealArgs a, XcdArgs x) {
 
   const XcdSlot slot = xcd_register(x, tid);
   const unsigned my_group = slot.my_group;
+  if (my_group >= (unsigned)x.groups) return;  // beyond the launch's groups
   const int group = (int)my_group + x.group_base;
   const int rb = slot.rb;
   const bool xcd_mode = slot.xcd_mode;
@@ -1030,7 +831,7 @@ __global__ __launch_bounds__(256, 1) void anneal_xrj8(AnnealArgs a, XcdArgs x) {
       if (ch >= NC) ch -= NC;
       int wb = 1024 * wave;  // LDS destination from an opaque per-wave base (no scalar register per address)
       asm volatile("" : "+s"(wb));
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(srs, ring + wb + buf * CHB, 16, dma_off, ch * XR8_KC, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(srs, ring + wb + buf * CHB, 16, dma_off, ch * XR8_KC, 0, AUX_SC1);
     };
     i32x8 fb[2][CT];  // [register set][column tile]: the spins of one 128-k chunk
     auto load = [&](int i) {
@@ -1230,8 +1031,8 @@ int xcd_pick_buffers(size_t room) {
 // ends in the bounded registration wait with an error rather than hanging. An ordinary launch is
 // used rather than the cooperative-launch API, under which the ROCm profiler cannot trace the
 // process.
-static hipError_t launch_resident(const void* fn, int grid, int block, size_t lds, const AnnealArgs& a,
-                                  const XcdArgs& x, hipStream_t st) {
+hipError_t launch_group_resident(const void* fn, int grid, int block, size_t lds, const AnnealArgs& a,
+                                 const XcdArgs& x, hipStream_t st) {
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
   int per_cu = 0, cus = 0, dev = 0;
@@ -1259,10 +1060,10 @@ static const void* xrj8_fn(int Kp) {
   }
 }
 
-hipError_t launch_anneal_xrj8(const AnnealArgs& a, const XcdArgs& x, int groups, hipStream_t st) {
+hipError_t launch_anneal_xrj8(const AnnealArgs& a, const XcdArgs& x, int grid, hipStream_t st) {
   const void* fn = xrj8_fn(a.Kp);
   if (!fn) return hipErrorInvalidValue;
-  return launch_resident(fn, groups * x.P, 256, (size_t)XR8_NB * XR8_CHB, a, x, st);
+  return launch_group_resident(fn, grid, 256, (size_t)XR8_NB * XR8_CHB, a, x, st);
 }
 
 static const void* xrj_fn(int Kp) {
@@ -1278,17 +1079,17 @@ static const void* xrj_fn(int Kp) {
   }
 }
 
-hipError_t launch_anneal_xrj(const AnnealArgs& a, const XcdArgs& x, int groups, hipStream_t st) {
+hipError_t launch_anneal_xrj(const AnnealArgs& a, const XcdArgs& x, int grid, hipStream_t st) {
   const void* fn = xrj_fn(a.Kp);
   if (!fn) return hipErrorInvalidValue;
-  return launch_resident(fn, groups * x.P, 256, (size_t)XRB_NB * XRB_CHB, a, x, st);
+  return launch_group_resident(fn, grid, 256, (size_t)XRB_NB * XRB_CHB, a, x, st);
 }
 
-hipError_t launch_anneal_xcd(int jfmt, const AnnealArgs& a, const XcdArgs& x, int groups, hipStream_t st) {
+hipError_t launch_anneal_xcd(int jfmt, const AnnealArgs& a, const XcdArgs& x, int grid, hipStream_t st) {
   const size_t lds = xcd_j_lds_bytes(jfmt, a.Kp) + (size_t)x.nbuf * xcd_chunk_bytes();
   const void* fn = jfmt == 0 ? xcd_fn<0>(x.nbuf) : (jfmt == 1 ? xcd_fn<1>(x.nbuf) : xcd_fn<2>(x.nbuf));
   if (!fn) return hipErrorInvalidValue;
-  return launch_resident(fn, groups * x.P, 512, lds, a, x, st);
+  return launch_group_resident(fn, grid, 512, lds, a, x, st);
 }
 
 }  // namespace nmfa
