@@ -187,6 +187,8 @@ static void free_run_buffers(nmfa_ctx* c) {
   (void)hipFree(c->d_Eint);
   (void)hipFree(c->d_Sp);
   (void)hipFree(c->d_E2);
+  (void)hipFree(c->d_Ep);
+  c->d_Ep = nullptr;
   c->d_Sp = nullptr;
   c->d_E2 = nullptr;
   (void)hipFree(c->d_S[0]);
@@ -655,6 +657,8 @@ static int ensure_run_buffers(nmfa_ctx* c, int R) {
     if (c->d_J8) {
       HIP_TRY(hipMalloc(&c->d_Sp, round_up(R, 64) * (size_t)c->Np8));
       HIP_TRY(hipMalloc(&c->d_E2, (size_t)R * 8));
+    } else {
+      HIP_TRY(hipMalloc(&c->d_Ep, energy_f64_part(c->n) * R * 8));
     }
     c->cap_R = R;
     c->state_valid = false;
@@ -771,8 +775,8 @@ int ctx_finish_run(nmfa_ctx* c, hipStream_t st) {
     HIP_TRY(launch_energy_i8(c->d_J8, c->Np8, c->d_h, c->h_integral ? 1 : 0, c->d_spins, c->n, c->R, c->d_Sp,
                              c->d_E2, c->d_Eint, c->d_E, st));
   else
-    HIP_TRY(launch_energy(nullptr, c->d_J64, c->d_h, c->exact_int ? 1 : 0, c->d_spins, c->n, c->R, c->d_Eint, c->d_E,
-                          st));
+    HIP_TRY(launch_energy_f64(c->d_J64, c->d_h, c->exact_int ? 1 : 0, c->d_spins, c->n, c->R, c->d_Ep, c->d_Eint,
+                              c->d_E, st));
   HIP_TRY(hipEventRecord(c->ev1, st));
   c->timed = true;
   c->state_valid = true;
@@ -1015,18 +1019,20 @@ extern "C" int nmfa_energies_of(nmfa_ctx* c, int32_t R, const int8_t* spins, dou
   long long* d_Ei = nullptr;
   int8_t* d_Sp = nullptr;
   unsigned long long* d_E2 = nullptr;
+  double* d_Ep = nullptr;
   const size_t cnt = (size_t)R * c->n;
   hipError_t e = hipMalloc(&d_s, cnt);
   if (e == hipSuccess) e = hipMalloc(&d_E, (size_t)R * 8);
   if (e == hipSuccess) e = hipMalloc(&d_Ei, (size_t)R * 8);
   if (e == hipSuccess && c->d_J8) e = hipMalloc(&d_Sp, round_up(R, 64) * (size_t)c->Np8);
   if (e == hipSuccess && c->d_J8) e = hipMalloc(&d_E2, (size_t)R * 8);
+  if (e == hipSuccess && !c->d_J8) e = hipMalloc(&d_Ep, energy_f64_part(c->n) * R * 8);
   if (e == hipSuccess) e = hipMemcpy(d_s, spins, cnt, hipMemcpyHostToDevice);
   if (e == hipSuccess) {
     if (c->d_J8)
       e = launch_energy_i8(c->d_J8, c->Np8, c->d_h, c->h_integral ? 1 : 0, d_s, c->n, R, d_Sp, d_E2, d_Ei, d_E, 0);
     else
-      e = launch_energy(nullptr, c->d_J64, c->d_h, c->exact_int ? 1 : 0, d_s, c->n, R, d_Ei, d_E, 0);
+      e = launch_energy_f64(c->d_J64, c->d_h, c->exact_int ? 1 : 0, d_s, c->n, R, d_Ep, d_Ei, d_E, 0);
   }
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (e == hipSuccess) e = hipMemcpy(E, d_E, (size_t)R * 8, hipMemcpyDeviceToHost);
@@ -1039,6 +1045,7 @@ extern "C" int nmfa_energies_of(nmfa_ctx* c, int32_t R, const int8_t* spins, dou
   (void)hipFree(d_Ei);
   (void)hipFree(d_Sp);
   (void)hipFree(d_E2);
+  (void)hipFree(d_Ep);
   if (e != hipSuccess) return fail(NMFA_EDEVICE, "nmfa_energies_of: %s", hipGetErrorString(e));
   return NMFA_OK;
 }

@@ -63,6 +63,7 @@ struct nmfa_ctx {
   long long* d_Eint = nullptr;
   int8_t* d_Sp = nullptr;    // energy scratch: padded signs [roundup(R, 64)][Np8]
   unsigned long long* d_E2 = nullptr;  // energy scratch [R]
+  double* d_Ep = nullptr;    // energy scratch with FP64 couplings: [energy_f64_part(n)][R]
   void* d_S[2] = {nullptr, nullptr};  // paths 1 and 2: [Rp][Ks] op_t
   int cap_Rp = 0;
   void* d_traj = nullptr;

@@ -82,10 +82,12 @@ hipError_t launch_anneal_step(int prec, int jfmt, const AnnealArgs& a, const voi
 hipError_t launch_pack_state(int prec, const void* state, void* S, int N, int R, int Kp, int ld, int Rp, int zero,
                              hipStream_t st);
 hipError_t launch_readout(int prec, const void* state, int8_t* spins, size_t count, hipStream_t st);
-// With J8: h_integral tells whether h is integral (then E_int is exact). With J64 instead: h_integral
-// = 1 states that J and h are integral and every sum fits in 2^53, so E_int is exact; else E_int = 0.
-hipError_t launch_energy(const int8_t* J8, const double* J64, const double* h, int h_integral,
-                         const int8_t* spins, int N, int R, long long* E_int, double* E, hipStream_t st);
+// Energies of Eq. 1 from FP64 couplings J64 [N][N]. exact: J and h are integral and every sum fits in
+// 2^53, so that E_int is exact; else E_int = 0. part: scratch of energy_f64_part(N) * R doubles, or
+// null (slower, the same bits).
+size_t energy_f64_part(int N);
+hipError_t launch_energy_f64(const double* J64, const double* h, int exact, const int8_t* spins, int N, int R,
+                             double* part, long long* E_int, double* E, hipStream_t st);
 // Sparse couplings in ELL form (D entries per row, ascending columns, zero-weight padding; values
 // in the accumulation type of prec: FP64 for PREC_FP64, else FP32); RB replicas per workgroup.
 // allow_rq: use the register-ELL kernel where it applies; *used_rq (if not null) tells whether it ran.

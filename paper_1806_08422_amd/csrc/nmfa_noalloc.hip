@@ -68,8 +68,8 @@ extern "C" int nmfa_energies_of_noalloc(nmfa_ctx* c, int32_t R, const int8_t* d_
                                  reinterpret_cast<unsigned long long*>(base + sp_bytes),
                                  reinterpret_cast<long long*>(d_E_int), d_E, st);
   } else if (e == hipSuccess) {
-    e = nmfa::launch_energy(nullptr, c->d_J64, c->d_h, c->exact_int ? 1 : 0, d_spins, c->n, R,
-                            reinterpret_cast<long long*>(d_E_int), d_E, st);
+    e = nmfa::launch_energy_f64(c->d_J64, c->d_h, c->exact_int ? 1 : 0, d_spins, c->n, R, nullptr,
+                                reinterpret_cast<long long*>(d_E_int), d_E, st);
   }
   // energies that are not exact integers are reported as 0, as nmfa_energies_of does
   if (e == hipSuccess && d_E_int && !c->exact_int)
