@@ -42,10 +42,33 @@ struct Philox4 {
   uint32_t x0, x1, x2, x3;
 };
 
+// The first two rounds: with a loop-invariant quad (c0) and a wave-uniform iteration and key, half of
+// each round is loop-invariant or scalar. PHILOX_LOOP writes those XORs so that the compiler can keep
+// them there (three-input XORs run on the vector unit), PHILOX_LOOP_R does the same for a wave-uniform
+// replica too; PHILOX_PLAIN is the fewest vector instructions where nothing is hoisted (the register-J
+// kernels, which have no registers for invariants).
+enum : int { PHILOX_PLAIN = 0, PHILOX_LOOP = 1, PHILOX_LOOP_R = 2 };
+
+template <int MODE = PHILOX_PLAIN>
 __device__ __forceinline__ Philox4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
                                                  uint32_t k0, uint32_t k1) {
 #pragma unroll
-  for (int round = 0; round < 10; ++round) {
+  for (int round = 0; round < (MODE == PHILOX_PLAIN ? 0 : 2); ++round) {
+    const uint64_t p0 = (uint64_t)0xD2511F53u * (uint64_t)c0;
+    const uint64_t p1 = (uint64_t)0xCD9E8D57u * (uint64_t)c2;
+    const uint32_t h0 = (uint32_t)(p0 >> 32), h1 = (uint32_t)(p1 >> 32);
+    const uint32_t n0 = round == 0 ? (h1 ^ k0) ^ c1 : (c1 ^ k0) ^ h1;
+    const uint32_t n2 = round == 0 || MODE == PHILOX_LOOP_R ? (h0 ^ k1) ^ c3
+                                                            : __builtin_amdgcn_bitop3_b32(h0, c3, k1, 0x96);
+    c1 = (uint32_t)p1;
+    c3 = (uint32_t)p0;
+    c0 = n0;
+    c2 = n2;
+    k0 += 0x9E3779B9u;
+    k1 += 0xBB67AE85u;
+  }
+#pragma unroll
+  for (int round = MODE == PHILOX_PLAIN ? 0 : 2; round < 10; ++round) {
     const uint64_t p0 = (uint64_t)0xD2511F53u * (uint64_t)c0;
     const uint64_t p1 = (uint64_t)0xCD9E8D57u * (uint64_t)c2;
     // three-input XOR in one instruction (v_bitop3_b32 with truth table 0x96)
@@ -81,21 +104,19 @@ __device__ __forceinline__ void sigma_gauss4_f32(const Philox4& w, float neg2ln2
 
 // Gaussian noise, FP64 validation path: u = (x + 1/2) 2^-32 exactly, z = sqrt(-2 ln u0) cos(2 pi u1)
 // and sin(2 pi u1) with the device math library; the caller multiplies by sigma.
-__device__ __forceinline__ void gauss4_f64(const Philox4& w, double z[4]) {
+__device__ __forceinline__ void gauss2_f64(uint32_t x0, uint32_t x1, double& zc, double& zs) {
   const double two_pi = 6.283185307179586476925286766559;
-  const double u0 = ((double)w.x0 + 0.5) * 0x1p-32;
-  const double u1 = ((double)w.x1 + 0.5) * 0x1p-32;
-  const double u2 = ((double)w.x2 + 0.5) * 0x1p-32;
-  const double u3 = ((double)w.x3 + 0.5) * 0x1p-32;
-  const double rho0 = sqrt(-2.0 * log(u0));
-  const double rho1 = sqrt(-2.0 * log(u2));
+  const double u0 = ((double)x0 + 0.5) * 0x1p-32;
+  const double u1 = ((double)x1 + 0.5) * 0x1p-32;
+  const double rho = sqrt(-2.0 * log(u0));
   double s, c;
   sincos(two_pi * u1, &s, &c);
-  z[0] = rho0 * c;
-  z[1] = rho0 * s;
-  sincos(two_pi * u3, &s, &c);
-  z[2] = rho1 * c;
-  z[3] = rho1 * s;
+  zc = rho * c;
+  zs = rho * s;
+}
+__device__ __forceinline__ void gauss4_f64(const Philox4& w, double z[4]) {
+  gauss2_f64(w.x0, w.x1, z[0], z[1]);
+  gauss2_f64(w.x2, w.x3, z[2], z[3]);
 }
 
 // -tanh(y) with e = exp(2y) computed as 2^(y * 2 log2 e); the caller passes a = 2 log2(e) * y.

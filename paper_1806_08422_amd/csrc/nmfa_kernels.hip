@@ -11,8 +11,8 @@
 //
 // Kernels:
 //   anneal_small<P>   persistent: one workgroup owns 16 replicas and all N <= 256 spins for the
-//                     whole anneal. J sits in LDS, the operand copy of S is double-buffered in
-//                     LDS, the master state lives in registers; one barrier per iteration.
+//                     whole anneal. J and the master state live in registers, the operand copy
+//                     of S is double-buffered in LDS; one barrier per iteration.
 //   anneal_step_tiled, anneal_step_tiled_f
 //                     one iteration for large N as a tiled matrix product through LDS (BF16
 //                     operands on 256 x 128 workgroup tiles; FP64 and FP32 on 128 x 64, 64 x 64 or
@@ -22,6 +22,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "nmfa_device.h"
 #include "nmfa_internal.h"
@@ -32,48 +33,86 @@ namespace nmfa {
 // Shared epilogue: from the accumulated field of four consecutive rows of one replica to the
 // updated master state. acc[v] = sum_j J_ij s_j for row i = row0 + v.
 // ------------------------------------------------------------------------------------------
+template <bool B>
+struct StBool {
+  static constexpr bool value = B;
+};
+
 template <int P>
 struct Epilogue;
 
 template <>
 struct Epilogue<PREC_FP64> {
-  __device__ static __forceinline__ void apply(const double acc[4], const double inv[4],
-                                               const double h[4], double s[4], const AnnealArgs& a,
-                                               double coef_t, uint32_t q, uint32_t r, uint32_t t) {
+  // sigma z, with the sign of the noise test hook
+  template <int MODE = PHILOX_PLAIN>
+  __device__ static __forceinline__ void noise(double z[4], const AnnealArgs& a, uint32_t q, uint32_t r, uint32_t t) {
+#pragma clang fp contract(off)
+    gauss4_f64(philox4x32_10<MODE>(q, r, t, 0u, a.key0, a.key1), z);
+    const double sg = a.negate_noise ? -a.sigma : a.sigma;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) z[v] = sg * z[v];
+  }
+  // the same for one half of the quad (z[0..1] of rows 2 half, 2 half + 1)
+  __device__ static __forceinline__ void noise_half(double z[2], const AnnealArgs& a, uint32_t q, uint32_t r,
+                                                    uint32_t t, int half) {
+#pragma clang fp contract(off)
+    const Philox4 w = philox4x32_10<PHILOX_LOOP>(q, r, t, 0u, a.key0, a.key1);
+    gauss2_f64(half ? w.x2 : w.x0, half ? w.x3 : w.x1, z[0], z[1]);
+    const double sg = a.negate_noise ? -a.sigma : a.sigma;
+    z[0] = sg * z[0];
+    z[1] = sg * z[1];
+  }
+  template <int NV>
+  __device__ static __forceinline__ void update(const double* acc, const double* inv, const double* h, double* s,
+                                                const double* z, const AnnealArgs& a, double coef_t) {
     // every operation rounded on its own (no contraction into FMAs), so that all kernels that
     // share this epilogue round alike, whatever the surrounding code lets the compiler fuse
 #pragma clang fp contract(off)
-    double z[4];
-    gauss4_f64(philox4x32_10(q, r, t, 0u, a.key0, a.key1), z);
-    const double sg = a.negate_noise ? -a.sigma : a.sigma;
     const double oma = 1.0 - a.alpha;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const double phi = (h[v] + acc[v]) * inv[v] + sg * z[v];
+    for (int v = 0; v < NV; ++v) {
+      const double phi = (h[v] + acc[v]) * inv[v] + z[v];
       const double s_hat = -tanh(phi * coef_t);
       s[v] = a.alpha * s_hat + oma * s[v];
     }
+  }
+  template <int MODE = PHILOX_PLAIN>
+  __device__ static __forceinline__ void apply(const double acc[4], const double inv[4], const double h[4],
+                                               double s[4], const AnnealArgs& a, double coef_t, uint32_t q,
+                                               uint32_t r, uint32_t t) {
+    double z[4];
+    noise<MODE>(z, a, q, r, t);
+    update<4>(acc, inv, h, s, z, a, coef_t);
   }
 };
 
 template <int P>
 struct EpilogueF32 {
-  __device__ static __forceinline__ void apply(const float acc[4], const float inv[4],
-                                               const float hinv[4], float s[4], const AnnealArgs& a,
-                                               float coef_t, uint32_t q, uint32_t r, uint32_t t) {
-    float z[4];
+  template <int MODE = PHILOX_PLAIN>
+  __device__ static __forceinline__ void noise(float z[4], const AnnealArgs& a, uint32_t q, uint32_t r, uint32_t t) {
     const float sg = (float)a.sigma;
-    sigma_gauss4_f32(philox4x32_10(q, r, t, 0u, a.key0, a.key1), -2.0f * 0.6931471805599453f * sg * sg,
-                     z);
+    sigma_gauss4_f32(philox4x32_10<MODE>(q, r, t, 0u, a.key0, a.key1), -2.0f * 0.6931471805599453f * sg * sg, z);
+  }
+  template <int NV>
+  __device__ static __forceinline__ void update(const float* acc, const float* inv, const float* hinv, float* s,
+                                                const float* z, const AnnealArgs& a, float coef_t) {
     const float alpha = (float)a.alpha;
     const float oma = (float)(1.0 - a.alpha);
+    const float sgn = a.negate_noise ? -1.0f : 1.0f;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
+    for (int v = 0; v < NV; ++v) {
       const float x = fmaf(acc[v], inv[v], hinv[v]);
-      const float phi = a.negate_noise ? x - z[v] : x + z[v];
+      const float phi = fmaf(z[v], sgn, x);  // x + z or x - z exactly rounded, in one instruction
       const float s_hat = neg_tanh_from_exp2_arg(phi * coef_t);
       s[v] = fmaf(alpha, s_hat, oma * s[v]);
     }
+  }
+  template <int MODE = PHILOX_PLAIN>
+  __device__ static __forceinline__ void apply(const float acc[4], const float inv[4], const float hinv[4], float s[4],
+                                               const AnnealArgs& a, float coef_t, uint32_t q, uint32_t r, uint32_t t) {
+    float z[4];
+    noise<MODE>(z, a, q, r, t);
+    update<4>(acc, inv, hinv, s, z, a, coef_t);
   }
 };
 template <>
@@ -82,137 +121,167 @@ template <>
 struct Epilogue<PREC_BF16> : EpilogueF32<PREC_BF16> {};
 
 // ------------------------------------------------------------------------------------------
-// anneal_small<P, J8>: see the file header. Block = 64 * (Mp/16) threads, wave w owns rows
-// [16w, 16w+16); grid = ceil(R / 16) workgroups, workgroup b owns replicas [16b, 16b+16).
-// LDS: Js[Mp][js] (op_t), Ss[2][16][js] (op_t), with js = padded row stride in elements.
-// J8: the global copy of J is FP8 e4m3 and is widened to BF16 while it is staged into LDS.
+// anneal_small<P, J8, NK, SPLIT>: see the file header. Wave w owns rows [16w, 16w+16) (FP64 with
+// SPLIT > 1: SPLIT waves share a tile's rows, see the launcher); grid = ceil(R / 16) workgroups,
+// workgroup b owns replicas [16b, 16b+16). Each lane keeps its part of J in registers (NK reads of 16
+// bytes; J8: FP8 E4M3 in memory, widened to BF16). LDS: Ss[2][16][js] (op_t), js = padded row stride in
+// elements. The iterations are unrolled by two, so that the buffers' addresses are constants.
 // The body is shared with anneal_small_batched, where one launch carries replica blocks of many
 // jobs (serving): a workgroup may then have more waves than its job has row tiles, and the extra
 // waves only take part in the barriers.
+// What bounds it: the vector instructions, about 120 per wave and iteration, most of them the noise
+// (BF16, N = 100, R = 16384: 28 waves per CU, 593 cycles per wave and iteration; five or seven
+// waves per SIMD make no difference); FP32: the chain of 16x16x4 products (32 cycles each) beside it.
+// Against J in LDS, a rolled k loop and buffer addresses multiplied out in every iteration, per
+// iteration: BF16 N = 100, R = 16384 1.94 -> 1.73 us, N = 173, R = 64 1.09 -> 0.70, N = 256, R = 1024
+// 1.55 -> 0.97; FP32 N = 100, R = 4096 1.42 -> 1.35; FP64 N = 20, R = 256 2.73 -> 1.48. Scheduling the
+// FP32 noise between the products (1.41) or drawing it after them in every second wave gained nothing.
 // ------------------------------------------------------------------------------------------
-template <int P, bool J8>
+template <int P, bool J8, int NK, int SPLIT = 1>
 __device__ __forceinline__ void anneal_small_body(const AnnealArgs& a, const int rblock) {
+  static_assert(SPLIT == 1 || P == PREC_FP64, "split tiles are built for FP64");
+  constexpr int NV = 4 / SPLIT;  // rows of a lane's quad that its wave updates
   using Tr = Traits<P>;
   using op_t = typename Tr::op_t;
   using acc_t = typename Tr::acc_t;
   using frag_t = typename Tr::frag_t;
   using acc4_t = typename Tr::acc4_t;
   constexpr int KW = Tr::KW;
-  constexpr int VEC = 16 / (KW * (int)sizeof(op_t));  // MFMA steps per 16-byte LDS read
+  constexpr int EPC = 16 / (int)sizeof(op_t);  // elements per 16-byte read
+  constexpr int VEC = EPC / KW;                // MFMA steps per 16-byte read
 
   extern __shared__ __align__(16) unsigned char smem[];
   const int N = a.N, Mp = a.Mp, Kp = a.Kp, js = a.lds_stride;
-  op_t* Js = reinterpret_cast<op_t*>(smem);
-  op_t* Ss = Js + (size_t)Mp * js;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = tid >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4;
   const int c = lane & 15;
   const int r = rblock * 16 + c;       // replica of this lane
-  const bool act = wave < (Mp >> 4);   // this wave owns a row tile of the job
-  const int row0 = wave * 16 + 4 * g;  // first of this lane's four rows (accumulator layout)
-  const int arow = wave * 16 + Tr::a_row(c);  // row this lane supplies to the A operand
+  const int tile = wave / SPLIT, part = wave % SPLIT;
+  const bool act = tile < (Mp >> 4);  // this wave owns (its part of) a row tile of the job
+  const int quad0 = tile * 16 + 4 * g;    // first of this lane's four rows (accumulator layout)
+  const int row0 = quad0 + NV * part;     // first of the rows this wave updates
+  const int arow = tile * 16 + Tr::a_row(c);  // row this lane supplies to the A operand
   const int Kq = Kp >> 2;
 
-  // ---- stage J into LDS (16-byte chunks), zero both S buffers --------------------------------
   {
-    const int chunks_per_row = (Kp * (int)sizeof(op_t)) / 16;
-    const int total = Mp * chunks_per_row;
-    for (int ch = tid; ch < total; ch += blockDim.x) {
-      const int row = ch / chunks_per_row;
-      const int cc = ch - row * chunks_per_row;
-      uint4 v;
-      if constexpr (J8) {
-        const uint8_t* src = reinterpret_cast<const uint8_t*>(a.J) + (size_t)row * Kp + cc * 8;
-        const uint2 raw = *reinterpret_cast<const uint2*>(src);
-        __bf16 w[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const uint32_t byte = ((k < 4 ? raw.x : raw.y) >> (8 * (k & 3))) & 0xffu;
-          w[k] = (__bf16)fp8e4m3_to_float(byte);
-        }
-        v = *reinterpret_cast<const uint4*>(w);
-      } else {
-        v = reinterpret_cast<const uint4*>(a.J)[(size_t)row * chunks_per_row + cc];
-      }
-      *reinterpret_cast<uint4*>(reinterpret_cast<unsigned char*>(Js + (size_t)row * js) + cc * 16) = v;
-    }
+    uint32_t* Sw = reinterpret_cast<uint32_t*>(smem);
     const int s_words = (2 * 16 * js * (int)sizeof(op_t)) / 4;
-    uint32_t* Sw = reinterpret_cast<uint32_t*>(Ss);
     for (int k = tid; k < s_words; k += blockDim.x) Sw[k] = 0u;
   }
+  __syncthreads();
+  if (!act) {  // spare wave of a batched launch: only the barriers
+    for (int t = a.t_begin; t <= a.t_end; ++t) __syncthreads();
+    return;
+  }
 
-  // ---- per-lane constants and initial state ----------------------------------------------
-  acc_t inv[4], hv[4], s[4];
+  // ---- this lane's part of J, its constants and initial state -------------------------------
+  uint4 jr[NK];
+#pragma unroll
+  for (int m = 0; m < NK; ++m) {
+    const size_t off = (size_t)arow * Kp + g * Kq + m * EPC;
+    if constexpr (J8) {
+      const uint2 raw = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint8_t*>(a.J) + off);
+      __bf16 w[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        w[k] = (__bf16)fp8e4m3_to_float(((k < 4 ? raw.x : raw.y) >> (8 * (k & 3))) & 0xffu);
+      jr[m] = *reinterpret_cast<const uint4*>(w);
+    } else {
+      jr[m] = *reinterpret_cast<const uint4*>(reinterpret_cast<const op_t*>(a.J) + off);
+    }
+  }
+  acc_t inv[NV], hv[NV], s[NV];
   const acc_t* inv_g = reinterpret_cast<const acc_t*>(a.inv_norm);
   const acc_t* h_g = reinterpret_cast<const acc_t*>(a.hterm);
   acc_t* state = reinterpret_cast<acc_t*>(a.state);
-  const bool live_r = act && r < a.R;
+  const bool live_r = r < a.R;
+  op_t* Sl = reinterpret_cast<op_t*>(smem) + (size_t)c * js;  // this lane's replica, buffer 0
+  const int sbuf = 16 * js;                                   // elements of one buffer
 #pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    inv[v] = act ? inv_g[row0 + v] : (acc_t)0;
-    hv[v] = act ? h_g[row0 + v] : (acc_t)0;
+  for (int v = 0; v < NV; ++v) {
+    // rows beyond N: a field that no 1 / T, however large, turns into a NaN (0 x NaN would spread it)
+    inv[v] = (row0 + v) < N ? inv_g[row0 + v] : (acc_t)1;
+    hv[v] = (row0 + v) < N ? h_g[row0 + v] : (acc_t)1;
     const bool live = live_r && (row0 + v) < N;
     s[v] = (a.load_state && live) ? state[(size_t)r * N + row0 + v] : (acc_t)0;
+    Sl[row0 + v] = (op_t)s[v];
   }
-  __syncthreads();
-  if (a.load_state && act) {
-#pragma unroll
-    for (int v = 0; v < 4; ++v) Ss[(size_t)c * js + row0 + v] = (op_t)s[v];
-  }
-  __syncthreads();
-
   const acc_t* coef = reinterpret_cast<const acc_t*>(a.coef);
   acc_t* traj = reinterpret_cast<acc_t*>(a.traj);
-  int cur = 0;
-  for (int t = a.t_begin; t <= a.t_end; ++t) {
-    if (!act) {  // spare wave of a batched launch
-      __syncthreads();
-      continue;
+  const uint32_t q = (uint32_t)(quad0 >> 2);
+  __syncthreads();
+
+  auto draw = [&](acc_t* z, int t) {
+    if constexpr (SPLIT == 1) {
+      Epilogue<P>::template noise<PHILOX_LOOP>(z, a, q, (uint32_t)r, (uint32_t)t);
+    } else {
+      acc_t zz[2];
+      Epilogue<P>::noise_half(zz, a, q, (uint32_t)r, (uint32_t)t, SPLIT == 2 ? part : part >> 1);
+      if constexpr (SPLIT == 2) {
+        z[0] = zz[0];
+        z[1] = zz[1];
+      } else {
+        z[0] = (part & 1) ? zz[1] : zz[0];
+      }
     }
-    // ---- mean field: D = J[rows of this wave] . S[:, replicas of this block] ----------------
+  };
+  // One iteration: read the operands of buffer CUR, draw the noise while they arrive, multiply, update,
+  // write buffer 1 - CUR. Rows beyond N are updated too: the couplings to them are zero.
+  auto step = [&](auto cur_c, int t) {
+    constexpr int CUR = decltype(cur_c)::value;
+    const acc_t coef_t = coef[t - 1];
+    uint4 bv[NK];
+    const op_t* Bc = Sl + (CUR ? sbuf : 0) + g * Kq;
+#pragma unroll
+    for (int m = 0; m < NK; ++m) bv[m] = *reinterpret_cast<const uint4*>(Bc + m * EPC);
+    acc_t z[NV];
+    draw(z, t);
     acc4_t acc;
 #pragma unroll
     for (int v = 0; v < 4; ++v) acc[v] = (acc_t)0;
-    const op_t* Arow = Js + (size_t)arow * js + g * Kq;
-    const op_t* Bcol = Ss + (size_t)cur * 16 * js + (size_t)c * js + g * Kq;
-    for (int m = 0; m < Kq; m += VEC * KW) {
-      const uint4 av = *reinterpret_cast<const uint4*>(Arow + m);
-      const uint4 bv = *reinterpret_cast<const uint4*>(Bcol + m);
-      const frag_t* af = reinterpret_cast<const frag_t*>(&av);
-      const frag_t* bf = reinterpret_cast<const frag_t*>(&bv);
+#pragma unroll
+    for (int m = 0; m < NK; ++m) {
+      const frag_t* af = reinterpret_cast<const frag_t*>(&jr[m]);
+      const frag_t* bf = reinterpret_cast<const frag_t*>(&bv[m]);
 #pragma unroll
       for (int u = 0; u < VEC; ++u) acc = Tr::mfma(af[u], bf[u], acc);
     }
-    // ---- fused epilogue ------------------------------------------------------------------
-    acc_t fld[4];
+    acc_t fld[NV];
+    if constexpr (SPLIT == 1) {
 #pragma unroll
-    for (int v = 0; v < 4; ++v) fld[v] = acc[v];
-    Epilogue<P>::apply(fld, inv, hv, s, a, coef[t - 1], (uint32_t)(row0 >> 2), (uint32_t)r,
-                       (uint32_t)t);
+      for (int v = 0; v < 4; ++v) fld[v] = acc[v];
+    } else if constexpr (SPLIT == 2) {
+      fld[0] = part ? acc[2] : acc[0];
+      fld[1] = part ? acc[3] : acc[1];
+    } else {
+      fld[0] = (part & 2) ? ((part & 1) ? acc[3] : acc[2]) : ((part & 1) ? acc[1] : acc[0]);
+    }
+    Epilogue<P>::template update<NV>(fld, inv, hv, s, z, a, coef_t);
+    op_t* Sn = Sl + (CUR ? 0 : sbuf) + row0;
 #pragma unroll
-    for (int v = 0; v < 4; ++v)
-      if (row0 + v >= N) s[v] = (acc_t)0;  // padding rows stay empty
-    const int nxt = cur ^ 1;
-    op_t* Sn = Ss + (size_t)nxt * 16 * js + (size_t)c * js + row0;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) Sn[v] = (op_t)s[v];
+    for (int v = 0; v < NV; ++v) Sn[v] = (op_t)s[v];
     const int k = t - a.t_begin;
     if (traj && k < a.record && live_r) {
 #pragma unroll
-      for (int v = 0; v < 4; ++v)
+      for (int v = 0; v < NV; ++v)
         if (row0 + v < N) traj[((size_t)k * a.R + r) * N + row0 + v] = s[v];
     }
     __syncthreads();
-    cur = nxt;
+  };
+  int t = a.t_begin;
+  for (; t < a.t_end; t += 2) {
+    step(StBool<false>{}, t);
+    step(StBool<true>{}, t + 1);
   }
+  if (t == a.t_end) step(StBool<false>{}, t);
 
   // ---- final state and sign readout -------------------------------------------------------
   if (live_r) {
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
+    for (int v = 0; v < NV; ++v) {
       if (row0 + v < N) {
         state[(size_t)r * N + row0 + v] = s[v];
         if (a.spins) a.spins[(size_t)r * N + row0 + v] = (s[v] >= (acc_t)0) ? (int8_t)1 : (int8_t)-1;
@@ -221,18 +290,74 @@ __device__ __forceinline__ void anneal_small_body(const AnnealArgs& a, const int
   }
 }
 
-template <int P, bool J8>
-__global__ __launch_bounds__(1024) void anneal_small(AnnealArgs a) {
-  anneal_small_body<P, J8>(a, (int)blockIdx.x);
+// 16-byte reads per lane group and operand row: a quarter of a row of Kp elements
+template <int P>
+__host__ __device__ constexpr int small_nk(int Kp) {
+  return Kp * (int)sizeof(typename Traits<P>::op_t) / 64;
+}
+
+// Largest workgroup (Mp / 16 waves) and the waves per SIMD that the registers must leave room for
+template <int P>
+constexpr int small_threads() {
+  return P == PREC_FP64 ? 512 : (P == PREC_FP32 ? 768 : 1024);
+}
+template <int P>
+constexpr int small_min_waves(int NK) {
+  return P == PREC_FP64 ? 2 : (P == PREC_FP32 || NK > 4 ? 4 : 5);
+}
+
+template <int P, bool J8, int NK, int SPLIT>
+__global__ __launch_bounds__(small_threads<P>(), small_min_waves<P>(NK)) void anneal_small(AnnealArgs a) {
+  anneal_small_body<P, J8, NK, SPLIT>(a, (int)blockIdx.x);
+}
+
+// Calls f with the number of 16-byte reads as a compile-time constant. Kp is a multiple of 32 (BF16, at
+// most 256) or 16 (FP32, at most 176; FP64, at most 112: what the path's limit on LDS admits).
+template <int NK>
+struct StInt {
+  static constexpr int value = NK;
+};
+template <int P, class F>
+__host__ __device__ __forceinline__ bool small_dispatch(int nk, F&& f) {
+  if constexpr (P == PREC_FP64) {
+    switch (nk) {
+      case 2: f(StInt<2>{}); return true;
+      case 4: f(StInt<4>{}); return true;
+      case 6: f(StInt<6>{}); return true;
+      case 8: f(StInt<8>{}); return true;
+      case 10: f(StInt<10>{}); return true;
+      case 12: f(StInt<12>{}); return true;
+      case 14: f(StInt<14>{}); return true;
+    }
+  } else {
+    switch (nk) {
+      case 1: f(StInt<1>{}); return true;
+      case 2: f(StInt<2>{}); return true;
+      case 3: f(StInt<3>{}); return true;
+      case 4: f(StInt<4>{}); return true;
+      case 5: f(StInt<5>{}); return true;
+      case 6: f(StInt<6>{}); return true;
+      case 7: f(StInt<7>{}); return true;
+      case 8: f(StInt<8>{}); return true;
+    }
+    if constexpr (P == PREC_FP32) {
+      switch (nk) {
+        case 9: f(StInt<9>{}); return true;
+        case 10: f(StInt<10>{}); return true;
+        case 11: f(StInt<11>{}); return true;
+      }
+    }
+  }
+  return false;
 }
 
 // One launch for replica blocks of many jobs: tasks[b] = (job index, replica block).
 template <int P, bool J8>
-__global__ __launch_bounds__(1024) void anneal_small_batched(const AnnealArgs* __restrict__ jobs,
+__global__ __launch_bounds__(small_threads<P>()) void anneal_small_batched(const AnnealArgs* __restrict__ jobs,
                                                              const int2* __restrict__ tasks) {
   const int2 tk = tasks[blockIdx.x];
   const AnnealArgs a = jobs[tk.x];
-  anneal_small_body<P, J8>(a, tk.y);
+  small_dispatch<P>(small_nk<P>(a.Kp), [&](auto nk) { anneal_small_body<P, J8, decltype(nk)::value>(a, tk.y); });
 }
 
 // ------------------------------------------------------------------------------------------
@@ -371,6 +496,12 @@ __global__ __launch_bounds__(P == PREC_FP64 ? 512 : 1024) void anneal_sparse(Ann
 // epilogue) is that of anneal_sparse; a zero-weight term adds a signed zero to a sum that starts
 // at +0 and so changes nothing. Both kernels therefore give bit-identical trajectories, whatever
 // RB and whichever kernel the launcher picks.
+// What bounds it: the vector instructions, about 108 per spin quad and replica at degree 3, of which
+// the noise takes 60; hence nothing per read but the read (addresses in both buffers held in registers
+// where there is room, iterations unrolled by two), no selects for padding spins or the noise's sign,
+// and slots for the degree rather than the next power of two. Per iteration: N = 2000, R = 1024,
+// degree 3 1.98 -> 1.71 us; degree 3, N = 2000, R = 100 0.93 -> 0.61 and N = 301, R = 64 0.73 -> 0.38;
+// degree 6, N = 1000, R = 512 0.99 -> 0.85; degree 10, N = 1537, R = 256 2.20 -> 1.22.
 // ------------------------------------------------------------------------------------------
 template <typename T, int RB>
 struct alignas(sizeof(T) * RB) RepVec {
@@ -385,6 +516,9 @@ __global__ __launch_bounds__(512) void anneal_sparse_rq(AnnealArgs a, const int*
   extern __shared__ __align__(16) unsigned char smem_sp[];
   const int N = a.N, Nq = (N + 3) / 4;
   const int buf_bytes = 4 * Nq * (int)sizeof(V);
+  // With few slots the neighbours' addresses in both buffers stay in registers, so that a read needs no
+  // address arithmetic; otherwise the buffer's base is added at each read.
+  constexpr bool TWO = DM * QP <= 4;
   const acc_t* val = reinterpret_cast<const acc_t*>(ell_val);
   const acc_t* inv_g = reinterpret_cast<const acc_t*>(a.inv_norm);
   const acc_t* h_g = reinterpret_cast<const acc_t*>(a.hterm);
@@ -393,7 +527,7 @@ __global__ __launch_bounds__(512) void anneal_sparse_rq(AnnealArgs a, const int*
   acc_t* traj = reinterpret_cast<acc_t*>(a.traj);
   const int r0 = blockIdx.x * RB;
 
-  int off[QP][4][DM];  // byte offset of the neighbour's replica vector within a state buffer
+  int off[TWO ? 2 : 1][QP][4][DM];  // byte offset of the neighbour's replica vector (in each buffer)
   acc_t w[QP][4][DM];
   acc_t inv[QP][4], hv[QP][4], s[QP][RB][4];
 #pragma unroll
@@ -409,7 +543,11 @@ __global__ __launch_bounds__(512) void anneal_sparse_rq(AnnealArgs a, const int*
 #pragma unroll
       for (int d = 0; d < DM; ++d) {
         const bool e = live && d < D;
-        off[k][v][d] = e ? ell_col[(size_t)i * D + d] * (int)sizeof(V) : 0;
+        off[0][k][v][d] = e ? ell_col[(size_t)i * D + d] * (int)sizeof(V) : 0;
+        if constexpr (TWO) {
+          off[1][k][v][d] = off[0][k][v][d] + buf_bytes;
+          asm volatile("" : "+v"(off[1][k][v][d]));  // a register of its own
+        }
         w[k][v][d] = e ? val[(size_t)i * D + d] : (acc_t)0;
       }
 #pragma unroll
@@ -429,10 +567,11 @@ __global__ __launch_bounds__(512) void anneal_sparse_rq(AnnealArgs a, const int*
     }
   }
   __syncthreads();
-  int cur = 0;
-  for (int t = a.t_begin; t <= a.t_end; ++t) {
+  // one iteration: reads buffer CUR, writes the other. Spins beyond N are updated too: nothing reads them.
+  auto step = [&](auto cur_c, int t) {
+    const int cur = cur_c;  // a compile-time constant where the loop is unrolled twice
     const acc_t coef_t = coef[t - 1];
-    const unsigned char* sc = smem_sp + (cur ? buf_bytes : 0);
+    const unsigned char* sc = smem_sp + (cur && !TWO ? buf_bytes : 0);
     unsigned char* sn = smem_sp + (cur ? 0 : buf_bytes);
     const int k_rec = t - a.t_begin;
 #pragma unroll
@@ -448,20 +587,19 @@ __global__ __launch_bounds__(512) void anneal_sparse_rq(AnnealArgs a, const int*
       for (int v = 0; v < 4; ++v)
 #pragma unroll
         for (int d = 0; d < DM; ++d) {
-          const V x = *reinterpret_cast<const V*>(sc + off[k][v][d]);
+          const V x = *reinterpret_cast<const V*>(sc + off[TWO ? cur : 0][k][v][d]);
 #pragma unroll
           for (int rr = 0; rr < RB; ++rr) acc[rr][v] = fma_acc(w[k][v][d], x.v[rr], acc[rr][v]);
         }
 #pragma unroll
       for (int rr = 0; rr < RB; ++rr)
-        Epilogue<P>::apply(acc[rr], inv[k], hv[k], s[k][rr], a, coef_t, (uint32_t)q, (uint32_t)(r0 + rr),
-                           (uint32_t)t);
+        Epilogue<P>::template apply<PHILOX_LOOP_R>(acc[rr], inv[k], hv[k], s[k][rr], a, coef_t, (uint32_t)q,
+                                                   (uint32_t)(r0 + rr), (uint32_t)t);
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const bool live = 4 * q + v < N;
         V y;
 #pragma unroll
-        for (int rr = 0; rr < RB; ++rr) y.v[rr] = live ? s[k][rr][v] : (acc_t)0;
+        for (int rr = 0; rr < RB; ++rr) y.v[rr] = s[k][rr][v];
         *reinterpret_cast<V*>(sn + (4 * q + v) * (int)sizeof(V)) = y;
       }
       if (traj && k_rec < a.record) {
@@ -476,7 +614,16 @@ __global__ __launch_bounds__(512) void anneal_sparse_rq(AnnealArgs a, const int*
       }
     }
     __syncthreads();
-    cur ^= 1;
+  };
+  if constexpr (QP == 1) {
+    int t = a.t_begin;
+    for (; t < a.t_end; t += 2) {
+      step(std::integral_constant<int, 0>{}, t);
+      step(std::integral_constant<int, 1>{}, t + 1);
+    }
+    if (t == a.t_end) step(std::integral_constant<int, 0>{}, t);
+  } else {
+    for (int t = a.t_begin; t <= a.t_end; ++t) step((t - a.t_begin) & 1, t);
   }
 #pragma unroll
   for (int k = 0; k < QP; ++k) {
@@ -537,14 +684,36 @@ __global__ void noise_values_kernel(uint32_t key0, uint32_t key1, uint32_t t, ui
 template <int P, bool J8>
 static hipError_t launch_small_t(const AnnealArgs& a, hipStream_t st) {
   const int waves = a.Mp / 16;
-  const size_t es = (P == PREC_FP64) ? 8 : (P == PREC_FP32 ? 4 : 2);
-  const size_t lds = ((size_t)a.Mp + 32) * a.lds_stride * es;
-  hipError_t e = hipFuncSetAttribute((const void*)anneal_small<P, J8>,
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e != hipSuccess) return e;
+  const size_t lds = (size_t)2 * 16 * a.lds_stride * sizeof(typename Traits<P>::op_t);
   const int blocks = (a.R + 15) / 16;
-  hipLaunchKernelGGL((anneal_small<P, J8>), dim3(blocks), dim3(64 * waves), lds, st, a);
-  return hipGetLastError();
+  hipError_t e = hipErrorInvalidValue;
+  // FP64: while every wave of a workgroup can have a SIMD to itself, a tile's waves share its rows,
+  // each running the whole matrix product (the matrix cores are idle) and the libm epilogue of its
+  // rows only. N = 20, R = 256: 2.6 us per iteration with one wave per tile, 1.5 with two; N = 16: 2.4
+  // with one, 1.4 with two, 1.2 with four. Two waves on a SIMD gain nothing (N = 20, four waves per
+  // tile: 2.15; N = 33, two: 2.9 against 2.7), nor do several workgroups per CU (N = 20, R = 16384).
+  int dev = 0, cus = 256;
+  if (hipGetDevice(&dev) == hipSuccess)
+    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  const int split = P != PREC_FP64 || blocks > cus ? 1 : 4 / waves;
+  small_dispatch<P>(small_nk<P>(a.Kp), [&](auto nk) {
+    constexpr int NK = decltype(nk)::value;
+    if constexpr (P == PREC_FP64 && NK <= 4) {  // at most two tiles
+      if (split == 4) {
+        hipLaunchKernelGGL((anneal_small<P, J8, NK, 4>), dim3(blocks), dim3(256 * waves), lds, st, a);
+        e = hipGetLastError();
+        return;
+      }
+      if (split == 2) {
+        hipLaunchKernelGGL((anneal_small<P, J8, NK, 2>), dim3(blocks), dim3(128 * waves), lds, st, a);
+        e = hipGetLastError();
+        return;
+      }
+    }
+    hipLaunchKernelGGL((anneal_small<P, J8, NK, 1>), dim3(blocks), dim3(64 * waves), lds, st, a);
+    e = hipGetLastError();
+  });
+  return e;
 }
 
 hipError_t launch_anneal_small(int prec, const AnnealArgs& a, hipStream_t st) {
@@ -578,9 +747,16 @@ hipError_t launch_anneal_small_batched(int prec, const AnnealArgs* jobs, const i
   return hipErrorInvalidValue;
 }
 
+// Decides whether an instance takes this path (the LDS that J and both spin buffers would need; J
+// itself is held in registers).
 size_t small_lds_bytes(int prec, int Mp, int stride) {
   const size_t es = (prec == PREC_FP64) ? 8 : (prec == PREC_FP32 ? 4 : 2);
   return ((size_t)Mp + 32) * stride * es;
+}
+
+size_t small_run_lds_bytes(int prec, int stride) {
+  const size_t es = (prec == PREC_FP64) ? 8 : (prec == PREC_FP32 ? 4 : 2);
+  return (size_t)2 * 16 * stride * es;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -652,11 +828,6 @@ __device__ __forceinline__ bf16x8 tiled_widen_fp4(uint32_t w) {
   const bf16x2 p3 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(w, 1.0f, 3);
   return bf16x8{p0[0], p0[1], p1[0], p1[1], p2[0], p2[1], p3[0], p3[1]};
 }
-
-template <bool B>
-struct StBool {
-  static constexpr bool value = B;
-};
 
 template <int NV>
 __device__ __forceinline__ void step_wait_vm() {
@@ -1211,28 +1382,48 @@ size_t sparse_lds_bytes(int prec, int N, int RB) {
   return (size_t)2 * 4 * ((N + 3) / 4) * RB * (prec == PREC_FP64 ? 8 : 4);
 }
 
-// Register-ELL variants: RB replicas per thread (4, 2, 1), DM = D rounded up to 4 / 8 / 16,
-// QP quads per thread (1 up to 512 quads, 2 up to 1024), with QP * DM * (value words + 1) <= 32.
-// FP64 keeps RB <= 2, and RB = 2 only for DM = 4, QP = 1: its epilogue, unrolled over the
-// replicas, would spill otherwise.
+// Register-ELL variants: RB replicas per thread (4, 2, 1), DM = D rounded up to 3, 4, 6, 8, 10, 12 or
+// 16 (a slot beyond D costs a gather and an FMA per spin all the same), QP quads per thread (1 up to
+// 512 quads, 2 up to 1024), with QP * (D rounded up to 4, 8 or 16) * (value words + 1) <= 32. FP64
+// keeps RB <= 2, and RB = 2 only for DM <= 4, QP = 1: its epilogue, unrolled over the replicas, would
+// spill otherwise.
 template <int P, int RB>
 static const void* rq_fn_d(int DM, int QP) {
   if (QP == 1) {
-    if (DM == 4) return (const void*)anneal_sparse_rq<P, RB, 4, 1>;
-    if (DM == 8) return (const void*)anneal_sparse_rq<P, RB, 8, 1>;
-    if constexpr (P != PREC_FP64)
-      if (DM == 16) return (const void*)anneal_sparse_rq<P, RB, 16, 1>;
+    switch (DM) {
+      case 3: return (const void*)anneal_sparse_rq<P, RB, 3, 1>;
+      case 4: return (const void*)anneal_sparse_rq<P, RB, 4, 1>;
+      case 6: return (const void*)anneal_sparse_rq<P, RB, 6, 1>;
+      case 8: return (const void*)anneal_sparse_rq<P, RB, 8, 1>;
+    }
+    if constexpr (P != PREC_FP64) {
+      switch (DM) {
+        case 10: return (const void*)anneal_sparse_rq<P, RB, 10, 1>;
+        case 12: return (const void*)anneal_sparse_rq<P, RB, 12, 1>;
+        case 16: return (const void*)anneal_sparse_rq<P, RB, 16, 1>;
+      }
+    }
   } else if (QP == 2) {
-    if (DM == 4) return (const void*)anneal_sparse_rq<P, RB, 4, 2>;
-    if constexpr (P != PREC_FP64)
-      if (DM == 8) return (const void*)anneal_sparse_rq<P, RB, 8, 2>;
+    switch (DM) {
+      case 3: return (const void*)anneal_sparse_rq<P, RB, 3, 2>;
+      case 4: return (const void*)anneal_sparse_rq<P, RB, 4, 2>;
+    }
+    if constexpr (P != PREC_FP64) {
+      switch (DM) {
+        case 6: return (const void*)anneal_sparse_rq<P, RB, 6, 2>;
+        case 8: return (const void*)anneal_sparse_rq<P, RB, 8, 2>;
+      }
+    }
   }
   return nullptr;
 }
 
 static const void* rq_fn(int prec, int RB, int DM, int QP) {
   if (prec == PREC_FP64) {
-    if (RB == 2) return DM == 4 && QP == 1 ? (const void*)anneal_sparse_rq<PREC_FP64, 2, 4, 1> : nullptr;
+    if (RB == 2) {
+      if (QP != 1 || DM > 4) return nullptr;
+      return DM == 3 ? (const void*)anneal_sparse_rq<PREC_FP64, 2, 3, 1> : (const void*)anneal_sparse_rq<PREC_FP64, 2, 4, 1>;
+    }
     return RB == 1 ? rq_fn_d<PREC_FP64, 1>(DM, QP) : nullptr;
   }
   if (RB == 4) return rq_fn_d<PREC_FP32, 4>(DM, QP);
@@ -1254,8 +1445,11 @@ struct SparseRq {
 static int sparse_rq_pick(int prec, int N, int D, int R, SparseRq* o) {
   const int Nq = (N + 3) / 4;
   const int QP = Nq <= 512 ? 1 : (Nq <= 1024 ? 2 : 0);
-  const int DM = D <= 4 ? 4 : (D <= 8 ? 8 : (D <= 16 ? 16 : 0));
-  if (!QP || !DM || QP * DM * (prec == PREC_FP64 ? 3 : 2) > 32) return 0;
+  const int cls = D <= 4 ? 4 : (D <= 8 ? 8 : (D <= 16 ? 16 : 0));  // registers of the slots: the kernel's limit
+  if (!QP || !cls || QP * cls * (prec == PREC_FP64 ? 3 : 2) > 32) return 0;
+  int DM = 16;
+  for (int m : {12, 10, 8, 6, 4, 3})
+    if (D <= m) DM = m;
   int dev = 0, cus = 256, max_lds = 65536;
   if (hipGetDevice(&dev) == hipSuccess) {
     (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);

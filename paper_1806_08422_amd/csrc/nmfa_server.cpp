@@ -408,7 +408,7 @@ void enqueue_round(nmfa_server* s, Round& r) {
     r.h_args.push_back(a);
     for (int b = 0; b < (j->R + 15) / 16; ++b) r.h_tasks.push_back(make_int2(job_index, b));
     max_Mp = std::max(max_Mp, j->ctx->Mp);
-    lds = std::max(lds, small_lds_bytes(j->ctx->prec, j->ctx->Mp, j->ctx->lds_stride));
+    lds = std::max(lds, small_run_lds_bytes(j->ctx->prec, j->ctx->lds_stride));
     batched.emplace_back(j, te[k]);
   }
   if (!batched.empty()) {

@@ -126,6 +126,10 @@ __device__ __forceinline__ void xrs_body(const AnnealArgs& a, const XcdArgs& x) 
   for (int rt = 0; rt < RT; ++rt) {
     inv[rt] = reinterpret_cast<const f32x4*>(a.inv_norm)[(row0 + 16 * rt) >> 2];
     hinv[rt] = reinterpret_cast<const f32x4*>(a.hterm)[(row0 + 16 * rt) >> 2];
+    // rows beyond N: a field that no 1 / T, however large, turns into a NaN (0 x NaN would spread it)
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      if (row0 + 16 * rt + v >= N) hinv[rt][v] = 1.0f;
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) {
       const int r = rgroup0 + 16 * ct + c;
