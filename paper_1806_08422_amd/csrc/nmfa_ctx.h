@@ -4,7 +4,12 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <array>
+#include <cmath>
+#include <exception>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "../../include/nmfa.h"
@@ -106,3 +111,35 @@ int ctx_read_results(nmfa_ctx* c, double* E, int64_t* E_int, int8_t* spins);
 int ctx_finish_run(nmfa_ctx* c, hipStream_t st);
 // Record an error message for nmfa_last_error() and return code.
 int nmfa_fail(int code, const char* fmt, ...);
+
+// Integral and below 9e15 in magnitude (exact as an int64); no call into libm, which this is asked of
+// every coupling.
+inline bool is_integral(double v) { return std::fabs(v) < 9e15 && (double)(long long)v == v; }
+
+// Runs f(lo, hi) over [0, n) split into contiguous ranges of at least `least` on up to 16 host threads, the
+// last on the calling one (one range for small n, where starting threads costs more than the pass). A
+// range whose thread cannot be started runs on the calling thread too; nothing is thrown.
+template <class F>
+void parallel_rows(int n, F&& f, int least = 128) {
+  std::array<std::thread, 16> th;
+  int T = (int)std::min((unsigned)th.size(), std::max(1u, std::thread::hardware_concurrency()));
+  T = std::min(T, n / least);
+  if (T <= 1) {
+    f(0, n);
+    return;
+  }
+  for (int t = 0; t < T; ++t) {
+    const int lo = (int)((long)n * t / T), hi = (int)((long)n * (t + 1) / T);
+    if (t + 1 == T) {
+      f(lo, hi);
+      break;
+    }
+    try {
+      th[t] = std::thread([&f, lo, hi] { f(lo, hi); });
+    } catch (const std::exception&) {
+      f(lo, hi);
+    }
+  }
+  for (auto& x : th)
+    if (x.joinable()) x.join();
+}
