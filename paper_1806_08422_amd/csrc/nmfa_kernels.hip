@@ -1098,19 +1098,22 @@ __global__ __launch_bounds__(512, 1) void anneal_step_tiled(AnnealArgs a, const 
 }
 
 // ------------------------------------------------------------------------------------------
-// anneal_step_tiled_f<P, RT, CT, WM, WR>: one FP64 or FP32 iteration for large N as a tiled matrix
-// product with the fused epilogue. A workgroup of WM x WR waves owns 16 RT WM rows x 16 CT WR
-// replicas, RT x CT accumulators of 16 x 16 per wave. J [Mp][Kp] and S_cur [Rp][Kp] (k contiguous)
-// stream through an LDS ring of NS stages, 256 bytes of k per row and stage, filled by
-// direct-to-LDS loads issued NS - 1 blocks ahead. The 16-byte unit u of tile row q is stored at
-// u ^ (q & 15) of its 256-byte row, so the lanes one LDS cycle serves hit distinct bank groups (the
-// A rows of a 16-row FP64 tile are permuted as that instruction's output needs, which keeps them
-// distinct modulo 16). Which k a unit holds:
+// anneal_step_tiled_f<P, JFMT, RT, CT, WM, WR, WPC>: one FP64 or FP32 iteration for large N, or a BF16
+// one whose grid of 256 x 128 tiles would leave CUs idle, as a tiled matrix product with the fused
+// epilogue. A workgroup of WM x WR waves owns 16 RT WM rows x 16 CT WR replicas, RT x CT accumulators of
+// 16 x 16 per wave; WPC of them share a CU. J [Mp][Kp] and S_cur [Rp][Kp] (k contiguous) stream through
+// an LDS ring of NS stages, 256 bytes of k per row of S and stage, filled by direct-to-LDS loads issued
+// NS - 1 blocks ahead. The 16-byte unit u of tile row q is stored at u ^ (q & 15) of its 256-byte row, so
+// the lanes one LDS cycle serves hit distinct bank groups (the A rows of a 16-row FP64 tile are permuted
+// as that instruction's output needs, which keeps them distinct modulo 16; the 128- and 64-byte rows of
+// FP8 and FP4 J take u ^ ((q >> 1) & 7) and u ^ ((q >> 2) & 3)). Which k a unit holds:
 //   FP64  a block is 32 consecutive k, four 8-k windows of two MFMA steps; in window i, step s, lane
 //         group g carries k = 8 i + 2 g + s, so unit 4 i + g holds both steps' operands.
 //   FP32  lane group g owns the k range [g Kp/4, (g+1) Kp/4); a block is 16 consecutive k of each of
 //         the four ranges, and in window i lane group g carries k = g Kp/4 + 16 kb + 4 i + s in
 //         step s = 0..3: unit 4 g + i holds the four steps' operands.
+//   BF16  a block is 128 consecutive k; in window i lane group g carries k = 32 i + 8 g .. + 7, unit
+//         4 i + g (of FP8 / FP4 J half or a quarter of a unit, widened to BF16 in registers).
 // Each wave loads its master states before the k loop, so that their latency hides under the
 // matrix work. The order of each output's sum does not depend on the tile, so every tile size gives
 // the same results bit for bit.
@@ -1123,33 +1126,49 @@ __global__ __launch_bounds__(512, 1) void anneal_step_tiled(AnnealArgs a, const 
 // 128 x 64 with four waves; FP32 without LDS, operands straight from L2): FP64 R = 1024 226 -> 178
 // us (46.0 TFLOP/s), R = 256 212 -> 55, R = 64 214 -> 34; FP32 R = 1024 270 -> 94 us, R = 256
 // 107 -> 31, N = 777 R = 256 45 -> 12. Padding the operand rows to spread them over the L2 channels
-// changed nothing.
+// changed nothing, nor did reading three windows ahead instead of one, nor (64 x 32, FP4 J, one workgroup
+// per CU: 0.37 us per block) a ring of 8 stages instead of 5; 3 stages take 0.58 us per block (BF16 J).
 // Needs Mp % 128 == 0, Kp % 64 == 0, and S buffers of roundup(R, 64) rows (padding rows finite).
 // ------------------------------------------------------------------------------------------
-template <int P, int RT, int CT, int WM, int WR>
+template <int P, int JFMT, int RT, int CT, int WM, int WR, int WPC = 1>
 struct SfTile {
   static constexpr int TM = 16 * RT * WM;               // rows per workgroup
   static constexpr int TR = 16 * CT * WR;               // replicas per workgroup
   static constexpr int W = WM * WR;                     // waves
-  static constexpr int STAGE = (TM + TR) * 256;         // J tile + S tile of one block
+  static constexpr int JRB = 256 >> JFMT;               // bytes of a J row per block
+  static constexpr int JT = TM * JRB;                   // bytes of the J tile of one block
+  static constexpr int JB = JT / 1024;                  // 1 KB loads of it
+  static constexpr int STAGE = JT + TR * 256;           // J tile + S tile of one block
   static constexpr int LPW = STAGE / 1024 / W;          // 1 KB direct-to-LDS loads per wave and block
-  static constexpr int NS = STAGE > 40 * 1024 ? 3 : (STAGE > 24 * 1024 ? 4 : 5);  // stages of the ring
-  static constexpr int BLK = P == PREC_FP64 ? 32 : 64;  // k per block
-  static_assert(LPW * 1024 * W == STAGE && NS * STAGE <= 160 * 1024, "whole loads per wave; the ring fits in LDS");
+  static constexpr int NS_LDS = 160 * 1024 / WPC / STAGE, NS_MAX = STAGE > 24 * 1024 ? 4 : 5;
+  static constexpr int NS = NS_LDS < NS_MAX ? NS_LDS : NS_MAX;  // stages of the ring
+  static constexpr int BLK = P == PREC_FP64 ? 32 : (P == PREC_FP32 ? 64 : 128);  // k per block
+  static constexpr int JADV = P == PREC_FP32 ? 64 : JRB;  // bytes from one block to the next in a row of J,
+  static constexpr int SADV = P == PREC_FP32 ? 64 : 256;  // of S
+  // where 16-byte unit u of tile row q of J is kept: u ^ swz(q)
+  __device__ static __forceinline__ int swz(int q) {
+    return JFMT == 0 ? (q & 15) : (JFMT == 1 ? ((q >> 1) & 7) : ((q >> 2) & 3));
+  }
+  static_assert(JFMT == 0 || P == PREC_BF16, "FP8 / FP4 couplings are widened to BF16");
+  static_assert(LPW * 1024 * W == STAGE && NS >= 3, "whole loads per wave; the ring fits in LDS");
   static_assert((NS - 2) * LPW <= 63, "wait counts fit the vmcnt field");
 };
 
-template <int P, int RT, int CT, int WM, int WR>
+template <int P, int JFMT, int RT, int CT, int WM, int WR, int WPC>
 __device__ __forceinline__ void step_tiled_f_body(const AnnealArgs& a, const void* __restrict__ S_cur,
                                                   void* __restrict__ S_next_v, int t) {
   using Tr = Traits<P>;
-  using T = SfTile<P, RT, CT, WM, WR>;
-  using acc_t = typename Tr::acc_t;  // the operand type too (FP64 or FP32)
+  using T = SfTile<P, JFMT, RT, CT, WM, WR, WPC>;
+  using op_t = typename Tr::op_t;
+  using acc_t = typename Tr::acc_t;
   using acc4_t = typename Tr::acc4_t;
-  acc_t* S_next = reinterpret_cast<acc_t*>(S_next_v);
-  constexpr int ES = sizeof(acc_t), SPU = 16 / ES;  // element bytes; MFMA steps per 16-byte unit
-  constexpr int LPW = T::LPW, NS = T::NS, LA = NS - 1;
-  typedef acc_t unit_t __attribute__((ext_vector_type(SPU)));
+  using frag_t = typename Tr::frag_t;
+  op_t* S_next = reinterpret_cast<op_t*>(S_next_v);
+  constexpr int ES = sizeof(op_t), EPU = 16 / ES;  // element bytes; elements of a 16-byte unit
+  constexpr int SPU = EPU / Tr::KW;                // MFMA steps per unit
+  constexpr int LPW = T::LPW, NS = T::NS, LA = NS - 1, JRB = T::JRB, UPR = JRB / 16;
+  typedef op_t unit_t __attribute__((ext_vector_type(EPU)));
+  typedef uint32_t junit_t __attribute__((ext_vector_type(4 >> JFMT)));  // a unit's worth of J as stored
   extern __shared__ __align__(16) unsigned char smem_sf[];  // NS x (J tile, S tile)
   const int N = a.N, Kp = a.Kp;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -1158,19 +1177,20 @@ __device__ __forceinline__ void step_tiled_f_body(const AnnealArgs& a, const voi
   const int m0 = blockIdx.x * T::TM, r0 = blockIdx.y * T::TR;
   const int wm = 16 * RT * (wave / WR), wr = 16 * CT * (wave % WR);
 
-  // direct-to-LDS loads: 1 KB blocks of four tile rows, first the J tile's, then the S tile's; wave
-  // w issues blocks LPW w .. LPW w + LPW - 1. Lane l fills position l % 16 of tile row 4 b' + l / 16
-  // (b' the block within its tile) with the global unit the swizzle puts there.
+  // direct-to-LDS loads: 1 KB blocks of whole tile rows (four of S), first the J tile's, then the S
+  // tile's; wave w issues blocks LPW w .. LPW w + LPW - 1. Lane l fills position l % (units per row) of
+  // tile row (rows per block) b' + l / (units per row) (b' the block within its tile) with the global
+  // unit the swizzle puts there.
+  const size_t jrow = P == PREC_BF16 ? (size_t)Kp * JRB / T::BLK : (size_t)Kp * ES;  // bytes of a J row
   size_t goff[LPW];
 #pragma unroll
   for (int u = 0; u < LPW; ++u) {
     const int b = LPW * wave + u;
-    const bool is_j = 4 * b < T::TM;
-    const int q = 4 * (is_j ? b : b - T::TM / 4) + (lane >> 4);
-    const int unit = (lane & 15) ^ (q & 15);
-    const size_t row = is_j ? m0 + q : r0 + q;
-    const size_t k = P == PREC_FP64 ? 2 * unit : (unit >> 2) * (Kp >> 2) + 4 * (unit & 3);
-    goff[u] = (row * Kp + k) * ES;
+    const bool is_j = b < T::JB;
+    const int q = is_j ? 1024 / JRB * b + lane / UPR : 4 * (b - T::JB) + (lane >> 4);
+    const int unit = is_j ? (lane % UPR) ^ T::swz(q) : (lane & 15) ^ (q & 15);
+    const size_t k = P == PREC_FP32 ? (size_t)(unit >> 2) * Kp + 16 * (unit & 3) : 16 * unit;  // bytes (Kp / 4 words)
+    goff[u] = (is_j ? (size_t)(m0 + q) * jrow : (size_t)(r0 + q) * Kp * ES) + k;
   }
   const unsigned char* Jb = reinterpret_cast<const unsigned char*>(a.J);
   const unsigned char* Sb = reinterpret_cast<const unsigned char*>(S_cur);
@@ -1179,7 +1199,7 @@ __device__ __forceinline__ void step_tiled_f_body(const AnnealArgs& a, const voi
 #pragma unroll
     for (int u = 0; u < LPW; ++u) {
       const int b = LPW * wave + u;
-      const unsigned char* src = (4 * b < T::TM ? Jb : Sb) + goff[u] + (size_t)kb * (T::BLK / (P == PREC_FP64 ? 1 : 4)) * ES;
+      const unsigned char* src = (b < T::JB ? Jb + (size_t)kb * T::JADV : Sb + (size_t)kb * T::SADV) + goff[u];
       __builtin_amdgcn_global_load_lds(reinterpret_cast<const uint32_t*>(src), ring + stage * T::STAGE + b * 1024,
                                        16, 0, 0);
     }
@@ -1188,16 +1208,17 @@ __device__ __forceinline__ void step_tiled_f_body(const AnnealArgs& a, const voi
   int aoff[RT][4], boff[CT][4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const int unit = P == PREC_FP64 ? 4 * i + g : 4 * g + i;
+    const int unit = P == PREC_FP32 ? 4 * g + i : 4 * i + g;
+    constexpr int JPU = 1 << JFMT;  // S units that a 16-byte unit of J covers
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
       const int q = wm + 16 * rt + Tr::a_row(c);
-      aoff[rt][i] = q * 256 + ((unit ^ (q & 15)) * 16);
+      aoff[rt][i] = q * JRB + (((unit / JPU) ^ T::swz(q)) * 16) + (unit % JPU) * (16 / JPU);
     }
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) {
       const int q = wr + 16 * ct + c;
-      boff[ct][i] = T::TM * 256 + q * 256 + ((unit ^ (q & 15)) * 16);
+      boff[ct][i] = T::JT + q * 256 + ((unit ^ (q & 15)) * 16);
     }
   }
 
@@ -1226,11 +1247,12 @@ __device__ __forceinline__ void step_tiled_f_body(const AnnealArgs& a, const voi
   // The fragments of a window are read into one register set while the MFMAs of the window before
   // it run on the other, across the block boundaries too: the barrier that makes block kb + 1
   // visible stands before the last window of block kb.
-  unit_t af[2][RT], bfr[2][CT];
+  junit_t af[2][RT];
+  unit_t bfr[2][CT];
   auto load = [&](int set, int stage, int i) {
     const unsigned char* base = ring + stage * T::STAGE;
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) af[set][rt] = *reinterpret_cast<const unit_t*>(base + aoff[rt][i]);
+    for (int rt = 0; rt < RT; ++rt) af[set][rt] = *reinterpret_cast<const junit_t*>(base + aoff[rt][i]);
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) bfr[set][ct] = *reinterpret_cast<const unit_t*>(base + boff[ct][i]);
   };
@@ -1261,12 +1283,23 @@ __device__ __forceinline__ void step_tiled_f_body(const AnnealArgs& a, const voi
         load(0, nxt, 0);
       }
       __builtin_amdgcn_sched_barrier(0);  // the reads go out ahead of the MFMAs
+      unit_t aw[RT];
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) {
+        const junit_t w = af[i & 1][rt];
+        if constexpr (JFMT == 2) aw[rt] = tiled_widen_fp4(w[0]);
+        else if constexpr (JFMT == 1) aw[rt] = tiled_widen_fp8(make_uint2(w[0], w[1]));
+        else aw[rt] = __builtin_bit_cast(unit_t, w);
+      }
 #pragma unroll
       for (int s = 0; s < SPU; ++s)
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-          for (int ct = 0; ct < CT; ++ct) acc[rt][ct] = Tr::mfma(af[i & 1][rt][s], bfr[i & 1][ct][s], acc[rt][ct]);
+          for (int ct = 0; ct < CT; ++ct) {
+            if constexpr (SPU == 1) acc[rt][ct] = Tr::mfma(aw[rt], bfr[i & 1][ct], acc[rt][ct]);
+            else acc[rt][ct] = Tr::mfma(aw[rt][s], bfr[i & 1][ct][s], acc[rt][ct]);
+          }
       __builtin_amdgcn_sched_barrier(0);
     }
     cur = nxt;
@@ -1299,8 +1332,9 @@ __device__ __forceinline__ void step_tiled_f_body(const AnnealArgs& a, const voi
 #pragma unroll
       for (int v = 0; v < 4; ++v)
         if (row0 + v >= N || !live_r) s[v] = (acc_t)0;
-      acc4_t* dst = reinterpret_cast<acc4_t*>(S_next + (size_t)r * Kp + row0);
-      *dst = acc4_t{s[0], s[1], s[2], s[3]};
+      typedef op_t op4_t __attribute__((ext_vector_type(4)));
+      *reinterpret_cast<op4_t*>(S_next + (size_t)r * Kp + row0) =
+          op4_t{(op_t)s[0], (op_t)s[1], (op_t)s[2], (op_t)s[3]};
       if (live_r) {
 #pragma unroll
         for (int v = 0; v < 4; ++v)
@@ -1313,10 +1347,10 @@ __device__ __forceinline__ void step_tiled_f_body(const AnnealArgs& a, const voi
   }
 }
 
-template <int P, int RT, int CT, int WM, int WR>
-__global__ __launch_bounds__(64 * WM * WR, 2) void anneal_step_tiled_f(AnnealArgs a, const void* __restrict__ S_cur,
+template <int P, int JFMT, int RT, int CT, int WM, int WR, int WPC>
+__global__ __launch_bounds__(64 * WM * WR, WM * WR * WPC / 4) void anneal_step_tiled_f(AnnealArgs a, const void* __restrict__ S_cur,
                                                                        void* __restrict__ S_next, int t) {
-  step_tiled_f_body<P, RT, CT, WM, WR>(a, S_cur, S_next, t);
+  step_tiled_f_body<P, JFMT, RT, CT, WM, WR, WPC>(a, S_cur, S_next, t);
 }
 
 template <int JFMT>
@@ -1330,16 +1364,23 @@ static hipError_t launch_step_tiled(const AnnealArgs& a, const void* S_cur, void
   return hipGetLastError();
 }
 
-template <int P, int RT, int CT, int WM, int WR>
+template <int P, int JFMT, int RT, int CT, int WM, int WR, int WPC>
 static hipError_t launch_step_f(const AnnealArgs& a, const void* S_cur, void* S_next, int t, hipStream_t st) {
-  using T = SfTile<P, RT, CT, WM, WR>;
+  using T = SfTile<P, JFMT, RT, CT, WM, WR, WPC>;
   const size_t lds = (size_t)T::NS * T::STAGE;
-  hipError_t e = hipFuncSetAttribute((const void*)anneal_step_tiled_f<P, RT, CT, WM, WR>,
+  hipError_t e = hipFuncSetAttribute((const void*)anneal_step_tiled_f<P, JFMT, RT, CT, WM, WR, WPC>,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
   const dim3 grid(a.Mp / T::TM, (a.R + T::TR - 1) / T::TR);
-  hipLaunchKernelGGL((anneal_step_tiled_f<P, RT, CT, WM, WR>), grid, dim3(64 * T::W), lds, st, a, S_cur, S_next, t);
+  hipLaunchKernelGGL((anneal_step_tiled_f<P, JFMT, RT, CT, WM, WR, WPC>), grid, dim3(64 * T::W), lds, st, a, S_cur, S_next, t);
   return hipGetLastError();
+}
+
+static int device_cus() {
+  int dev = 0, cus = 256;
+  if (hipGetDevice(&dev) == hipSuccess)
+    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  return cus;
 }
 
 // Tile of the FP64 / FP32 iteration: 128 x 64 or 64 x 64 with eight waves, one workgroup per CU, or
@@ -1350,17 +1391,56 @@ static hipError_t launch_step_f(const AnnealArgs& a, const void* S_cur, void* S_
 // 64 x 64 and 213 with 32 x 32; 64 x 64 at R = 512; 32 x 32 at R = 256, 55 us against 89 and 158.)
 template <int P>
 static hipError_t launch_step_f_pick(const AnnealArgs& a, const void* S_cur, void* S_next, int t, hipStream_t st) {
-  int dev = 0, cus = 256;
-  if (hipGetDevice(&dev) == hipSuccess)
-    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  const int cus = device_cus();
   auto rounds = [&](int tm, int tr) {
     const long tiles = (long)(a.Mp / tm) * ((a.R + tr - 1) / tr);
     return (double)((tiles + cus - 1) / cus);
   };
   const double big = 6.2 * rounds(128, 64), mid = 3.3 * rounds(64, 64), small = 1.0 / 3 + rounds(32, 32);
-  if (big <= mid && big <= small) return launch_step_f<P, 2, 2, 4, 2>(a, S_cur, S_next, t, st);
-  if (mid <= small) return launch_step_f<P, 1, 2, 4, 2>(a, S_cur, S_next, t, st);
-  return launch_step_f<P, 1, 1, 2, 2>(a, S_cur, S_next, t, st);
+  if (big <= mid && big <= small) return launch_step_f<P, 0, 2, 2, 4, 2, 1>(a, S_cur, S_next, t, st);
+  if (mid <= small) return launch_step_f<P, 0, 1, 2, 4, 2, 1>(a, S_cur, S_next, t, st);
+  return launch_step_f<P, 0, 1, 1, 2, 2, 2>(a, S_cur, S_next, t, st);
+}
+
+// Tile of the BF16 iteration. The cost of a tile size in us, fitted to measurements at N = 2100, 4100 and
+// 8192, R = 64 .. 1024 (within 10 % of them but for a few at 2100): `once` plus, for every time the tiles
+// fill the chip, 2 us and a time per 128-k block, s1 while a CU has one workgroup and s2 with the two it
+// can hold. 64 x 32 is the least serial time for a few tiles; 128 x 32 (BF16 J: 128 x 64) and 256 x 64
+// read less per product; 256 x 128 is the best that fills the chip whole. Measured with 256 x 128 always
+// and with this rule, us per iteration: FP4 J N = 2100, R = 64 39.0 -> 10.8, R = 1024 44 -> 30; N = 4100,
+// R = 200 67 -> 19; N = 8192, R = 64 110 -> 27, R = 256 113 -> 47, R = 512 117 -> 84, R = 1024 142 (the
+// next best, 256 x 64: 165); FP8 J N = 4100, R = 200 72 -> 21, R = 512 74 -> 51; BF16 J N = 2100,
+// R = 300 45 -> 15, N = 8192, R = 64 118 -> 28, R = 256 122 -> 62, R = 512 127 -> 121, R = 1024 162 (the
+// next best, 128 x 64: 245).
+template <int JFMT>
+static hipError_t launch_step_b_pick(const AnnealArgs& a, const void* S_cur, void* S_next, int t, hipStream_t st) {
+  constexpr int P = PREC_BF16;
+  const int cus = device_cus();
+  auto cost = [&](int tm, int tr, int per_cu, double once, double s1, double s2) {
+    const long tiles = (long)(a.Mp / tm) * ((a.R + tr - 1) / tr), full = tiles / (per_cu * cus);
+    const long rest = tiles % (per_cu * cus);
+    const double nb = a.Kp / 128;
+    return once + full * (2 + s2 * nb) + (rest == 0 ? 0.0 : 2 + (rest <= cus ? s1 : s2) * nb);
+  };
+  if constexpr (JFMT == 0) {
+    if ((long)(a.Mp / 64) * ((a.R + 31) / 32) <= cus)  // a workgroup per CU: the longer ring (s1 = 0.37)
+      return launch_step_f<P, JFMT, 1, 2, 4, 1, 1>(a, S_cur, S_next, t, st);
+    const double c64 = cost(64, 32, 2, 3, 0.58, 0.65), c128 = cost(128, 64, 1, 8, 0.88, 0.88),
+                 c256 = cost(256, 128, 1, 6, 2.3, 2.3);
+    if (c64 <= c128 && c64 <= c256) return launch_step_f<P, JFMT, 1, 2, 4, 1, 2>(a, S_cur, S_next, t, st);
+    if (c128 <= c256) return launch_step_f<P, JFMT, 2, 2, 4, 2, 1>(a, S_cur, S_next, t, st);
+  } else {
+    constexpr bool F4 = JFMT == 2;
+    const double c64 = cost(64, 32, 2, 3, F4 ? 0.37 : 0.36, F4 ? 0.53 : 0.52),
+                 c128 = cost(128, 32, 2, F4 ? 4 : 5, F4 ? 0.39 : 0.5, F4 ? 0.7 : 0.85),
+                 c256s = cost(256, 64, 1, 10, F4 ? 1.1 : 1.15, F4 ? 1.1 : 1.15),
+                 c256 = cost(256, 128, 1, 6, F4 ? 2.08 : 2.15, F4 ? 2.08 : 2.15);
+    const double least = std::min(std::min(c64, c128), std::min(c256s, c256));
+    if (c64 == least) return launch_step_f<P, JFMT, 1, 2, 4, 1, 2>(a, S_cur, S_next, t, st);
+    if (c128 == least) return launch_step_f<P, JFMT, 1, 2, 8, 1, 2>(a, S_cur, S_next, t, st);
+    if (c256s == least) return launch_step_f<P, JFMT, 2, 4, 8, 1, 1>(a, S_cur, S_next, t, st);
+  }
+  return launch_step_tiled<JFMT>(a, S_cur, S_next, t, st);
 }
 
 hipError_t launch_anneal_step(int prec, int jfmt, const AnnealArgs& a, const void* S_cur, void* S_next, int t,
@@ -1371,9 +1451,9 @@ hipError_t launch_anneal_step(int prec, int jfmt, const AnnealArgs& a, const voi
     case PREC_FP32: return launch_step_f_pick<PREC_FP32>(a, S_cur, S_next, t, st);
     case PREC_BF16:
     case PREC_FP8J_BF16S:
-      if (jfmt == 2) return launch_step_tiled<2>(a, S_cur, S_next, t, st);
-      if (jfmt == 1) return launch_step_tiled<1>(a, S_cur, S_next, t, st);
-      return launch_step_tiled<0>(a, S_cur, S_next, t, st);
+      if (jfmt == 2) return launch_step_b_pick<2>(a, S_cur, S_next, t, st);
+      if (jfmt == 1) return launch_step_b_pick<1>(a, S_cur, S_next, t, st);
+      return launch_step_b_pick<0>(a, S_cur, S_next, t, st);
   }
   return hipErrorInvalidValue;
 }
