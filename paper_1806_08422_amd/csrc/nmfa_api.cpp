@@ -808,7 +808,7 @@ extern "C" int nmfa_anneal_range(nmfa_ctx* c, int32_t R, int32_t t_f, int32_t t_
 }
 
 // The tile of a group-kernel run: the large tile of the context's kernel (tile -1) or, with J in
-// registers and BF16 spins, one of the small tiles. Small tiles put more CUs on a replica (a group of
+// registers, one of the small tiles. Small tiles put more CUs on a replica (a group of
 // few replicas spreads over more workgroups) and read the spins more often per update, so the
 // choice is by the time of one iteration of all R replicas: launches (groups over the groups that
 // fit in width workgroups) times the measured time of one iteration of a launch, a + b Kp / 1024 us:
@@ -817,6 +817,11 @@ extern "C" int nmfa_anneal_range(nmfa_ctx* c, int32_t R, int32_t t_f, int32_t t_
 //   128 x 16 (tile 1)       1.6    2.2    3.4                      3.5   3.6   7.0   13.8
 //   128 x 32 (tile 2)       2.2    3.1    4.8                      4.7   4.8   5.0    9.6
 //   256 x 32 (anneal_xrj)   3.4    4.7    7.3                      7.3   7.3   7.4    8.2
+// and with FP8 spins
+//   64 x 16 (tile 0)        1.4    1.5    2.0                      2.0   4.0   8.0   15.7
+//   128 x 16 (tile 1)       1.7    1.8    2.1                      2.1   2.2   4.3    8.5
+//   128 x 32 (tile 2)       2.1    2.4    3.2                      3.0   3.2   3.3    6.4
+//   256 x 32 (anneal_xrj8)  3.2    3.6    5.0                      5.0   5.0   5.0    5.1
 // Launches in which every XCD holds whole groups need groups in multiples of eight; the others pay
 // for device-scope fences, most with the smallest tile (N = 2000, R = 100: 2.6 -> 7.0, 3.6 -> 5.3,
 // 4.9 -> 6.7 and 7.3 -> 8.8 us). Two workgroups per CU gained nothing (128 x 16, R = 512: 7.0 us for
@@ -824,7 +829,11 @@ extern "C" int nmfa_anneal_range(nmfa_ctx* c, int32_t R, int32_t t_f, int32_t t_
 bool ctx_group_plan(const nmfa_ctx* c, int32_t R, int width, GroupPlan* out) {
   if (c->path != 2) return false;
   width = std::min(width, GROUP_MAX_WGS);
-  static const double kTime[3][3] = {{0.9, 0.75, 4.0}, {1.0, 1.2, 1.8}, {1.4, 1.7, 1.8}};  // a, b, fences
+  // a, b, fences of tiles 0, 1, 2 with BF16 and with FP8 spins
+  static const double kTime[2][3][3] = {{{0.9, 0.75, 4.0}, {1.0, 1.2, 1.8}, {1.4, 1.7, 1.8}},
+                                        {{1.2, 0.4, 4.0}, {1.5, 0.32, 1.8}, {1.65, 0.78, 1.8}}};
+  const bool fp8s = c->xvar == 2;
+  const int fmt = fp8s ? XRS_FP8S : c->jfmt;
   bool any = false;
   auto consider = [&](int tile, int rows, int rg, double a, double b, double fences) {
     const int P = c->Mp / rows, G = (R + rg - 1) / rg;
@@ -839,13 +848,14 @@ bool ctx_group_plan(const nmfa_ctx* c, int32_t R, int width, GroupPlan* out) {
     }
     return P;
   };
-  if (c->xvar == 1 || c->xvar == 3)
+  if (c->xvar != 0)
     for (int tile : {2, 1, 0})
-      if (xrs_applies(c->jfmt, tile, c->Kp))
-        consider(tile, xrs_rows(tile), xrs_group_replicas(tile), kTime[tile][0], kTime[tile][1], kTime[tile][2]);
+      if (xrs_applies(fmt, tile, c->Kp))
+        consider(tile, xrs_rows(tile), xrs_group_replicas(tile), kTime[fp8s][tile][0], kTime[fp8s][tile][1],
+                 kTime[fp8s][tile][2]);
   if (c->xvar == 0) consider(-1, xcd_rows(), xcd_group_replicas(), 2.0, 5.6, 1.0);
   if (c->xvar == 1) consider(-1, xrj_rows(0), xrj_group_replicas(0), 2.1, 2.6, 0.8);
-  if (c->xvar == 2) consider(-1, xrj_rows(1), xrj_group_replicas(1), 1.8, 1.6, 0.8);
+  if (c->xvar == 2) consider(-1, xrj_rows(1), xrj_group_replicas(1), 2.6, 1.2, 0.8);
   if (!any) {  // not even one group fits in width: one group per launch
     width = 1 << 20;
     if (c->xvar == 0) consider(-1, xcd_rows(), xcd_group_replicas(), 2.0, 5.6, 1.0);
@@ -910,7 +920,7 @@ int ctx_launch_run(nmfa_ctx* c, int32_t R, int32_t t_f, int32_t t_begin, int32_t
       x.groups = ng;
       x.force_fenced = (c->flags & NMFA_FLAG_FORCE_FENCED) ? 1 : 0;
       x.nbuf = c->nbuf;
-      if (gp.tile >= 0) HIP_TRY(launch_anneal_xrs(c->jfmt, gp.tile, a, x, grid, st));
+      if (gp.tile >= 0) HIP_TRY(launch_anneal_xrs(c->xvar == 2 ? XRS_FP8S : c->jfmt, gp.tile, a, x, grid, st));
       else if (c->xvar == 2) HIP_TRY(launch_anneal_xrj8(a, x, grid, st));
       else if (c->xvar) HIP_TRY(launch_anneal_xrj(a, x, grid, st));
       else HIP_TRY(launch_anneal_xcd(c->jfmt, a, x, grid, st));

@@ -18,13 +18,17 @@
 //     them at once held the waves back by 1085 cycles of 8145 at N = 2000).
 //   * J is kept as BF16 in registers as far as they go, because the widening of FP4 (8 v_cvt per step
 //     and wave) takes longer than the step's two MFMAs.
+// With FP8 spins (XRS_FP8S) the decomposition is the same and the arithmetic, k order and operand layouts
+// are those of anneal_xrj8: FP4 J and FP8 spins go to the mixed-format instruction as they are stored.
 // What bounds it (cycles of one iteration, N = 2000, 128 x 16 tiles, one workgroup per CU): 4440 of
 // 8420 the k loop, where widening and MFMAs share the issue slots of the single wave; 560 the
 // epilogue; 760 two noise draws; the rest the exchange (stores, arrival, poll, first chunks), which
 // is nearly all of the time at N = 300. Measured per iteration against anneal_xrj (FP4) and the
 // LDS-J and tiled kernels (BF16 J): N = 2000, R = 100 8.0 -> 2.4 us, R = 256 7.3 -> 3.5, R = 512
 // 7.3 -> 5.0; N = 1000, R = 1024 4.8 -> 3.2; N = 300, R = 64 3.7 -> 1.4; BF16 J, N = 1000, R = 512
-// 12.0 -> 2.3, N = 1500, R = 256 34.8 -> 4.4, N = 2000, R = 1024 42 -> 23.
+// 12.0 -> 2.3, N = 1500, R = 256 34.8 -> 4.4, N = 2000, R = 1024 42 -> 23; FP8 spins against
+// anneal_xrj8, N = 2000, R = 100 5.0 -> 2.0, R = 256 5.0 -> 2.2, R = 512 5.0 -> 3.3, N = 1000, R = 256
+// 3.5 -> 1.5, R = 1024 3.6 -> 2.4, N = 300, R = 64 3.1 -> 1.1.
 #include <hip/hip_runtime.h>
 
 #include "nmfa_device.h"
@@ -33,28 +37,32 @@
 
 namespace nmfa {
 
-constexpr int XRS_KC = 128;  // k per spin chunk
+typedef int i32x8 __attribute__((ext_vector_type(8)));
 
-// JFMT: format of J in memory (0 BF16, 1 FP8 E4M3, 2 FP4 E2M1). The first NB chunks of J are held in
-// registers as BF16, widened once at the start; with FP4 J the others stay in FP4 and are widened at
+// JFMT: format of J in memory (0 BF16, 1 FP8 E4M3, 2 FP4 E2M1), spins in BF16; XRS_FP8S: FP4 J and FP8
+// E4M3 spins, both taken by the matrix instruction as they are stored (a chunk of 256 bytes per replica
+// is 256 k then, else 128). The first NB chunks of J are held in registers as BF16, widened once at the start; with FP4 J the others stay in FP4 and are widened at
 // every use. NB is what the registers of one wave per SIMD have room for beside about 110 (one
 // column tile) or 150 (two) others; a tile whose FP8 or BF16 J does not fit is not built.
 template <int JFMT, int RT, int CT, int NCH>
 struct XrsCfg {
   static constexpr int ROWS = 64 * RT;         // rows of J per workgroup (16 RT per wave)
   static constexpr int RG = 16 * CT;           // replicas per group
-  static constexpr int CHB = RG * XRS_KC * 2;  // bytes of one chunk of BF16 spins
+  static constexpr int CHB = RG * 256;         // bytes of one chunk of spins
+  static constexpr bool S8 = JFMT == XRS_FP8S;
+  static constexpr int ES = S8 ? 1 : 2;        // bytes per spin
+  static constexpr int NST = S8 ? 2 : 4;       // matrix steps per chunk (of 128 or 32 k)
   static constexpr int MW = JFMT == 0 ? 4 : (JFMT == 1 ? 2 : 1);  // 32-bit words per 8 couplings in memory
   static constexpr int JBUDGET = CT == 1 ? 336 : 304;             // registers for J
   static constexpr int NBMAX = (JBUDGET / (4 * RT) - NCH) / 3;
-  static constexpr int NB = JFMT != 2 || NBMAX > NCH ? NCH : NBMAX;
-  static constexpr int JREGS = 4 * RT * (4 * NB + MW * (NCH - NB));
+  static constexpr int NB = S8 ? 0 : (JFMT != 2 || NBMAX > NCH ? NCH : NBMAX);
+  static constexpr int JREGS = S8 ? 8 * RT * NCH : 4 * RT * (4 * NB + MW * (NCH - NB));
 };
 
 // 8 couplings of format JFMT as BF16 (exact in every format)
 template <int JFMT>
 __device__ __forceinline__ bf16x8 xrs_widen(const uint32_t (&m)[JFMT == 0 ? 4 : (JFMT == 1 ? 2 : 1)]) {
-  if constexpr (JFMT == 2) return fp4x8_to_bf16x8(m[0]);
+  if constexpr (JFMT >= 2) return fp4x8_to_bf16x8(m[0]);
   else if constexpr (JFMT == 1) return fp8x8_to_bf16x8(m[0], m[1]);
   else return __builtin_bit_cast(bf16x8, uint4{m[0], m[1], m[2], m[3]});
 }
@@ -62,13 +70,14 @@ __device__ __forceinline__ bf16x8 xrs_widen(const uint32_t (&m)[JFMT == 0 ? 4 : 
 template <int JFMT, int RT, int CT, int NCH>
 __device__ __forceinline__ void xrs_body(const AnnealArgs& a, const XcdArgs& x) {
   using C = XrsCfg<JFMT, RT, CT, NCH>;
-  constexpr int NC = NCH, NST = 4, NSTEP = NC * NST;  // chunks; 32-k steps per chunk
-  constexpr int D = 4;                                // spin fragments read D steps ahead
-  constexpr int GB = CT == 1 ? 2 : 4;                 // chunks per workgroup barrier
+  constexpr bool S8 = C::S8;
+  constexpr int NC = NCH, NST = C::NST, NSTEP = NC * NST, ES = C::ES;
+  constexpr int D = NST;                              // spin fragments read D steps (one chunk) ahead
+  constexpr int GB = (CT == 1 ? 2 : 4) / (S8 ? 2 : 1);  // chunks per workgroup barrier
   constexpr int PRO = NC < 7 ? NC : 7;                // chunks issued before the k loop
   constexpr int CHB = C::CHB, ROWS = C::ROWS, RG = C::RG, MW = C::MW, NB = C::NB;
   constexpr int DPW = CHB / 1024 / 4;                 // 1 KB direct-to-LDS loads per wave and chunk
-  constexpr bool XRJ = JFMT == 2;  // arithmetic and k order of anneal_xrj, else those of anneal_xcd
+  constexpr bool XRJ = JFMT >= 2;  // arithmetic and k order of anneal_xrj, else those of anneal_xcd
   static_assert(NC * DPW <= 63 && D % NST == 0, "wait counts fit the vmcnt field");
   extern __shared__ __align__(16) unsigned char smem[];  // one buffer per chunk
   __shared__ unsigned abort_word;                        // the group barrier's decision
@@ -84,13 +93,26 @@ __device__ __forceinline__ void xrs_body(const AnnealArgs& a, const XcdArgs& x) 
   const int rb = slot.rb;
   const bool xcd_mode = slot.xcd_mode;
   bool aborted = slot.aborted;
-  const int ch0 = XRJ ? (rb * ROWS / 256) * 2 : 0;  // first chunk of the pass over k
+  const int ch0 = XRJ ? (rb * ROWS / 256) * (S8 ? 1 : 2) : 0;  // first chunk of the pass over k
 
   // J of this wave: jr[i][st][rt] = the 8 couplings of row rb ROWS + 16 (RT wave + rt) + c at
   // k = 128 ch + 32 st + 8 g .. +7 with ch = (ch0 + i) mod NC
+  // (FP8 spins: j8[i][st][rt] = the 32 of that row at k = 256 ch + 128 st + 32 g ..)
   bf16x8 jb[NB > 0 ? NB : 1][NST][RT];                // chunks 0 .. NB - 1, widened
   uint32_t jn[NC > NB ? NC - NB : 1][NST][RT][MW];    // the others
-  {
+  uint4 j8[S8 ? NC : 1][NST][RT];
+  if constexpr (S8) {
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+      const unsigned char* p = reinterpret_cast<const unsigned char*>(a.J) +
+                               (size_t)(rb * ROWS + 16 * (RT * wave + rt) + c) * (128 * NC) + 16 * g;
+#pragma unroll
+      for (int i = 0; i < NC; ++i)
+#pragma unroll
+        for (int st = 0; st < NST; ++st)
+          j8[i][st][rt] = *reinterpret_cast<const uint4*>(p + 128 * ((ch0 + i) % NC) + 64 * st);
+    }
+  } else {
     const size_t jrow = (size_t)64 * NC * MW;  // bytes of one row (Kp couplings)
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
@@ -147,17 +169,19 @@ __device__ __forceinline__ void xrs_body(const AnnealArgs& a, const XcdArgs& x) 
 
   // Spin chunks: replica rows of 16 units of 16 bytes; unit u of replica q sits at u ^ (q & 15), so
   // the 16 lanes that one ds_read_b128 serves at a time hit all 64 banks once
-  int boff[NST];
+  // (BF16: unit 4 st + g in step st; FP8, whose operand takes k = 16 g .. and 64 + 16 g .. of a step: units
+  // 8 st + g and 8 st + 4 + g)
+  int boff[4];
 #pragma unroll
-  for (int st = 0; st < NST; ++st) boff[st] = c * 256 + (((4 * st + g) ^ c) * 16);
+  for (int j = 0; j < 4; ++j) boff[j] = c * 256 + (((4 * j + g) ^ c) * 16);
   unsigned dma_off[DPW];
 #pragma unroll
   for (int u = 0; u < DPW; ++u) {
     const int q = 4 * (DPW * wave + u) + lane / 16;
-    dma_off[u] = (unsigned)(q * ks + ((lane % 16) ^ (q & 15)) * 8) * 2u;
+    dma_off[u] = (unsigned)(q * ks * ES + ((lane % 16) ^ (q & 15)) * 16);
   }
   // where this lane's new spins go in the group's rows of S
-  const unsigned out_off = (unsigned)(c * ks + row0) * 2u;
+  const unsigned out_off = (unsigned)(c * ks + row0) * ES;
 
   // The noise of one iteration, drawn while the group barrier of the one before completes: w is
   // (h_i + sigma z) / (T_t norm_i) in exp2 units with anneal_xrj's arithmetic, else sigma z
@@ -186,8 +210,8 @@ __device__ __forceinline__ void xrs_body(const AnnealArgs& a, const XcdArgs& x) 
 #pragma unroll
   for (int d = 0; d < RT * CT; ++d) draw(a.t_begin, d, coef_next);
 
-  unsigned char* S0 = reinterpret_cast<unsigned char*>(x.S[0]) + (size_t)group * RG * ks * 2;
-  unsigned char* S1 = reinterpret_cast<unsigned char*>(x.S[1]) + (size_t)group * RG * ks * 2;
+  unsigned char* S0 = reinterpret_cast<unsigned char*>(x.S[0]) + (size_t)group * RG * ks * ES;
+  unsigned char* S1 = reinterpret_cast<unsigned char*>(x.S[1]) + (size_t)group * RG * ks * ES;
   unsigned* bar = &x.ctl[CTL_BAR + 16 * (int)my_group];
   int epoch = 0;
   __syncthreads();
@@ -196,7 +220,7 @@ __device__ __forceinline__ void xrs_body(const AnnealArgs& a, const XcdArgs& x) 
     const float coef_t = coef_next;
     unsigned char* Sg = (t & 1) ? S1 : S0;
     unsigned char* Sn = (t & 1) ? S0 : S1;
-    const __amdgpu_buffer_rsrc_t srs = __builtin_amdgcn_make_buffer_rsrc(Sg, 0, RG * ks * 2, 0x00020000);
+    const __amdgpu_buffer_rsrc_t srs = __builtin_amdgcn_make_buffer_rsrc(Sg, 0, RG * ks * ES, 0x00020000);
     int ch_t = ch0, wb = DPW * 1024 * wave;  // opaque, so that no address is held across the loop
     asm volatile("" : "+s"(ch_t));
     asm volatile("" : "+s"(wb));
@@ -205,17 +229,22 @@ __device__ __forceinline__ void xrs_body(const AnnealArgs& a, const XcdArgs& x) 
       if (ch >= NC) ch -= NC;
 #pragma unroll
       for (int u = 0; u < DPW; ++u)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(srs, smem + wb + i * CHB + u * 1024, 16, dma_off[u], ch * 2 * XRS_KC,
-                                                 0, AUX_SC1);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(srs, smem + wb + i * CHB + u * 1024, 16, dma_off[u], ch * 256, 0,
+                                                 AUX_SC1);
     };
 #pragma unroll
     for (int i = 0; i < PRO; ++i) issue(i);
-    bf16x8 fb[D + 1][CT];
+    // FP8 spins are read as BF16 vectors too: an integer read would wait for every direct-to-LDS load in
+    // flight, which the compiler takes to be integer stores (N = 2000, R = 100, BF16: 2.4 -> 3.4 us)
+    bf16x8 fb[D + 1][CT][S8 ? 2 : 1];
     auto load = [&](int sidx) {
+      constexpr int NU = S8 ? 2 : 1;  // 16-byte units of a step
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct)
-        fb[sidx % (D + 1)][ct] =
-            *reinterpret_cast<const bf16x8*>(smem + (sidx / NST) * CHB + ct * 4096 + boff[sidx % NST]);
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+          fb[sidx % (D + 1)][ct][u] = *reinterpret_cast<const bf16x8*>(smem + (sidx / NST) * CHB + ct * 4096 +
+                                                                       boff[sidx % NST * NU + u]);
     };
     f32x4 acc[RT][CT];
     wait_vm<(PRO > GB ? PRO - GB : 0) * DPW>();
@@ -245,13 +274,27 @@ __device__ __forceinline__ void xrs_body(const AnnealArgs& a, const XcdArgs& x) 
           if constexpr (nxt < NSTEP) load(nxt);
 #pragma unroll
           for (int rt = 0; rt < RT; ++rt) {
-            bf16x8 af;
-            if constexpr (i < NB) af = jb[i][st][rt];
-            else af = xrs_widen<JFMT>(jn[i - NB][st][rt]);
+            if constexpr (S8) {
+              const uint4 j = j8[i][st][rt];
+              const i32x8 af = i32x8{(int)j.x, (int)j.y, (int)j.z, (int)j.w, 0, 0, 0, 0};
 #pragma unroll
-            for (int ct = 0; ct < CT; ++ct)
-              acc[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, fb[sidx % (D + 1)][ct],
-                                                                   sidx == 0 ? f32x4{} : acc[rt][ct], 0, 0, 0);
+              for (int ct = 0; ct < CT; ++ct) {
+                const uint4 lo = __builtin_bit_cast(uint4, fb[sidx % (D + 1)][ct][0]);
+                const uint4 hi = __builtin_bit_cast(uint4, fb[sidx % (D + 1)][ct][S8 ? 1 : 0]);
+                const i32x8 bf = i32x8{(int)lo.x, (int)lo.y, (int)lo.z, (int)lo.w,
+                                       (int)hi.x, (int)hi.y, (int)hi.z, (int)hi.w};
+                acc[rt][ct] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(
+                    af, bf, sidx == 0 ? f32x4{} : acc[rt][ct], 4, 0, 0, 0x7f7f7f7f, 0, 0x7f7f7f7f);
+              }
+            } else {
+              bf16x8 af;
+              if constexpr (i < NB) af = jb[i][st][rt];
+              else af = xrs_widen<JFMT>(jn[i - NB][st][rt]);
+#pragma unroll
+              for (int ct = 0; ct < CT; ++ct)
+                acc[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                    af, fb[sidx % (D + 1)][ct][0], sidx == 0 ? f32x4{} : acc[rt][ct], 0, 0, 0);
+            }
           }
           __builtin_amdgcn_sched_barrier(0);  // keeps the reads D steps ahead of their use
         },
@@ -263,7 +306,6 @@ __device__ __forceinline__ void xrs_body(const AnnealArgs& a, const XcdArgs& x) 
     for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct) {
-        __bf16 outv[4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           float sv;
@@ -276,10 +318,16 @@ __device__ __forceinline__ void xrs_body(const AnnealArgs& a, const XcdArgs& x) 
             sv = fmaf(alpha, neg_tanh_from_exp2_arg(phi * coef_t), oma * s[rt][ct][v]);
           }
           s[rt][ct][v] = sv;
-          outv[v] = (__bf16)sv;
         }
-        *reinterpret_cast<uint2*>(Sn + (out_off + 32u * rt + (unsigned)(ct * 16 * ks) * 2u)) =
-            *reinterpret_cast<const uint2*>(outv);
+        unsigned char* dst = Sn + (out_off + (unsigned)(16 * rt + ct * 16 * ks) * ES);
+        if constexpr (S8) {
+          const int lo = __builtin_amdgcn_cvt_pk_fp8_f32(s[rt][ct][0], s[rt][ct][1], 0, false);
+          *reinterpret_cast<int*>(dst) = __builtin_amdgcn_cvt_pk_fp8_f32(s[rt][ct][2], s[rt][ct][3], lo, true);
+        } else {
+          const __bf16 outv[4] = {(__bf16)s[rt][ct][0], (__bf16)s[rt][ct][1], (__bf16)s[rt][ct][2],
+                                  (__bf16)s[rt][ct][3]};
+          *reinterpret_cast<uint2*>(dst) = *reinterpret_cast<const uint2*>(outv);
+        }
       }
     const int k_rec = t - a.t_begin;
     if (traj && k_rec < a.record) {
@@ -344,14 +392,15 @@ static const void* xrs_fn_n() {
 
 template <int JFMT, int RT, int CT>
 static const void* xrs_fn_k(int Kp) {
+  constexpr int CPK = JFMT == XRS_FP8S ? 1 : 2;  // chunks per 256 k
   switch (Kp) {
-    case 512: return xrs_fn_n<JFMT, RT, CT, 4>();
-    case 768: return xrs_fn_n<JFMT, RT, CT, 6>();
-    case 1024: return xrs_fn_n<JFMT, RT, CT, 8>();
-    case 1280: return xrs_fn_n<JFMT, RT, CT, 10>();
-    case 1536: return xrs_fn_n<JFMT, RT, CT, 12>();
-    case 1792: return xrs_fn_n<JFMT, RT, CT, 14>();
-    case 2048: return xrs_fn_n<JFMT, RT, CT, 16>();
+    case 512: return xrs_fn_n<JFMT, RT, CT, 2 * CPK>();
+    case 768: return xrs_fn_n<JFMT, RT, CT, 3 * CPK>();
+    case 1024: return xrs_fn_n<JFMT, RT, CT, 4 * CPK>();
+    case 1280: return xrs_fn_n<JFMT, RT, CT, 5 * CPK>();
+    case 1536: return xrs_fn_n<JFMT, RT, CT, 6 * CPK>();
+    case 1792: return xrs_fn_n<JFMT, RT, CT, 7 * CPK>();
+    case 2048: return xrs_fn_n<JFMT, RT, CT, 8 * CPK>();
     default: return nullptr;
   }
 }
@@ -364,7 +413,13 @@ static const void* xrs_fn_t(int tile, int Kp) {
 }
 
 static const void* xrs_fn(int jfmt, int tile, int Kp) {
-  return jfmt == 2 ? xrs_fn_t<2>(tile, Kp) : (jfmt == 1 ? xrs_fn_t<1>(tile, Kp) : xrs_fn_t<0>(tile, Kp));
+  switch (jfmt) {
+    case 0: return xrs_fn_t<0>(tile, Kp);
+    case 1: return xrs_fn_t<1>(tile, Kp);
+    case 2: return xrs_fn_t<2>(tile, Kp);
+    case XRS_FP8S: return xrs_fn_t<XRS_FP8S>(tile, Kp);
+    default: return nullptr;
+  }
 }
 
 bool xrs_applies(int jfmt, int tile, int Kp) { return xrs_fn(jfmt, tile, Kp) != nullptr; }
@@ -372,7 +427,8 @@ bool xrs_applies(int jfmt, int tile, int Kp) { return xrs_fn(jfmt, tile, Kp) != 
 hipError_t launch_anneal_xrs(int jfmt, int tile, const AnnealArgs& a, const XcdArgs& x, int grid, hipStream_t st) {
   const void* fn = xrs_fn(jfmt, tile, a.Kp);
   if (!fn) return hipErrorInvalidValue;
-  return launch_group_resident(fn, grid, 256, (size_t)a.Kp * 2 * xrs_group_replicas(tile), a, x, st);
+  return launch_group_resident(fn, grid, 256, (size_t)a.Kp * (jfmt == XRS_FP8S ? 1 : 2) * xrs_group_replicas(tile), a,
+                               x, st);
 }
 
 }  // namespace nmfa
