@@ -783,6 +783,21 @@ size_t small_run_lds_bytes(int prec, int stride) {
 // f = (q >> 1) & 7, (q >> 2) & 3, (q >> 3) & 1 for the three formats, so the 16 rows one fragment
 // read spans hit distinct banks.
 // ------------------------------------------------------------------------------------------
+// Tile of a workgroup of the tiled kernels: row tile and replica tile. Workgroups are dispatched round robin
+// over the eight XCDs; each XCD takes a contiguous eighth of the tiles, replica tiles within a row tile
+// first, so that it reads about an eighth of J through its L2 whatever the number of row tiles is. (Plain
+// two-dimensional grids do so only if that is a multiple of 8: FP64, N = 2000, R = 256, 63 row tiles, 57.0
+// us per iteration against 53.7; BF16 J, N = 2100, R = 300, 33 row tiles, 18.0 against 15.3; FP4 J, N =
+// 8192, R = 1024, 32 row tiles, 120.5 against 118.9.)
+constexpr int TILE_XCDS = 8;
+static dim3 tile_grid(int rows, int cols) { return dim3((rows * cols + TILE_XCDS - 1) / TILE_XCDS * TILE_XCDS); }
+__device__ __forceinline__ bool tile_of(int rows, int cols, int& row, int& col) {
+  const int tile = (int)(blockIdx.x % TILE_XCDS * (gridDim.x / TILE_XCDS) + blockIdx.x / TILE_XCDS);
+  row = tile / cols;
+  col = tile - row * cols;
+  return row < rows;
+}
+
 constexpr int ST_M = 256;                 // rows per workgroup
 constexpr int ST_R = 128;                 // replicas per workgroup
 constexpr int ST_K = 64;                  // k per block
@@ -847,7 +862,10 @@ __device__ __forceinline__ void step_tiled_body(const AnnealArgs& a, const __bf1
   const int N = a.N, Kp = a.Kp;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int g4 = lane >> 4, c = lane & 15;
-  const int m0 = blockIdx.x * ST_M, r0 = blockIdx.y * ST_R;
+  int m0, r0;
+  if (!tile_of((N + ST_M - 1) / ST_M, (a.R + ST_R - 1) / ST_R, m0, r0)) return;
+  m0 *= ST_M;
+  r0 *= ST_R;
   const int wm = 64 * (wave >> 1), wr = 64 * (wave & 1);
 
   // direct-to-LDS loads: blocks 0 .. JB - 1 hold the J tile (1024 / JRB rows each), JB .. JB + 15
@@ -902,7 +920,7 @@ __device__ __forceinline__ void step_tiled_body(const AnnealArgs& a, const __bf1
 #pragma unroll
       for (int v = 0; v < 4; ++v) acc[rt][ct][v] = 0.0f;
 
-  const int nkb = Kp / ST_K;
+  const int nkb = (N + ST_K - 1) / ST_K;  // the blocks beyond N would add zeros
   // This wave's 64 x 64 master states are loaded before the k loop, so that their latency hides
   // under the matrix work rather than stalling the epilogue. They are issued ahead of the first
   // blocks, so the first block's wait also covers them. When the wave's tile lies inside N x R and
@@ -1128,7 +1146,12 @@ __global__ __launch_bounds__(512, 1) void anneal_step_tiled(AnnealArgs a, const 
 // 107 -> 31, N = 777 R = 256 45 -> 12. Padding the operand rows to spread them over the L2 channels
 // changed nothing, nor did reading three windows ahead instead of one, nor (64 x 32, FP4 J, one workgroup
 // per CU: 0.37 us per block) a ring of 8 stages instead of 5; 3 stages take 0.58 us per block (BF16 J).
-// Needs Mp % 128 == 0, Kp % 64 == 0, and S buffers of roundup(R, 64) rows (padding rows finite).
+// The grid covers the N rows; rows of the last tile beyond N are written as zeros, and the columns of S
+// past them, which the last block of k multiplies by zero couplings, hold the zeros they were allocated
+// with. (With rows and k padded to a multiple of 256, FP64, us per iteration: N = 120, R = 64 8.9 against
+// 7.4; N = 300, R = 256 13.5, 10.7; N = 777, R = 256 21.9, 18.7; N = 1100, R = 200 33.4, 23.3. FP32, N =
+// 1100, R = 200 19.7, 14.4.)
+// Needs Mp % 256 == 0, Kp = Mp, and S buffers of roundup(R, 64) rows (padding rows finite).
 // ------------------------------------------------------------------------------------------
 template <int P, int JFMT, int RT, int CT, int WM, int WR, int WPC = 1>
 struct SfTile {
@@ -1174,7 +1197,10 @@ __device__ __forceinline__ void step_tiled_f_body(const AnnealArgs& a, const voi
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: scalar registers
   const int g = lane >> 4, c = lane & 15;
-  const int m0 = blockIdx.x * T::TM, r0 = blockIdx.y * T::TR;
+  int m0, r0;
+  if (!tile_of((N + T::TM - 1) / T::TM, (a.R + T::TR - 1) / T::TR, m0, r0)) return;
+  m0 *= T::TM;
+  r0 *= T::TR;
   const int wm = 16 * RT * (wave / WR), wr = 16 * CT * (wave % WR);
 
   // direct-to-LDS loads: 1 KB blocks of whole tile rows (four of S), first the J tile's, then the S
@@ -1243,7 +1269,8 @@ __device__ __forceinline__ void step_tiled_f_body(const AnnealArgs& a, const voi
 #pragma unroll
       for (int v = 0; v < 4; ++v) acc[rt][ct][v] = (acc_t)0;
 
-  const int nkb = Kp / T::BLK;
+  // blocks beyond N would add zeros (in FP32 every block holds some k below N)
+  const int nkb = P == PREC_FP32 ? Kp / T::BLK : (N + T::BLK - 1) / T::BLK;
   // The fragments of a window are read into one register set while the MFMAs of the window before
   // it run on the other, across the block boundaries too: the barrier that makes block kb + 1
   // visible stands before the last window of block kb.
@@ -1359,7 +1386,7 @@ static hipError_t launch_step_tiled(const AnnealArgs& a, const void* S_cur, void
   hipError_t e = hipFuncSetAttribute((const void*)anneal_step_tiled<JFMT>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                      (int)lds);
   if (e != hipSuccess) return e;
-  const dim3 grid(a.Mp / ST_M, (a.R + ST_R - 1) / ST_R);
+  const dim3 grid = tile_grid((a.N + ST_M - 1) / ST_M, (a.R + ST_R - 1) / ST_R);
   hipLaunchKernelGGL(anneal_step_tiled<JFMT>, grid, dim3(512), lds, st, a, (const __bf16*)S_cur, (__bf16*)S_next, t);
   return hipGetLastError();
 }
@@ -1371,7 +1398,7 @@ static hipError_t launch_step_f(const AnnealArgs& a, const void* S_cur, void* S_
   hipError_t e = hipFuncSetAttribute((const void*)anneal_step_tiled_f<P, JFMT, RT, CT, WM, WR, WPC>,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  const dim3 grid(a.Mp / T::TM, (a.R + T::TR - 1) / T::TR);
+  const dim3 grid = tile_grid((a.N + T::TM - 1) / T::TM, (a.R + T::TR - 1) / T::TR);
   hipLaunchKernelGGL((anneal_step_tiled_f<P, JFMT, RT, CT, WM, WR, WPC>), grid, dim3(64 * T::W), lds, st, a, S_cur, S_next, t);
   return hipGetLastError();
 }
@@ -1393,7 +1420,7 @@ template <int P>
 static hipError_t launch_step_f_pick(const AnnealArgs& a, const void* S_cur, void* S_next, int t, hipStream_t st) {
   const int cus = device_cus();
   auto rounds = [&](int tm, int tr) {
-    const long tiles = (long)(a.Mp / tm) * ((a.R + tr - 1) / tr);
+    const long tiles = (long)((a.N + tm - 1) / tm) * ((a.R + tr - 1) / tr);
     return (double)((tiles + cus - 1) / cus);
   };
   const double big = 6.2 * rounds(128, 64), mid = 3.3 * rounds(64, 64), small = 1.0 / 3 + rounds(32, 32);
@@ -1417,13 +1444,13 @@ static hipError_t launch_step_b_pick(const AnnealArgs& a, const void* S_cur, voi
   constexpr int P = PREC_BF16;
   const int cus = device_cus();
   auto cost = [&](int tm, int tr, int per_cu, double once, double s1, double s2) {
-    const long tiles = (long)(a.Mp / tm) * ((a.R + tr - 1) / tr), full = tiles / (per_cu * cus);
+    const long tiles = (long)((a.N + tm - 1) / tm) * ((a.R + tr - 1) / tr), full = tiles / (per_cu * cus);
     const long rest = tiles % (per_cu * cus);
-    const double nb = a.Kp / 128;
+    const double nb = (a.N + 127) / 128;
     return once + full * (2 + s2 * nb) + (rest == 0 ? 0.0 : 2 + (rest <= cus ? s1 : s2) * nb);
   };
   if constexpr (JFMT == 0) {
-    if ((long)(a.Mp / 64) * ((a.R + 31) / 32) <= cus)  // a workgroup per CU: the longer ring (s1 = 0.37)
+    if ((long)((a.N + 63) / 64) * ((a.R + 31) / 32) <= cus)  // a workgroup per CU: the longer ring (s1 = 0.37)
       return launch_step_f<P, JFMT, 1, 2, 4, 1, 1>(a, S_cur, S_next, t, st);
     const double c64 = cost(64, 32, 2, 3, 0.58, 0.65), c128 = cost(128, 64, 1, 8, 0.88, 0.88),
                  c256 = cost(256, 128, 1, 6, 2.3, 2.3);
