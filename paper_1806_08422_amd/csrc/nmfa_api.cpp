@@ -185,6 +185,8 @@ static void free_run_buffers(nmfa_ctx* c) {
   (void)hipFree(c->d_spins);
   (void)hipFree(c->d_E);
   (void)hipFree(c->d_Eint);
+  (void)hipFree(c->d_z);
+  c->d_z = nullptr;
   (void)hipFree(c->d_Sp);
   (void)hipFree(c->d_E2);
   (void)hipFree(c->d_Ep);
@@ -868,6 +870,21 @@ bool ctx_group_plan(const nmfa_ctx* c, int32_t R, int width, GroupPlan* out) {
   return true;
 }
 
+// Iterations of a small-N run whose noise is drawn ahead by a launch of its own, 0 where the annealing kernel
+// draws it: also for a recorded run (the trajectory counts its iterations from the launch's first) and where
+// the buffer is not there and cannot be allocated, as while a stream is captured.
+static int small_noise_ahead(nmfa_ctx* c, const AnnealArgs& a, hipStream_t st) {
+  const int ahead = a.traj ? 0 : small_noise_iters(c->prec, a.Mp, a.R, a.t_end - a.t_begin + 1);
+  if (ahead == 0 || c->d_z) return ahead;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
+      hipMalloc(&c->d_z, small_noise_bytes()) == hipSuccess)
+    return ahead;
+  (void)hipGetLastError();
+  c->d_z = nullptr;
+  return 0;
+}
+
 int ctx_launch_run(nmfa_ctx* c, int32_t R, int32_t t_f, int32_t t_begin, int32_t t_end, uint64_t seed,
                    hipStream_t st, bool finish, int max_workgroups) {
   AnnealArgs a{};
@@ -876,8 +893,19 @@ int ctx_launch_run(nmfa_ctx* c, int32_t R, int32_t t_f, int32_t t_begin, int32_t
 
   HIP_TRY(hipEventRecord(c->ev0, st));
   if (c->path == 0) {
-    HIP_TRY(launch_anneal_small(c->prec, a, st));
-    c->launches = 1;
+    const int ahead = small_noise_ahead(c, a, st);
+    c->launches = 0;
+    for (int t = t_begin; t <= t_end; t += ahead > 0 ? ahead : t_end - t_begin + 1) {
+      if (ahead > 0) {
+        a.t_begin = t;
+        a.t_end = std::min(t + ahead - 1, t_end);
+        a.load_state = t > 1 ? 1 : 0;
+        HIP_TRY(launch_small_noise(a, c->d_z, st));
+        a.z = c->d_z;
+      }
+      HIP_TRY(launch_anneal_small(c->prec, a, st));
+      ++c->launches;
+    }
     HIP_TRY(hipEventRecord(c->evm, st));
   } else if (c->path == 3) {
     HIP_TRY(launch_anneal_sparse(c->prec == NMFA_FP64 ? 0 : 1, a, c->d_ell_col, c->d_ell_val, c->ell_D, c->sp_RB,

@@ -66,6 +66,7 @@ struct nmfa_ctx {
   int8_t* d_spins = nullptr; // [R][n]
   double* d_E = nullptr;     // [R]
   long long* d_Eint = nullptr;
+  void* d_z = nullptr;       // noise of the small-N kernel, small_noise_bytes()
   int8_t* d_Sp = nullptr;    // energy scratch: padded signs [roundup(R, 64)][Np8]
   unsigned long long* d_E2 = nullptr;  // energy scratch [R]
   double* d_Ep = nullptr;    // energy scratch with FP64 couplings: [energy_f64_part(n)][R]

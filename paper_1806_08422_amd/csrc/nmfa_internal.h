@@ -24,6 +24,7 @@ struct AnnealArgs {
   uint32_t key0, key1;   // Philox key = 64-bit seed
   double alpha, sigma;
   int negate_noise;      // test hook: z -> -z
+  const void* z;         // small-N kernel: noise of iterations t_begin .. t_end (launch_small_noise), or null
 };
 
 constexpr int GROUP_MAX_WGS = 256;  // workgroups of one group-kernel launch (control block size)
@@ -41,6 +42,11 @@ struct XcdArgs {
 };
 
 hipError_t launch_anneal_small(int prec, const AnnealArgs& a, hipStream_t st);
+// Noise drawn ahead of the small-N kernel (FP64): iterations per launch, or 0 where the kernel draws its own; z holds
+// those of iterations t_begin .. t_end, small_noise_bytes() bytes of up to that many.
+int small_noise_iters(int prec, int Mp, int R, int iters);
+size_t small_noise_bytes();
+hipError_t launch_small_noise(const AnnealArgs& a, void* z, hipStream_t st);
 // jobs: device array of AnnealArgs (one per job); tasks: device array of (job, replica block).
 hipError_t launch_anneal_small_batched(int prec, const AnnealArgs* jobs, const int2* tasks, int n_tasks,
                                        int max_Mp, size_t lds, hipStream_t st);

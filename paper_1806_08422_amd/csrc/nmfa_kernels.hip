@@ -37,6 +37,10 @@ template <bool B>
 struct StBool {
   static constexpr bool value = B;
 };
+template <int I>
+struct StInt {
+  static constexpr int value = I;
+};
 
 template <int P>
 struct Epilogue;
@@ -121,7 +125,7 @@ template <>
 struct Epilogue<PREC_BF16> : EpilogueF32<PREC_BF16> {};
 
 // ------------------------------------------------------------------------------------------
-// anneal_small<P, J8, NK, SPLIT>: see the file header. Wave w owns rows [16w, 16w+16) (FP64 with
+// anneal_small<P, J8, NK, SPLIT, PRE>: see the file header. Wave w owns rows [16w, 16w+16) (FP64 with
 // SPLIT > 1: SPLIT waves share a tile's rows, see the launcher); grid = ceil(R / 16) workgroups,
 // workgroup b owns replicas [16b, 16b+16). Each lane keeps its part of J in registers (NK reads of 16
 // bytes; J8: FP8 E4M3 in memory, widened to BF16). LDS: Ss[2][16][js] (op_t), js = padded row stride in
@@ -134,10 +138,11 @@ struct Epilogue<PREC_BF16> : EpilogueF32<PREC_BF16> {};
 // waves per SIMD make no difference); FP32: the chain of 16x16x4 products (32 cycles each) beside it.
 // Against J in LDS, a rolled k loop and buffer addresses multiplied out in every iteration, per
 // iteration: BF16 N = 100, R = 16384 1.94 -> 1.73 us, N = 173, R = 64 1.09 -> 0.70, N = 256, R = 1024
-// 1.55 -> 0.97; FP32 N = 100, R = 4096 1.42 -> 1.35; FP64 N = 20, R = 256 2.73 -> 1.48. Scheduling the
+// 1.55 -> 0.97; FP32 N = 100, R = 4096 1.42 -> 1.35; FP64 N = 20, R = 256 2.73 -> 1.48
+// (1.20 with the noise drawn ahead, PRE: launch_small_noise). Scheduling the
 // FP32 noise between the products (1.41) or drawing it after them in every second wave gained nothing.
 // ------------------------------------------------------------------------------------------
-template <int P, bool J8, int NK, int SPLIT = 1>
+template <int P, bool J8, int NK, int SPLIT = 1, bool PRE = false>
 __device__ __forceinline__ void anneal_small_body(const AnnealArgs& a, const int rblock) {
   static_assert(SPLIT == 1 || P == PREC_FP64, "split tiles are built for FP64");
   constexpr int NV = 4 / SPLIT;  // rows of a lane's quad that its wave updates
@@ -230,15 +235,32 @@ __device__ __forceinline__ void anneal_small_body(const AnnealArgs& a, const int
   };
   // One iteration: read the operands of buffer CUR, draw the noise while they arrive, multiply, update,
   // write buffer 1 - CUR. Rows beyond N are updated too: the couplings to them are zero.
-  auto step = [&](auto cur_c, int t) {
-    constexpr int CUR = decltype(cur_c)::value;
+  // PRE: the noise comes from memory (launch_small_noise), read four iterations ahead
+  static_assert(!PRE || P == PREC_FP64, "noise drawn ahead is built for FP64");
+  constexpr int NPRE = 4;
+  typedef acc_t zvec __attribute__((ext_vector_type(NV)));
+  zvec zr[PRE ? NPRE : 1];
+  const size_t zstep = (size_t)gridDim.x * (Mp >> 4) * 256;  // values per iteration
+  const acc_t* zl = reinterpret_cast<const acc_t*>(a.z) + ((size_t)rblock * (Mp >> 4) + tile) * 256 + lane * 4 + NV * part;
+  auto read_z = [&](int t) {
+    return *reinterpret_cast<const zvec*>(zl + (size_t)((t < a.t_end ? t : a.t_end) - a.t_begin) * zstep);
+  };
+  auto step = [&](auto cur_c, auto slot_c, int t) {
+    constexpr int CUR = decltype(cur_c)::value, SLOT = decltype(slot_c)::value;
     const acc_t coef_t = coef[t - 1];
     uint4 bv[NK];
     const op_t* Bc = Sl + (CUR ? sbuf : 0) + g * Kq;
 #pragma unroll
     for (int m = 0; m < NK; ++m) bv[m] = *reinterpret_cast<const uint4*>(Bc + m * EPC);
     acc_t z[NV];
-    draw(z, t);
+    if constexpr (PRE) {
+      const zvec zt = zr[SLOT];
+#pragma unroll
+      for (int v = 0; v < NV; ++v) z[v] = zt[v];
+      zr[SLOT] = read_z(t + NPRE);
+    } else {
+      draw(z, t);
+    }
     acc4_t acc;
 #pragma unroll
     for (int v = 0; v < 4; ++v) acc[v] = (acc_t)0;
@@ -269,14 +291,35 @@ __device__ __forceinline__ void anneal_small_body(const AnnealArgs& a, const int
       for (int v = 0; v < NV; ++v)
         if (row0 + v < N) traj[((size_t)k * a.R + r) * N + row0 + v] = s[v];
     }
-    __syncthreads();
+    if constexpr (PRE) {  // a barrier that does not wait for the noise in flight
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_waitcnt(0xC07F);
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+    } else {
+      __syncthreads();
+    }
   };
   int t = a.t_begin;
-  for (; t < a.t_end; t += 2) {
-    step(StBool<false>{}, t);
-    step(StBool<true>{}, t + 1);
+  if constexpr (PRE) {
+#pragma unroll
+    for (int k = 0; k < NPRE; ++k) zr[k] = read_z(t + k);
+    for (; t + 3 <= a.t_end; t += 4) {
+      step(StBool<false>{}, StInt<0>{}, t);
+      step(StBool<true>{}, StInt<1>{}, t + 1);
+      step(StBool<false>{}, StInt<2>{}, t + 2);
+      step(StBool<true>{}, StInt<3>{}, t + 3);
+    }
+    if (t <= a.t_end) step(StBool<false>{}, StInt<0>{}, t);
+    if (t + 1 <= a.t_end) step(StBool<true>{}, StInt<1>{}, t + 1);
+    if (t + 2 <= a.t_end) step(StBool<false>{}, StInt<2>{}, t + 2);
+  } else {
+    for (; t < a.t_end; t += 2) {
+      step(StBool<false>{}, StInt<0>{}, t);
+      step(StBool<true>{}, StInt<0>{}, t + 1);
+    }
+    if (t == a.t_end) step(StBool<false>{}, StInt<0>{}, t);
   }
-  if (t == a.t_end) step(StBool<false>{}, t);
 
   // ---- final state and sign readout -------------------------------------------------------
   if (live_r) {
@@ -306,17 +349,27 @@ constexpr int small_min_waves(int NK) {
   return P == PREC_FP64 ? 2 : (P == PREC_FP32 || NK > 4 ? 4 : 5);
 }
 
-template <int P, bool J8, int NK, int SPLIT>
+template <int P, bool J8, int NK, int SPLIT, bool PRE>
 __global__ __launch_bounds__(small_threads<P>(), small_min_waves<P>(NK)) void anneal_small(AnnealArgs a) {
-  anneal_small_body<P, J8, NK, SPLIT>(a, (int)blockIdx.x);
+  anneal_small_body<P, J8, NK, SPLIT, PRE>(a, (int)blockIdx.x);
+}
+
+// The noise of iterations t_begin .. t_end for anneal_small, the values it would draw itself: a wave per
+// iteration, replica block and row tile, the four of a lane's quad side by side. Bound by the vector
+// instructions, like the draws in the annealing kernel, but spread over the whole chip.
+__global__ __launch_bounds__(256) void small_noise(AnnealArgs a, double* __restrict__ out, int blocks) {
+  const int tiles = a.Mp >> 4, lane = threadIdx.x & 63;
+  const unsigned w = blockIdx.x * 4u + (threadIdx.x >> 6);
+  const unsigned per = (unsigned)(blocks * tiles), it = w / per, k = w - it * per;
+  if (it > (unsigned)(a.t_end - a.t_begin)) return;
+  const unsigned b = k / tiles, tile = k - b * tiles;
+  double z[4];
+  Epilogue<PREC_FP64>::noise(z, a, tile * 4 + (lane >> 4), b * 16 + (lane & 15), (uint32_t)a.t_begin + it);
+  reinterpret_cast<double4*>(out)[(size_t)w * 64 + lane] = make_double4(z[0], z[1], z[2], z[3]);
 }
 
 // Calls f with the number of 16-byte reads as a compile-time constant. Kp is a multiple of 32 (BF16, at
 // most 256) or 16 (FP32, at most 176; FP64, at most 112: what the path's limit on LDS admits).
-template <int NK>
-struct StInt {
-  static constexpr int value = NK;
-};
 template <int P, class F>
 __host__ __device__ __forceinline__ bool small_dispatch(int nk, F&& f) {
   if constexpr (P == PREC_FP64) {
@@ -681,6 +734,13 @@ __global__ void noise_values_kernel(uint32_t key0, uint32_t key1, uint32_t t, ui
 // ------------------------------------------------------------------------------------------
 // Host-side launchers.
 // ------------------------------------------------------------------------------------------
+static int device_cus() {
+  int dev = 0, cus = 256;
+  if (hipGetDevice(&dev) == hipSuccess)
+    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  return cus;
+}
+
 template <int P, bool J8>
 static hipError_t launch_small_t(const AnnealArgs& a, hipStream_t st) {
   const int waves = a.Mp / 16;
@@ -692,28 +752,60 @@ static hipError_t launch_small_t(const AnnealArgs& a, hipStream_t st) {
   // rows only. N = 20, R = 256: 2.6 us per iteration with one wave per tile, 1.5 with two; N = 16: 2.4
   // with one, 1.4 with two, 1.2 with four. Two waves on a SIMD gain nothing (N = 20, four waves per
   // tile: 2.15; N = 33, two: 2.9 against 2.7), nor do several workgroups per CU (N = 20, R = 16384).
-  int dev = 0, cus = 256;
-  if (hipGetDevice(&dev) == hipSuccess)
-    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  const int cus = device_cus();
   const int split = P != PREC_FP64 || blocks > cus ? 1 : 4 / waves;
   small_dispatch<P>(small_nk<P>(a.Kp), [&](auto nk) {
     constexpr int NK = decltype(nk)::value;
     if constexpr (P == PREC_FP64 && NK <= 4) {  // at most two tiles
       if (split == 4) {
-        hipLaunchKernelGGL((anneal_small<P, J8, NK, 4>), dim3(blocks), dim3(256 * waves), lds, st, a);
+        if (a.z) hipLaunchKernelGGL((anneal_small<P, J8, NK, 4, true>), dim3(blocks), dim3(256 * waves), lds, st, a);
+        else hipLaunchKernelGGL((anneal_small<P, J8, NK, 4, false>), dim3(blocks), dim3(256 * waves), lds, st, a);
         e = hipGetLastError();
         return;
       }
       if (split == 2) {
-        hipLaunchKernelGGL((anneal_small<P, J8, NK, 2>), dim3(blocks), dim3(128 * waves), lds, st, a);
+        if (a.z) hipLaunchKernelGGL((anneal_small<P, J8, NK, 2, true>), dim3(blocks), dim3(128 * waves), lds, st, a);
+        else hipLaunchKernelGGL((anneal_small<P, J8, NK, 2, false>), dim3(blocks), dim3(128 * waves), lds, st, a);
         e = hipGetLastError();
         return;
       }
     }
-    hipLaunchKernelGGL((anneal_small<P, J8, NK, 1>), dim3(blocks), dim3(64 * waves), lds, st, a);
+    if constexpr (P == PREC_FP64) {
+      if (a.z) {
+        hipLaunchKernelGGL((anneal_small<P, J8, NK, 1, true>), dim3(blocks), dim3(64 * waves), lds, st, a);
+        e = hipGetLastError();
+        return;
+      }
+    }
+    hipLaunchKernelGGL((anneal_small<P, J8, NK, 1, false>), dim3(blocks), dim3(64 * waves), lds, st, a);
     e = hipGetLastError();
   });
   return e;
+}
+
+// With few replica blocks the FP64 noise (libm log and sincos) is a third of the small-N kernel's time while
+// most CUs are idle: another launch draws it on all of them, as many iterations ahead as 2 MB hold (a buffer
+// of 4 MB costs a new context 0.35 ms to allocate, 2 MB 0.1). A pair of launches costs about 7.5 us and an
+// iteration saves 0.5 us or more, hence at least 24 iterations per pair. ms per 1000 iterations without and
+// with it: N = 20, R = 256 (32 iterations per pair) 1.52, 1.20; N = 55, R = 131 (28) 2.84, 2.35. In FP32 and
+// BF16 an iteration saves 0.13 to 0.17 us, which pays for the launches from 64 iterations per pair on, but
+// hardly for the buffer: not built.
+constexpr size_t NOISE_BYTES = (size_t)2 << 20;
+
+size_t small_noise_bytes() { return NOISE_BYTES; }
+
+int small_noise_iters(int prec, int Mp, int R, int iters) {
+  if (prec != PREC_FP64) return 0;
+  const size_t per = (size_t)((R + 15) / 16) * Mp * 16 * sizeof(double);
+  const int n = (int)std::min(NOISE_BYTES / per, (size_t)iters);
+  return n >= 24 ? n : 0;
+}
+
+hipError_t launch_small_noise(const AnnealArgs& a, void* z, hipStream_t st) {
+  const int blocks = (a.R + 15) / 16;
+  const size_t waves = (size_t)(a.t_end - a.t_begin + 1) * blocks * (a.Mp / 16);
+  hipLaunchKernelGGL(small_noise, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st, a, (double*)z, blocks);
+  return hipGetLastError();
 }
 
 hipError_t launch_anneal_small(int prec, const AnnealArgs& a, hipStream_t st) {
@@ -1401,13 +1493,6 @@ static hipError_t launch_step_f(const AnnealArgs& a, const void* S_cur, void* S_
   const dim3 grid = tile_grid((a.N + T::TM - 1) / T::TM, (a.R + T::TR - 1) / T::TR);
   hipLaunchKernelGGL((anneal_step_tiled_f<P, JFMT, RT, CT, WM, WR, WPC>), grid, dim3(64 * T::W), lds, st, a, S_cur, S_next, t);
   return hipGetLastError();
-}
-
-static int device_cus() {
-  int dev = 0, cus = 256;
-  if (hipGetDevice(&dev) == hipSuccess)
-    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  return cus;
 }
 
 // Tile of the FP64 / FP32 iteration: 128 x 64 or 64 x 64 with eight waves, one workgroup per CU, or
