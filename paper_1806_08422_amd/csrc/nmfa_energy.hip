@@ -233,8 +233,9 @@ __global__ void energy_finish_kernel(const unsigned long long* __restrict__ E2, 
 }
 
 // n <= 256: one launch does all of it (the launches above take about 4.5 us each, whatever their work:
-// n = 173, R = 64 with fields 31 -> 10 us; n = 100, R = 16384 16 -> 8 us). A block owns 16 replicas and all rows: wave w the 16-row tiles w, w + 4, ...; the signs are
-// staged, zero-padded, in LDS, and J8p comes from L2.
+// n = 173, R = 64 with fields 31 -> 10 us; n = 100, R = 16384 16 -> 8 us). A block owns 16 replicas and
+// all rows: wave w the 16-row tiles w, w + 4, ...; the signs are staged, zero-padded, in LDS, and J8p
+// comes from L2.
 constexpr int ESM_NP = 256;
 __global__ __launch_bounds__(256) void energy_small_i8(const int8_t* __restrict__ J8p, int Np,
                                                        const double* __restrict__ h, int h_integral,

@@ -10,13 +10,14 @@
 // energy of Eq. 1 are evaluated.
 //
 // Kernels:
-//   anneal_small<P>   persistent: one workgroup owns 16 replicas and all N <= 256 spins for the
+//   anneal_small      persistent: one workgroup owns 16 replicas and all N <= 256 spins for the
 //                     whole anneal. J and the master state live in registers, the operand copy
 //                     of S is double-buffered in LDS; one barrier per iteration.
+//   small_noise       the noise of small FP64 runs with few replicas, drawn ahead on the whole chip.
 //   anneal_step_tiled, anneal_step_tiled_f
-//                     one iteration for large N as a tiled matrix product through LDS (BF16
-//                     operands on 256 x 128 workgroup tiles; FP64 and FP32 on 128 x 64, 64 x 64 or
-//                     32 x 32), with the fused epilogue.
+//                     one iteration for large N as a tiled matrix product through LDS with the fused
+//                     epilogue: BF16 operands on 256 x 128 workgroup tiles where they fill the chip,
+//                     and on 64 x 32 to 256 x 64; FP64 and FP32 on 128 x 64, 64 x 64 or 32 x 32.
 //   anneal_sparse*    degree-d graphs with J in ELL rows (see their own comments).
 //   readout_kernel    s~ = sign(s) (s = 0 reads +1).
 #include <hip/hip_runtime.h>
