@@ -98,6 +98,17 @@ struct EpilogueF32 {
     const float sg = (float)a.sigma;
     sigma_gauss4_f32(philox4x32_10<MODE>(q, r, t, 0u, a.key0, a.key1), -2.0f * 0.6931471805599453f * sg * sg, z);
   }
+  // sigma_gauss4_f32 for one half of the quad
+  __device__ static __forceinline__ void noise_half(float z[2], const AnnealArgs& a, uint32_t q, uint32_t r, uint32_t t,
+                                                    int half) {
+    const float sg = (float)a.sigma;
+    const Philox4 w = philox4x32_10<PHILOX_LOOP>(q, r, t, 0u, a.key0, a.key1);
+    const float u0 = fmaf((float)(half ? w.x2 : w.x0), 0x1p-32f, 0x1p-33f);
+    const float u1 = fmaf((float)(half ? w.x3 : w.x1), 0x1p-32f, 0x1p-33f);
+    const float rho = __builtin_amdgcn_sqrtf(-2.0f * 0.6931471805599453f * sg * sg * __builtin_amdgcn_logf(u0));
+    z[0] = rho * __builtin_amdgcn_cosf(u1);
+    z[1] = rho * __builtin_amdgcn_sinf(u1);
+  }
   template <int NV>
   __device__ static __forceinline__ void update(const float* acc, const float* inv, const float* hinv, float* s,
                                                 const float* z, const AnnealArgs& a, float coef_t) {
@@ -126,9 +137,10 @@ template <>
 struct Epilogue<PREC_BF16> : EpilogueF32<PREC_BF16> {};
 
 // ------------------------------------------------------------------------------------------
-// anneal_small<P, J8, NK, SPLIT, PRE>: see the file header. Wave w owns rows [16w, 16w+16) (FP64 with
+// anneal_small<P, J8, NK, SPLIT, PRE, LS>: see the file header. Wave w owns rows [16w, 16w+16) (FP64 with
 // SPLIT > 1: SPLIT waves share a tile's rows, see the launcher); grid = ceil(R / 16) workgroups,
-// workgroup b owns replicas [16b, 16b+16). Each lane keeps its part of J in registers (NK reads of 16
+// workgroup b owns replicas [16b, 16b+16) (LS > 1: 16 / LS of them, each in LS columns of the product
+// whose lanes share the replica's rows; while a CU is free for every workgroup, see the launcher). Each lane keeps its part of J in registers (NK reads of 16
 // bytes; J8: FP8 E4M3 in memory, widened to BF16). LDS: Ss[2][16][js] (op_t), js = padded row stride in
 // elements. The iterations are unrolled by two, so that the buffers' addresses are constants.
 // The body is shared with anneal_small_batched, where one launch carries replica blocks of many
@@ -143,10 +155,11 @@ struct Epilogue<PREC_BF16> : EpilogueF32<PREC_BF16> {};
 // (1.20 with the noise drawn ahead, PRE: launch_small_noise). Scheduling the
 // FP32 noise between the products (1.41) or drawing it after them in every second wave gained nothing.
 // ------------------------------------------------------------------------------------------
-template <int P, bool J8, int NK, int SPLIT = 1, bool PRE = false>
+template <int P, bool J8, int NK, int SPLIT = 1, bool PRE = false, int LS = 1>
 __device__ __forceinline__ void anneal_small_body(const AnnealArgs& a, const int rblock) {
   static_assert(SPLIT == 1 || P == PREC_FP64, "split tiles are built for FP64");
-  constexpr int NV = 4 / SPLIT;  // rows of a lane's quad that its wave updates
+  constexpr int SUB = SPLIT * LS, NV = 4 / SUB;  // rows of its quad that a lane updates
+  constexpr int RPB = 16 / LS;                   // replicas of the workgroup
   using Tr = Traits<P>;
   using op_t = typename Tr::op_t;
   using acc_t = typename Tr::acc_t;
@@ -164,8 +177,8 @@ __device__ __forceinline__ void anneal_small_body(const AnnealArgs& a, const int
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4;
   const int c = lane & 15;
-  const int r = rblock * 16 + c;       // replica of this lane
-  const int tile = wave / SPLIT, part = wave % SPLIT;
+  const int cr = c % RPB, r = rblock * RPB + cr;  // replica of this lane
+  const int tile = wave / SPLIT, part = wave % SPLIT * LS + c / RPB;  // part of the quad's rows
   const bool act = tile < (Mp >> 4);  // this wave owns (its part of) a row tile of the job
   const int quad0 = tile * 16 + 4 * g;    // first of this lane's four rows (accumulator layout)
   const int row0 = quad0 + NV * part;     // first of the rows this wave updates
@@ -204,7 +217,7 @@ __device__ __forceinline__ void anneal_small_body(const AnnealArgs& a, const int
   const acc_t* h_g = reinterpret_cast<const acc_t*>(a.hterm);
   acc_t* state = reinterpret_cast<acc_t*>(a.state);
   const bool live_r = r < a.R;
-  op_t* Sl = reinterpret_cast<op_t*>(smem) + (size_t)c * js;  // this lane's replica, buffer 0
+  op_t* Sl = reinterpret_cast<op_t*>(smem) + (size_t)cr * js;  // this lane's replica, buffer 0
   const int sbuf = 16 * js;                                   // elements of one buffer
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
@@ -221,12 +234,12 @@ __device__ __forceinline__ void anneal_small_body(const AnnealArgs& a, const int
   __syncthreads();
 
   auto draw = [&](acc_t* z, int t) {
-    if constexpr (SPLIT == 1) {
+    if constexpr (SUB == 1) {
       Epilogue<P>::template noise<PHILOX_LOOP>(z, a, q, (uint32_t)r, (uint32_t)t);
     } else {
       acc_t zz[2];
-      Epilogue<P>::noise_half(zz, a, q, (uint32_t)r, (uint32_t)t, SPLIT == 2 ? part : part >> 1);
-      if constexpr (SPLIT == 2) {
+      Epilogue<P>::noise_half(zz, a, q, (uint32_t)r, (uint32_t)t, SUB == 2 ? part : part >> 1);
+      if constexpr (SUB == 2) {
         z[0] = zz[0];
         z[1] = zz[1];
       } else {
@@ -241,8 +254,9 @@ __device__ __forceinline__ void anneal_small_body(const AnnealArgs& a, const int
   constexpr int NPRE = 4;
   typedef acc_t zvec __attribute__((ext_vector_type(NV)));
   zvec zr[PRE ? NPRE : 1];
-  const size_t zstep = (size_t)gridDim.x * (Mp >> 4) * 256;  // values per iteration
-  const acc_t* zl = reinterpret_cast<const acc_t*>(a.z) + ((size_t)rblock * (Mp >> 4) + tile) * 256 + lane * 4 + NV * part;
+  const size_t zstep = (size_t)((a.R + 15) / 16) * (Mp >> 4) * 256;  // values per iteration
+  const acc_t* zl = reinterpret_cast<const acc_t*>(a.z) + ((size_t)(rblock / LS) * (Mp >> 4) + tile) * 256 +
+                    (16 * g + rblock % LS * RPB + cr) * 4 + NV * part;
   auto read_z = [&](int t) {
     return *reinterpret_cast<const zvec*>(zl + (size_t)((t < a.t_end ? t : a.t_end) - a.t_begin) * zstep);
   };
@@ -273,10 +287,10 @@ __device__ __forceinline__ void anneal_small_body(const AnnealArgs& a, const int
       for (int u = 0; u < VEC; ++u) acc = Tr::mfma(af[u], bf[u], acc);
     }
     acc_t fld[NV];
-    if constexpr (SPLIT == 1) {
+    if constexpr (SUB == 1) {
 #pragma unroll
       for (int v = 0; v < 4; ++v) fld[v] = acc[v];
-    } else if constexpr (SPLIT == 2) {
+    } else if constexpr (SUB == 2) {
       fld[0] = part ? acc[2] : acc[0];
       fld[1] = part ? acc[3] : acc[1];
     } else {
@@ -350,9 +364,9 @@ constexpr int small_min_waves(int NK) {
   return P == PREC_FP64 ? 2 : (P == PREC_FP32 || NK > 4 ? 4 : 5);
 }
 
-template <int P, bool J8, int NK, int SPLIT, bool PRE>
+template <int P, bool J8, int NK, int SPLIT, bool PRE, int LS>
 __global__ __launch_bounds__(small_threads<P>(), small_min_waves<P>(NK)) void anneal_small(AnnealArgs a) {
-  anneal_small_body<P, J8, NK, SPLIT, PRE>(a, (int)blockIdx.x);
+  anneal_small_body<P, J8, NK, SPLIT, PRE, LS>(a, (int)blockIdx.x);
 }
 
 // The noise of iterations t_begin .. t_end for anneal_small, the values it would draw itself: a wave per
@@ -755,31 +769,42 @@ static hipError_t launch_small_t(const AnnealArgs& a, hipStream_t st) {
   // tile: 2.15; N = 33, two: 2.9 against 2.7), nor do several workgroups per CU (N = 20, R = 16384).
   const int cus = device_cus();
   const int split = P != PREC_FP64 || blocks > cus ? 1 : 4 / waves;
+  // While all its workgroups find a CU each, a workgroup takes 8 or (FP64) 4 replicas (LS = 2 or 4): the
+  // other columns of its product repeat them, and the lanes of the copies take over rows. us per iteration
+  // with LS = 1, 2, 4: FP64 N = 62, R = 1000 2.84, 1.72, 1.46, N = 100, R = 1000 5.67, 3.85, 3.41, N = 62,
+  // R = 2000 2.79, 1.79, 2.60, N = 20, R = 256 (two waves per tile) 1.15, 0.97; BF16 N = 173, R = 64 0.68,
+  // 0.60, 0.60, N = 256, R = 1024 0.92, 0.81, 0.85; FP32 N = 50, R = 1024 0.58, 0.49, 0.53. Two workgroups
+  // on a CU lose: BF16 N = 250, R = 4096 0.97, 1.63, FP32 N = 100, R = 4096 1.30, 2.19.
+  const int ls = P == PREC_FP64 && split == 1 && 4 * a.R <= 16 * cus ? 4 : (2 * a.R <= 16 * cus ? 2 : 1);
   small_dispatch<P>(small_nk<P>(a.Kp), [&](auto nk) {
     constexpr int NK = decltype(nk)::value;
+    auto launch = [&](auto split_c, auto ls_c, auto pre_c) {
+      constexpr int SP = decltype(split_c)::value, LS = decltype(ls_c)::value;
+      hipLaunchKernelGGL((anneal_small<P, J8, NK, SP, decltype(pre_c)::value, LS>), dim3((a.R * LS + 15) / 16),
+                         dim3(64 * SP * waves), lds, st, a);
+      e = hipGetLastError();
+    };
+    auto with_ls = [&](auto split_c, auto pre_c) {
+      constexpr int SP = decltype(split_c)::value;
+      if constexpr (P == PREC_FP64 && SP == 1) {
+        if (ls == 4) return launch(split_c, StInt<4>{}, pre_c);
+      }
+      if constexpr (SP <= 2) {
+        if (ls == 2) return launch(split_c, StInt<2>{}, pre_c);
+      }
+      launch(split_c, StInt<1>{}, pre_c);
+    };
+    auto with_pre = [&](auto split_c) {
+      if constexpr (P == PREC_FP64) {
+        if (a.z) return with_ls(split_c, StBool<true>{});
+      }
+      with_ls(split_c, StBool<false>{});
+    };
     if constexpr (P == PREC_FP64 && NK <= 4) {  // at most two tiles
-      if (split == 4) {
-        if (a.z) hipLaunchKernelGGL((anneal_small<P, J8, NK, 4, true>), dim3(blocks), dim3(256 * waves), lds, st, a);
-        else hipLaunchKernelGGL((anneal_small<P, J8, NK, 4, false>), dim3(blocks), dim3(256 * waves), lds, st, a);
-        e = hipGetLastError();
-        return;
-      }
-      if (split == 2) {
-        if (a.z) hipLaunchKernelGGL((anneal_small<P, J8, NK, 2, true>), dim3(blocks), dim3(128 * waves), lds, st, a);
-        else hipLaunchKernelGGL((anneal_small<P, J8, NK, 2, false>), dim3(blocks), dim3(128 * waves), lds, st, a);
-        e = hipGetLastError();
-        return;
-      }
+      if (split == 4) return with_pre(StInt<4>{});
+      if (split == 2) return with_pre(StInt<2>{});
     }
-    if constexpr (P == PREC_FP64) {
-      if (a.z) {
-        hipLaunchKernelGGL((anneal_small<P, J8, NK, 1, true>), dim3(blocks), dim3(64 * waves), lds, st, a);
-        e = hipGetLastError();
-        return;
-      }
-    }
-    hipLaunchKernelGGL((anneal_small<P, J8, NK, 1, false>), dim3(blocks), dim3(64 * waves), lds, st, a);
-    e = hipGetLastError();
+    with_pre(StInt<1>{});
   });
   return e;
 }
