@@ -150,9 +150,9 @@ struct Epilogue<PREC_BF16> : EpilogueF32<PREC_BF16> {};
 // (BF16, N = 100, R = 16384: 28 waves per CU, 593 cycles per wave and iteration; five or seven
 // waves per SIMD make no difference); FP32: the chain of 16x16x4 products (32 cycles each) beside it.
 // Against J in LDS, a rolled k loop and buffer addresses multiplied out in every iteration, per
-// iteration: BF16 N = 100, R = 16384 1.94 -> 1.73 us, N = 173, R = 64 1.09 -> 0.70, N = 256, R = 1024
-// 1.55 -> 0.97; FP32 N = 100, R = 4096 1.42 -> 1.35; FP64 N = 20, R = 256 2.73 -> 1.48
-// (1.20 with the noise drawn ahead, PRE: launch_small_noise). Scheduling the
+// iteration: BF16 N = 100, R = 16384 1.94 -> 1.73 us, N = 173, R = 64 1.09 -> 0.60, N = 256, R = 1024
+// 1.55 -> 0.81; FP32 N = 100, R = 4096 1.42 -> 1.35; FP64 N = 20, R = 256 2.73 -> 0.88
+// (with the noise drawn ahead, PRE: launch_small_noise). Scheduling the
 // FP32 noise between the products (1.41) or drawing it after them in every second wave gained nothing.
 // ------------------------------------------------------------------------------------------
 template <int P, bool J8, int NK, int SPLIT = 1, bool PRE = false, int LS = 1>
@@ -764,9 +764,10 @@ static hipError_t launch_small_t(const AnnealArgs& a, hipStream_t st) {
   hipError_t e = hipErrorInvalidValue;
   // FP64: while every wave of a workgroup can have a SIMD to itself, a tile's waves share its rows,
   // each running the whole matrix product (the matrix cores are idle) and the libm epilogue of its
-  // rows only. N = 20, R = 256: 2.6 us per iteration with one wave per tile, 1.5 with two; N = 16: 2.4
-  // with one, 1.4 with two, 1.2 with four. Two waves on a SIMD gain nothing (N = 20, four waves per
-  // tile: 2.15; N = 33, two: 2.9 against 2.7), nor do several workgroups per CU (N = 20, R = 16384).
+  // rows only. us per iteration with 16 replicas per workgroup: N = 20, R = 256 2.6 with one wave per tile,
+  // 1.5 with two; N = 16 2.4 with one, 1.4 with two, 1.2 with four. Two waves on a SIMD gain nothing (N =
+  // 20, four waves per tile: 2.15; N = 33, two: 2.9 against 2.7), nor do several workgroups per CU (N =
+  // 20, R = 16384).
   const int cus = device_cus();
   const int split = P != PREC_FP64 || blocks > cus ? 1 : 4 / waves;
   // While all its workgroups find a CU each, a workgroup takes 8 or (FP64) 4 replicas (LS = 2 or 4): the
@@ -812,10 +813,10 @@ static hipError_t launch_small_t(const AnnealArgs& a, hipStream_t st) {
 // With few replica blocks the FP64 noise (libm log and sincos) is a third of the small-N kernel's time while
 // most CUs are idle: another launch draws it on all of them, as many iterations ahead as 2 MB hold (a buffer
 // of 4 MB costs a new context 0.35 ms to allocate, 2 MB 0.1). A pair of launches costs about 7.5 us and an
-// iteration saves 0.5 us or more, hence at least 24 iterations per pair. ms per 1000 iterations without and
-// with it: N = 20, R = 256 (32 iterations per pair) 1.52, 1.20; N = 55, R = 131 (28) 2.84, 2.35. In FP32 and
-// BF16 an iteration saves 0.13 to 0.17 us, which pays for the launches from 64 iterations per pair on, but
-// hardly for the buffer: not built.
+// iteration saves 0.4 us or more, hence at least 24 iterations per pair. ms per 1000 iterations without and
+// with it: N = 16, R = 64 1.12, 0.58; N = 20, R = 256 (32 iterations per pair) 1.20, 0.88; N = 35, R = 217
+// (24) 1.29, 1.12; N = 100, R = 64 (36) 3.79, 2.99. In FP32 and BF16 an iteration saves 0.13 to 0.17 us,
+// which pays for the launches from 64 iterations per pair on, but hardly for the buffer: not built.
 constexpr size_t NOISE_BYTES = (size_t)2 << 20;
 
 size_t small_noise_bytes() { return NOISE_BYTES; }
