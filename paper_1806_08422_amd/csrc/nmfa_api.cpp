@@ -537,12 +537,17 @@ extern "C" int nmfa_create(int32_t n, const double* J, const double* h, const nm
   if (jbytes) parallel_rows(n, [&](int lo, int hi) {
   CouplingCodes codes;
   for (int i = lo; i < hi; ++i) {
-    if (jfmt2 == 2) {  // exact in FP4 (so in FP8 as well), two to a byte, the even column low; Kp is even
+    if (jfmt2 == 2) {  // two to a byte, the even column low; Kp is even
       const double* src = Jf + (size_t)i * n;
       unsigned char* dst = &jbuf[(size_t)i * Kp / 2];
-      for (int j = 0; j + 1 < n; j += 2)
-        dst[j / 2] = (uint8_t)(CouplingCodes::fp4(src[j]) | (CouplingCodes::fp4(src[j + 1]) << 4));
-      if (n & 1) dst[n / 2] = (uint8_t)CouplingCodes::fp4(src[n - 1]);
+      // what FP4 holds is the coupling that the precision prescribes: with FP8 J the given one rounded to
+      // FP8, which is an FP4 value for given ones that are not (1.01). Halves up to 6 are FP8 values.
+      const bool fp8j = c->prec == NMFA_FP8J_BF16S || fp8s;
+      auto code = [&](double v) {
+        return CouplingCodes::fp4(fp8j && half_index(v) < 0 ? codes.fp8_value(v) : v);
+      };
+      for (int j = 0; j + 1 < n; j += 2) dst[j / 2] = (uint8_t)(code(src[j]) | (code(src[j + 1]) << 4));
+      if (n & 1) dst[n / 2] = (uint8_t)code(src[n - 1]);
       continue;
     }
     for (int j = 0; j < n; ++j) {
