@@ -202,17 +202,17 @@ __global__ __launch_bounds__(256) void energy_pairs_i8(const int8_t* __restrict_
 #pragma unroll
   for (int ct = 0; ct < 4; ++ct) {
     const int r = rep0 + wr + 16 * ct + c;
-    int part = 0;
+    long long part = 0;  // other values than +-1 are taken as the integers they are: a row's product may need 36 bits
 #pragma unroll
     for (int rt = 0; rt < 4; ++rt) {
       const int row = m0 + wm + 16 * rt + 4 * g4;
       const int sv = (r < R && row < Np) ? *reinterpret_cast<const int*>(Sp + (size_t)r * Np + row) : 0;  // 4 signs
 #pragma unroll
-      for (int v = 0; v < 4; ++v) part += (int)(int8_t)(sv >> (8 * v)) * acc[rt][ct][v];
+      for (int v = 0; v < 4; ++v) part += (long long)(int8_t)(sv >> (8 * v)) * acc[rt][ct][v];
     }
     part += __shfl_xor(part, 16, 64);
     part += __shfl_xor(part, 32, 64);
-    if (g4 == 0 && r < R) atomicAdd(&E2[r], (unsigned long long)(long long)part);
+    if (g4 == 0 && r < R) atomicAdd(&E2[r], (unsigned long long)part);
   }
 }
 
@@ -243,7 +243,7 @@ __global__ __launch_bounds__(256) void energy_small_i8(const int8_t* __restrict_
                                                        long long* __restrict__ E_int, double* __restrict__ E) {
   __shared__ __align__(16) int8_t sp[16 * (ESM_NP + 16)];
   __shared__ double hs[ESM_NP];
-  __shared__ int red[4][16];
+  __shared__ long long red[4][16];
   const int st = Np + 16;  // row stride: the 16 rows of a fragment read fall on distinct banks
   const int r0 = blockIdx.x * 16;
   for (int idx = threadIdx.x; idx < 16 * Np; idx += 256) {
@@ -255,7 +255,7 @@ __global__ __launch_bounds__(256) void energy_small_i8(const int8_t* __restrict_
   __syncthreads();
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int c = lane & 15, g4 = lane >> 4;
-  int part = 0;
+  long long part = 0;
   for (int row0 = 16 * wave; row0 < Np; row0 += 64) {
     i32x4 acc = i32x4{0, 0, 0, 0};
     const int8_t* a_ptr = J8p + (size_t)(row0 + c) * Np + 16 * g4;
@@ -265,7 +265,7 @@ __global__ __launch_bounds__(256) void energy_small_i8(const int8_t* __restrict_
                                                   0, 0);
     const int sv = *reinterpret_cast<const int*>(sp + c * st + row0 + 4 * g4);
 #pragma unroll
-    for (int v = 0; v < 4; ++v) part += (int)(int8_t)(sv >> (8 * v)) * acc[v];
+    for (int v = 0; v < 4; ++v) part += (long long)(int8_t)(sv >> (8 * v)) * acc[v];
   }
   part += __shfl_xor(part, 16, 64);
   part += __shfl_xor(part, 32, 64);
