@@ -325,7 +325,7 @@ __global__ __launch_bounds__(256) void energy_f64(const double* __restrict__ J, 
   const int nb = (N + 63) / 64;
   double total = 0.0;  // of replica rep0 + threadIdx.x
   for (int b = blockIdx.x; b < nb; b += gridDim.x) {
-    const int arow = min(64 * b + 16 * wave + Tr::a_row(c), N - 1);  // rows beyond N meet signs of 0
+    const int arow = min(64 * b + 16 * wave + Tr::a_row(c), N - 1);  // rows beyond N are left out of the sums
     const double* Jr = J + (size_t)arow * N + g;
     f64x4 acc[CT];
 #pragma unroll
@@ -381,8 +381,8 @@ __global__ __launch_bounds__(256) void energy_f64(const double* __restrict__ J, 
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int i = 64 * b + 16 * wave + 4 * g + v;
-        const double s = (r < R && i < N) ? (double)spins[(size_t)r * N + i] : 0.0;
-        p = __builtin_fma(s, acc[ct][v], p);
+        // rows beyond N are left out: they repeat row N - 1, whose y may be infinite (0 x inf)
+        if (r < R && i < N) p = __builtin_fma((double)spins[(size_t)r * N + i], acc[ct][v], p);
       }
       p += __shfl_xor(p, 16, 64);
       p += __shfl_xor(p, 32, 64);
