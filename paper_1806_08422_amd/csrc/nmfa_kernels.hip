@@ -27,6 +27,7 @@
 
 #include "nmfa_device.h"
 #include "nmfa_internal.h"
+#include "nmfa_plan.h"
 
 namespace nmfa {
 
@@ -1541,43 +1542,17 @@ static hipError_t launch_step_f_pick(const AnnealArgs& a, const void* S_cur, voi
   return launch_step_f<P, 0, 1, 1, 2, 2, 2>(a, S_cur, S_next, t, st);
 }
 
-// Tile of the BF16 iteration. The cost of a tile size in us, fitted to measurements at N = 2100, 4100 and
-// 8192, R = 64 .. 1024 (within 10 % of them but for a few at 2100): `once` plus, for every time the tiles
-// fill the chip, 2 us and a time per 128-k block, s1 while a CU has one workgroup and s2 with the two it
-// can hold. 64 x 32 is the least serial time for a few tiles; 128 x 32 (BF16 J: 128 x 64) and 256 x 64
-// read less per product; 256 x 128 is the best that fills the chip whole. Measured with 256 x 128 always
-// and with this rule, us per iteration: FP4 J N = 2100, R = 64 39.0 -> 10.8, R = 1024 44 -> 30; N = 4100,
-// R = 200 67 -> 19; N = 8192, R = 64 110 -> 27, R = 256 113 -> 47, R = 512 117 -> 84, R = 1024 142 (the
-// next best, 256 x 64: 165); FP8 J N = 4100, R = 200 72 -> 21, R = 512 74 -> 51; BF16 J N = 2100,
-// R = 300 45 -> 15, N = 8192, R = 64 118 -> 28, R = 256 122 -> 62, R = 512 127 -> 121, R = 1024 162 (the
-// next best, 128 x 64: 245).
 template <int JFMT>
-static hipError_t launch_step_b_pick(const AnnealArgs& a, const void* S_cur, void* S_next, int t, hipStream_t st) {
+static hipError_t launch_step_b(const AnnealArgs& a, const void* S_cur, void* S_next, int t, hipStream_t st) {
   constexpr int P = PREC_BF16;
-  const int cus = device_cus();
-  auto cost = [&](int tm, int tr, int per_cu, double once, double s1, double s2) {
-    const long tiles = (long)((a.N + tm - 1) / tm) * ((a.R + tr - 1) / tr), full = tiles / (per_cu * cus);
-    const long rest = tiles % (per_cu * cus);
-    const double nb = (a.N + 127) / 128;
-    return once + full * (2 + s2 * nb) + (rest == 0 ? 0.0 : 2 + (rest <= cus ? s1 : s2) * nb);
-  };
+  const StepTile tile = step_pick(JFMT, a.N, a.R, device_cus()).tile;
+  if (tile == STEP_64X32) return launch_step_f<P, JFMT, 1, 2, 4, 1, 2>(a, S_cur, S_next, t, st);
   if constexpr (JFMT == 0) {
-    if ((long)((a.N + 63) / 64) * ((a.R + 31) / 32) <= cus)  // a workgroup per CU: the longer ring (s1 = 0.37)
-      return launch_step_f<P, JFMT, 1, 2, 4, 1, 1>(a, S_cur, S_next, t, st);
-    const double c64 = cost(64, 32, 2, 3, 0.58, 0.65), c128 = cost(128, 64, 1, 8, 0.88, 0.88),
-                 c256 = cost(256, 128, 1, 6, 2.3, 2.3);
-    if (c64 <= c128 && c64 <= c256) return launch_step_f<P, JFMT, 1, 2, 4, 1, 2>(a, S_cur, S_next, t, st);
-    if (c128 <= c256) return launch_step_f<P, JFMT, 2, 2, 4, 2, 1>(a, S_cur, S_next, t, st);
+    if (tile == STEP_64X32_ALONE) return launch_step_f<P, JFMT, 1, 2, 4, 1, 1>(a, S_cur, S_next, t, st);
+    if (tile == STEP_128) return launch_step_f<P, JFMT, 2, 2, 4, 2, 1>(a, S_cur, S_next, t, st);
   } else {
-    constexpr bool F4 = JFMT == 2;
-    const double c64 = cost(64, 32, 2, 3, F4 ? 0.37 : 0.36, F4 ? 0.53 : 0.52),
-                 c128 = cost(128, 32, 2, F4 ? 4 : 5, F4 ? 0.39 : 0.5, F4 ? 0.7 : 0.85),
-                 c256s = cost(256, 64, 1, 10, F4 ? 1.1 : 1.15, F4 ? 1.1 : 1.15),
-                 c256 = cost(256, 128, 1, 6, F4 ? 2.08 : 2.15, F4 ? 2.08 : 2.15);
-    const double least = std::min(std::min(c64, c128), std::min(c256s, c256));
-    if (c64 == least) return launch_step_f<P, JFMT, 1, 2, 4, 1, 2>(a, S_cur, S_next, t, st);
-    if (c128 == least) return launch_step_f<P, JFMT, 1, 2, 8, 1, 2>(a, S_cur, S_next, t, st);
-    if (c256s == least) return launch_step_f<P, JFMT, 2, 4, 8, 1, 1>(a, S_cur, S_next, t, st);
+    if (tile == STEP_128) return launch_step_f<P, JFMT, 1, 2, 8, 1, 2>(a, S_cur, S_next, t, st);
+    if (tile == STEP_256X64) return launch_step_f<P, JFMT, 2, 4, 8, 1, 1>(a, S_cur, S_next, t, st);
   }
   return launch_step_tiled<JFMT>(a, S_cur, S_next, t, st);
 }
@@ -1590,9 +1565,9 @@ hipError_t launch_anneal_step(int prec, int jfmt, const AnnealArgs& a, const voi
     case PREC_FP32: return launch_step_f_pick<PREC_FP32>(a, S_cur, S_next, t, st);
     case PREC_BF16:
     case PREC_FP8J_BF16S:
-      if (jfmt == 2) return launch_step_b_pick<2>(a, S_cur, S_next, t, st);
-      if (jfmt == 1) return launch_step_b_pick<1>(a, S_cur, S_next, t, st);
-      return launch_step_b_pick<0>(a, S_cur, S_next, t, st);
+      if (jfmt == 2) return launch_step_b<2>(a, S_cur, S_next, t, st);
+      if (jfmt == 1) return launch_step_b<1>(a, S_cur, S_next, t, st);
+      return launch_step_b<0>(a, S_cur, S_next, t, st);
   }
   return hipErrorInvalidValue;
 }
