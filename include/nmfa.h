@@ -193,7 +193,8 @@ int nmfa_trajectory(nmfa_ctx *c, double *out);
 /* Information about a context: writes n, the precision and the kernel path (0 = persistent
  * small-N kernel with J in LDS; 1 = per-iteration kernel; 2 = persistent XCD-group kernel
  * (J rows in registers as FP8 or BF16, n <= 2048, or in LDS) whose groups exchanged spins through
- * one XCD's L2; 3 = the same with device-scope fences, used when a group's workgroups were not all
+ * one XCD's L2 (where J is neither FP4-exact nor forced onto this kernel, large replica counts run
+ * the per-iteration kernel instead, and path is 1 after such an anneal); 3 = the same with device-scope fences, used when a group's workgroups were not all
  * placed on one XCD; 4 and 5 = the XCD-group kernel with J rows held in registers as FP4
  * (FP4-exact couplings, n <= 2048), exchange as for 2 and 3; 6 = the sparse kernel, J as nonzeros per row (chosen for n > 256 when every
  * row has at most min(64, n/8) couplings and either the register variant below applies or no

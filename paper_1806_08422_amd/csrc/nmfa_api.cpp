@@ -15,6 +15,7 @@
 #include "../../include/nmfa.h"
 #include "nmfa_ctx.h"
 #include "nmfa_internal.h"
+#include "nmfa_plan.h"
 
 using namespace nmfa;
 
@@ -499,11 +500,14 @@ extern "C" int nmfa_create(int32_t n, const double* J, const double* h, const nm
     c->Kp = xrj_kp(n);
     c->lds_stride = 0;
     c->jfmt = x_jfmt;
+    c->lds_Kp = x_ok ? Kp_x : 0;
+    c->nbuf = x_nbuf;
   } else if (c->path == 2) {
     c->Mp = Mp_x;
     c->Kp = Kp_x;
     c->lds_stride = 0;
     c->jfmt = x_jfmt;
+    c->lds_Kp = Kp_x;
     c->nbuf = x_nbuf;
   } else {
     c->Mp = (int)round_up(n, 256);  // the tiled per-iteration kernels work on 256-row (BF16) and 128-row (FP64) tiles
@@ -512,7 +516,8 @@ extern "C" int nmfa_create(int32_t n, const double* J, const double* h, const nm
     c->jfmt = bf ? x_jfmt : 0;  // BF16-operand precisions: J streamed as FP4 / FP8 where exact
   }
   c->Ks = c->path == 2 ? xcd_spin_stride(c->Kp) : c->Kp;
-  const int Mp = c->Mp, Kp = c->Kp;
+  // rows of J in memory: the per-iteration kernel, which may run beside the small tiles, needs Kp
+  const int Mp = c->path == 2 && c->xvar == 3 ? c->Kp : c->Mp, Kp = c->Kp;
 
   // normalisers sqrt(h_i^2 + sum_j J_ij^2) in FP64; a zero normaliser gives inv = 0
   std::vector<double> inv(Mp, 0.0), hterm(Mp, 0.0);
@@ -829,22 +834,33 @@ extern "C" int nmfa_anneal_range(nmfa_ctx* c, int32_t R, int32_t t_f, int32_t t_
 //   128 x 16 (tile 1)       1.7    1.8    2.1                      2.1   2.2   4.3    8.5
 //   128 x 32 (tile 2)       2.1    2.4    3.2                      3.0   3.2   3.3    6.4
 //   256 x 32 (anneal_xrj8)  3.2    3.6    5.0                      5.0   5.0   5.0    5.1
+// FP8 and BF16 J have no 256 x 32 tile, and above N = 1024 mostly only 64 x 16 fits the registers: from some R
+// on the LDS-J kernel (64 rows x 128 replicas: 2 us + 6 (BF16) or 6.5 (FP8) per 1024 k, 7.7 with two chunk
+// buffers only, and 10 us more with fences) or the per-iteration kernel is faster. us per iteration, small
+// tiles / LDS-J / per-iteration: FP8 J N = 1300, R = 512 8.2 / 10.9 / 11.7, R = 1024 16.2 / 10.9 / 16.9, R = 2048
+// 32 / 21 / 28, R = 4096 65 / 43 / 37; N = 2000, R = 1024 20 / 17 / 22, R = 2048 40 / 34 / 37, R = 4096 80 / 67 / 49;
+// BF16 J (which fits LDS up to N = 1024) N = 1500, R = 1024 17 / - / 20, R = 2048 34 / - / 38, R = 4096 64 / - /
+// 41; N = 2000, R = 2048 43 / - / 43, R = 4096 80 / - / 50; N = 1000, R = 8192 25 / 34 / -. Same bits whichever runs.
 // Launches in which every XCD holds whole groups need groups in multiples of eight; the others pay
 // for device-scope fences, most with the smallest tile (N = 2000, R = 100: 2.6 -> 7.0, 3.6 -> 5.3,
 // 4.9 -> 6.7 and 7.3 -> 8.8 us). Two workgroups per CU gained nothing (128 x 16, R = 512: 7.0 us for
 // one launch of 512 workgroups, 2 x 3.5 for two of 256), so width counts one per CU.
 bool ctx_group_plan(const nmfa_ctx* c, int32_t R, int width, GroupPlan* out) {
   if (c->path != 2) return false;
+  int cus = width;  // the per-iteration kernel's launches need not be resident: they may take every CU
+  (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device);
   width = std::min(width, GROUP_MAX_WGS);
-  // a, b, fences of tiles 0, 1, 2 with BF16 and with FP8 spins
-  static const double kTime[2][3][3] = {{{0.9, 0.75, 4.0}, {1.0, 1.2, 1.8}, {1.4, 1.7, 1.8}},
-                                        {{1.2, 0.4, 4.0}, {1.5, 0.32, 1.8}, {1.65, 0.78, 1.8}}};
+  // a, b, fences of tiles 0, 1, 2 with FP4 J, with FP8 spins, and with FP8 or BF16 J
+  static const double kTime[3][3][3] = {{{0.9, 0.75, 4.0}, {1.0, 1.2, 1.8}, {1.4, 1.7, 1.8}},
+                                        {{1.2, 0.4, 4.0}, {1.5, 0.32, 1.8}, {1.65, 0.78, 1.8}},
+                                        {{0.55, 1.0, 4.0}, {1.1, 1.25, 1.8}, {1.5, 1.9, 1.8}}};
   const bool fp8s = c->xvar == 2;
+  const int kind = fp8s ? 1 : (c->xvar == 3 ? 2 : 0);
   const int fmt = fp8s ? XRS_FP8S : c->jfmt;
   bool any = false;
   auto consider = [&](int tile, int rows, int rg, double a, double b, double fences) {
-    const int P = c->Mp / rows, G = (R + rg - 1) / rg;
-    const double t = a + b * c->Kp / 1024.0;
+    const int P = tile == TILE_LDS ? (c->n + rows - 1) / rows : c->Mp / rows, G = (R + rg - 1) / rg;
+    const double t = a + b * (tile == TILE_LDS ? c->lds_Kp : c->Kp) / 1024.0;
     const int local = width / (8 * P) * 8, fenced = width / P;
     for (const int per : {local, fenced}) {
       if (per < 1) continue;
@@ -858,16 +874,23 @@ bool ctx_group_plan(const nmfa_ctx* c, int32_t R, int width, GroupPlan* out) {
   if (c->xvar != 0)
     for (int tile : {2, 1, 0})
       if (xrs_applies(fmt, tile, c->Kp))
-        consider(tile, xrs_rows(tile), xrs_group_replicas(tile), kTime[fp8s][tile][0], kTime[fp8s][tile][1],
-                 kTime[fp8s][tile][2]);
-  if (c->xvar == 0) consider(-1, xcd_rows(), xcd_group_replicas(), 2.0, 5.6, 1.0);
-  if (c->xvar == 1) consider(-1, xrj_rows(0), xrj_group_replicas(0), 2.1, 2.6, 0.8);
-  if (c->xvar == 2) consider(-1, xrj_rows(1), xrj_group_replicas(1), 2.6, 1.2, 0.8);
+        consider(tile, xrs_rows(tile), xrs_group_replicas(tile), kTime[kind][tile][0], kTime[kind][tile][1],
+                 kTime[kind][tile][2]);
+  const double lds_b = c->jfmt == 2 ? 5.6 : (c->jfmt == 0 ? 6.0 : (c->nbuf > 2 ? 6.5 : 7.7));
+  if (c->lds_Kp > 0) consider(TILE_LDS, xcd_rows(), xcd_group_replicas(), 2.0, lds_b, 10.0);
+  if (c->xvar == 1) consider(TILE_LARGE, xrj_rows(0), xrj_group_replicas(0), 2.1, 2.6, 0.8);
+  if (c->xvar == 2) consider(TILE_LARGE, xrj_rows(1), xrj_group_replicas(1), 2.6, 1.2, 0.8);
+  if (c->xvar == 3 && !(c->flags & NMFA_FLAG_FORCE_XCD)) {
+    const double us = 1.1 * step_pick(c->jfmt, c->n, R, cus).us;  // below n = 2100 its estimate is a little low
+    if (!any || us < out->us) {
+      *out = GroupPlan{TILE_STEP, 1, 1, 0, 1, us};
+      any = true;
+    }
+  }
   if (!any) {  // not even one group fits in width: one group per launch
     width = 1 << 20;
-    if (c->xvar == 0) consider(-1, xcd_rows(), xcd_group_replicas(), 2.0, 5.6, 1.0);
-    else if (c->xvar == 3) consider(0, xrs_rows(0), xrs_group_replicas(0), 0.9, 0.75, 4.0);
-    else consider(-1, xrj_rows(c->xvar == 2), xrj_group_replicas(c->xvar == 2), 2.1, 2.6, 0.8);
+    if (c->xvar == 0) consider(TILE_LDS, xcd_rows(), xcd_group_replicas(), 2.0, 5.6, 1.0);
+    else consider(TILE_LARGE, xrj_rows(c->xvar == 2), xrj_group_replicas(c->xvar == 2), 2.1, 2.6, 0.8);
     out->per_launch = 1;
     out->us = 1e9;
     return false;
@@ -888,6 +911,64 @@ static int small_noise_ahead(nmfa_ctx* c, const AnnealArgs& a, hipStream_t st) {
   (void)hipGetLastError();
   c->d_z = nullptr;
   return 0;
+}
+
+// All iterations of a run on the group kernel of plan gp, launches of at most width workgroups one after the other.
+static int launch_groups(nmfa_ctx* c, AnnealArgs a, const GroupPlan& gp, int width, hipStream_t st) {
+  const int Rg = gp.rg, G = gp.G, P = gp.P, per_launch = gp.per_launch;
+  HIP_TRY(launch_pack_state(c->prec, c->d_state, c->d_S[a.t_begin & 1], c->n, a.R, c->Kp, c->Ks, G * Rg,
+                            a.t_begin == 1 ? 1 : 0, st));
+  HIP_TRY(hipEventRecord(c->ev0, st));
+  if (gp.tile == TILE_LDS) a.Kp = c->lds_Kp;
+  c->launches = 0;
+  for (int gb = 0; gb < G; gb += per_launch) {
+    const int ng = std::min(per_launch, G - gb);
+    // workgroups are dispatched round robin over the eight XCDs: a multiple of 8 P of them, where
+    // that many fit, gives every XCD a multiple of P, so that every group exchanges through one L2
+    const int even = (ng + 7) / 8 * 8 * P;
+    const int grid = even <= width ? even : ng * P;
+    if (gb > 0 || a.t_begin > 1)  // fresh registration and barrier counters; abort and mode persist
+      HIP_TRY(launch_zero_words(reinterpret_cast<uint32_t*>(c->d_ctl), 0, 17, 64, (size_t)xcd_ctl_words(), st));
+    XcdArgs x{};
+    x.S[0] = c->d_S[0];
+    x.S[1] = c->d_S[1];
+    x.ks = c->Ks;
+    x.jk = c->Kp;
+    x.ctl = c->d_ctl;
+    x.P = P;
+    x.group_base = gb;
+    x.groups = ng;
+    x.force_fenced = (c->flags & NMFA_FLAG_FORCE_FENCED) ? 1 : 0;
+    x.nbuf = c->nbuf;
+    if (gp.tile >= 0) HIP_TRY(launch_anneal_xrs(c->xvar == 2 ? XRS_FP8S : c->jfmt, gp.tile, a, x, grid, st));
+    else if (gp.tile == TILE_LDS) HIP_TRY(launch_anneal_xcd(c->jfmt, a, x, grid, st));
+    else if (c->xvar == 2) HIP_TRY(launch_anneal_xrj8(a, x, grid, st));
+    else HIP_TRY(launch_anneal_xrj(a, x, grid, st));
+    ++c->launches;
+  }
+  HIP_TRY(hipEventRecord(c->evm, st));
+  c->ctl_pending = true;
+  return NMFA_OK;
+}
+
+// All iterations of a run as one launch of the per-iteration kernel each.
+static int launch_steps(nmfa_ctx* c, AnnealArgs a, hipStream_t st) {
+  a.Mp = a.Kp;  // rows of the copy of J
+  if (a.t_begin == 1)
+    HIP_TRY(launch_zero_words(reinterpret_cast<uint32_t*>(c->d_state), 0, (size_t)a.R * c->n * c->acc_size() / 4, 0, 0,
+                              st));
+  HIP_TRY(launch_pack_state(c->prec, c->d_state, c->d_S[0], c->n, a.R, c->Kp, c->Kp, a.Rp, a.t_begin == 1 ? 1 : 0,
+                            st));
+  HIP_TRY(hipEventRecord(c->ev0, st));
+  int cur = 0;
+  for (int t = a.t_begin; t <= a.t_end; ++t) {
+    HIP_TRY(launch_anneal_step(c->prec, c->jfmt, a, c->d_S[cur], c->d_S[cur ^ 1], t, st));
+    cur ^= 1;
+  }
+  c->launches = a.t_end - a.t_begin + 1;
+  HIP_TRY(hipEventRecord(c->evm, st));
+  HIP_TRY(launch_readout(c->prec, c->d_state, c->d_spins, (size_t)a.R * c->n, st));
+  return NMFA_OK;
 }
 
 int ctx_launch_run(nmfa_ctx* c, int32_t R, int32_t t_f, int32_t t_begin, int32_t t_end, uint64_t seed,
@@ -917,64 +998,22 @@ int ctx_launch_run(nmfa_ctx* c, int32_t R, int32_t t_f, int32_t t_begin, int32_t
                                  (c->flags & NMFA_FLAG_SPARSE_GENERIC) ? 0 : 1, &c->sp_rq, st));
     c->launches = 1;
     HIP_TRY(hipEventRecord(c->evm, st));
-  } else if (c->path == 2) {
-    int width = 0;
-    HIP_TRY(hipDeviceGetAttribute(&width, hipDeviceAttributeMultiprocessorCount, c->device));
-    if (max_workgroups > 0) width = std::min(width, max_workgroups);
-    GroupPlan gp;
-    ctx_group_plan(c, R, width, &gp);
-    const int Rg = gp.rg, G = gp.G, P = gp.P, per_launch = gp.per_launch;
-    HIP_TRY(launch_pack_state(c->prec, c->d_state, c->d_S[t_begin & 1], c->n, R, c->Kp, c->Ks, G * Rg,
-                              t_begin == 1 ? 1 : 0, st));
-    // A new run clears the whole control block; a continued one (and every launch after the
-    // first) only the registration and barrier counters, so that an abort in an earlier chunk of
-    // the run stays raised, ends the later ones at once, and is reported when the run is read.
-    const size_t ctl_words = (size_t)xcd_ctl_words();
-    uint32_t* ctl = reinterpret_cast<uint32_t*>(c->d_ctl);
-    if (t_begin == 1) HIP_TRY(launch_zero_words(ctl, 0, ctl_words, 0, 0, st));
-    HIP_TRY(hipEventRecord(c->ev0, st));
-    c->launches = 0;
-    for (int gb = 0; gb < G; gb += per_launch) {
-      const int ng = std::min(per_launch, G - gb);
-      // workgroups are dispatched round robin over the eight XCDs: a multiple of 8 P of them, where
-      // that many fit, gives every XCD a multiple of P, so that every group exchanges through one L2
-      const int even = (ng + 7) / 8 * 8 * P;
-      const int grid = even <= width ? even : ng * P;
-      if (gb > 0 || t_begin > 1) {  // fresh registration and barrier counters; abort and mode persist
-        HIP_TRY(launch_zero_words(ctl, 0, 17, 64, ctl_words, st));
-      }
-      XcdArgs x{};
-      x.S[0] = c->d_S[0];
-      x.S[1] = c->d_S[1];
-      x.ks = c->Ks;
-      x.ctl = c->d_ctl;
-      x.P = P;
-      x.group_base = gb;
-      x.groups = ng;
-      x.force_fenced = (c->flags & NMFA_FLAG_FORCE_FENCED) ? 1 : 0;
-      x.nbuf = c->nbuf;
-      if (gp.tile >= 0) HIP_TRY(launch_anneal_xrs(c->xvar == 2 ? XRS_FP8S : c->jfmt, gp.tile, a, x, grid, st));
-      else if (c->xvar == 2) HIP_TRY(launch_anneal_xrj8(a, x, grid, st));
-      else if (c->xvar) HIP_TRY(launch_anneal_xrj(a, x, grid, st));
-      else HIP_TRY(launch_anneal_xcd(c->jfmt, a, x, grid, st));
-      ++c->launches;
-    }
-    HIP_TRY(hipEventRecord(c->evm, st));
-    c->ctl_pending = true;
   } else {
-    if (t_begin == 1)
-      HIP_TRY(launch_zero_words(reinterpret_cast<uint32_t*>(c->d_state), 0, (size_t)R * c->n * c->acc_size() / 4, 0, 0,
-                                st));
-    HIP_TRY(launch_pack_state(c->prec, c->d_state, c->d_S[0], c->n, R, c->Kp, c->Kp, a.Rp, t_begin == 1 ? 1 : 0, st));
-    HIP_TRY(hipEventRecord(c->ev0, st));
-    int cur = 0;
-    for (int t = t_begin; t <= t_end; ++t) {
-      HIP_TRY(launch_anneal_step(c->prec, c->path == 1 ? c->jfmt : 0, a, c->d_S[cur], c->d_S[cur ^ 1], t, st));
-      cur ^= 1;
+    GroupPlan gp;
+    int width = 0;
+    if (c->path == 2) {
+      HIP_TRY(hipDeviceGetAttribute(&width, hipDeviceAttributeMultiprocessorCount, c->device));
+      if (max_workgroups > 0) width = std::min(width, max_workgroups);
+      ctx_group_plan(c, R, width, &gp);
+      c->stepped = gp.tile == TILE_STEP;
+      // A new run clears the whole control block; a continued one (and every launch after the
+      // first) only the registration and barrier counters, so that an abort in an earlier chunk of
+      // the run stays raised, ends the later ones at once, and is reported when the run is read.
+      if (t_begin == 1)
+        HIP_TRY(launch_zero_words(reinterpret_cast<uint32_t*>(c->d_ctl), 0, (size_t)xcd_ctl_words(), 0, 0, st));
     }
-    c->launches = t_end - t_begin + 1;
-    HIP_TRY(hipEventRecord(c->evm, st));
-    HIP_TRY(launch_readout(c->prec, c->d_state, c->d_spins, (size_t)R * c->n, st));
+    rc = c->path == 2 && !c->stepped ? launch_groups(c, a, gp, width, st) : launch_steps(c, a, st);
+    if (rc != NMFA_OK) return rc;
   }
   if (!finish) {
     c->state_valid = true;
@@ -1178,7 +1217,7 @@ extern "C" int nmfa_info(nmfa_ctx* c, int32_t* n, int32_t* precision, int32_t* p
         int rc = sync_ctx(c);
         if (rc) return rc;
       }
-      *path = ((c->exchange_mode == 2) ? 3 : 2) + (c->xvar == 1 || c->xvar == 2 ? 2 : 0);
+      *path = c->stepped ? 1 : ((c->exchange_mode == 2) ? 3 : 2) + (c->xvar == 1 || c->xvar == 2 ? 2 : 0);
     } else {
       *path = (c->path == 3) ? 6 + c->sp_rq : c->path;
     }

@@ -22,7 +22,10 @@ struct nmfa_ctx {
   int jfmt = 1;              // path 2: J format in LDS (0 BF16, 1 FP8 E4M3, 2 FP4 E2M1)
   int nbuf = 2;              // path 2: spin chunk buffers in LDS (2, 3, 4 or 6)
   int xvar = 0;              // path 2: 0 = J rows in LDS; in registers: 1 = FP4, 2 = FP4 with FP8 spins,
-                             // 3 = FP8 or BF16 (small tiles only)
+                             // 3 = FP8 or BF16 (small tiles; from some replica count on J in LDS, or the
+                             // per-iteration kernel)
+  int lds_Kp = 0;            // xvar 0 and 3: k length of the LDS-J kernel, 0 where its J does not fit
+  bool stepped = false;      // path 2: the last anneal ran the per-iteration kernel
   unsigned* d_ctl = nullptr; // path 2: control block
   bool ctl_pending = false;  // path 2: abort/mode flags not yet read back
   int exchange_mode = 0;     // path 2: 1 = XCD-local, 2 = device-scope fences
@@ -91,8 +94,10 @@ int ctx_prepare_run(nmfa_ctx* c, int32_t R, int32_t t_f, int32_t t_begin, int32_
 // For the persistent XCD-group path (whose workgroups wait for each other, so that all of one
 // launch must be resident at once): the tile for R replicas when one launch may hold width
 // workgroups. Returns false for the other paths, and where not even one replica group fits.
+enum : int { TILE_LARGE = -1, TILE_LDS = -2, TILE_STEP = -3 };
 struct GroupPlan {
-  int tile = -1;       // small tile (launch_anneal_xrs), or -1 for the large tile of the context's kernel
+  int tile = TILE_LARGE;  // small tile (launch_anneal_xrs), TILE_LARGE: the register-J kernel of FP4 couplings,
+                          // TILE_LDS: the LDS-J kernel, TILE_STEP: per-iteration launches (no groups)
   int P = 1, rg = 1;   // workgroups and replicas per group
   int G = 1;           // groups
   int per_launch = 1;  // groups per launch

@@ -33,6 +33,7 @@ constexpr int GROUP_MAX_WGS = 256;  // workgroups of one group-kernel launch (co
 struct XcdArgs {
   void* S[2];        // operand copies of the spins, BF16 [Rp][ks], double-buffered by parity of t
   int ks;            // row stride of S in elements (>= Kp, a multiple of 8)
+  int jk;            // couplings of a row of J in memory (>= Kp; the LDS-J kernel reads the first Kp)
   unsigned* ctl;     // control block (xcd_ctl_words() words, zeroed before every launch)
   int P;             // workgroups per replica group = Mp / xcd_rows()
   int group_base;    // first replica group of this launch

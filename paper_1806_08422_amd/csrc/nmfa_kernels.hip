@@ -1267,9 +1267,9 @@ __global__ __launch_bounds__(512, 1) void anneal_step_tiled(AnnealArgs a, const 
 // changed nothing, nor did reading three windows ahead instead of one, nor (64 x 32, FP4 J, one workgroup
 // per CU: 0.37 us per block) a ring of 8 stages instead of 5; 3 stages take 0.58 us per block (BF16 J).
 // The grid covers the N rows; rows of the last tile beyond N are written as zeros, and the columns of S
-// past them, which the last block of k multiplies by zero couplings, hold the zeros they were allocated
-// with. (With rows and k padded to a multiple of 256, FP64, us per iteration: N = 120, R = 64 8.9 against
-// 7.4; N = 300, R = 256 13.5, 10.7; N = 777, R = 256 21.9, 18.7; N = 1100, R = 200 33.4, 23.3. FP32, N =
+// past them, which the last block of k multiplies by zero couplings, are finite: the zeros they were
+// allocated with, or what a group kernel kept there. (With rows and k padded to a multiple of 256, FP64,
+// us per iteration: N = 120, R = 64 8.9 against 7.4; N = 300, R = 256 13.5, 10.7; N = 777, R = 256 21.9, 18.7; N = 1100, R = 200 33.4, 23.3. FP32, N =
 // 1100, R = 200 19.7, 14.4.)
 // Needs Mp % 256 == 0, Kp = Mp, and S buffers of roundup(R, 64) rows (padding rows finite).
 // ------------------------------------------------------------------------------------------

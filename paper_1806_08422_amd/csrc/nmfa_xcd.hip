@@ -53,7 +53,8 @@ __global__ __launch_bounds__(512, 1) void anneal_xcd(AnnealArgs a, XcdArgs x) {
   constexpr int CB = JFMT == 0 ? 16 : (JFMT == 1 ? 8 : 4);  // bytes of 8 J values
   typedef typename JRaw<JFMT>::T AT;
   const int N = a.N, Kp = a.Kp, P = x.P, ks = x.ks;
-  const int jrow = JFMT == 0 ? Kp * 2 : (JFMT == 1 ? Kp : Kp / 2);  // bytes of one J row
+  const int jrow = JFMT == 0 ? Kp * 2 : (JFMT == 1 ? Kp : Kp / 2);  // bytes of one J row in LDS
+  const int jrow_g = JFMT == 0 ? x.jk * 2 : (JFMT == 1 ? x.jk : x.jk / 2);  // and in memory
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int g4 = lane >> 4, c = lane & 15;
   const int wa = wave >> 2, wb = wave & 3;  // rows 32*wa.., replicas 32*wb..
@@ -75,12 +76,12 @@ __global__ __launch_bounds__(512, 1) void anneal_xcd(AnnealArgs a, XcdArgs x) {
     // chunks of 8 values: 16 bytes (BF16), 8 (FP8) or 4 (FP4); XOR-swizzled with the row
     constexpr int cb = JFMT == 0 ? 16 : (JFMT == 1 ? 8 : 4);
     const int chunks_per_row = Kp / 8;
-    const unsigned char* Jg = reinterpret_cast<const unsigned char*>(a.J) + (size_t)rb * XCD_ROWS * jrow;
+    const unsigned char* Jg = reinterpret_cast<const unsigned char*>(a.J) + (size_t)rb * XCD_ROWS * jrow_g;
     for (int idx = tid; idx < XCD_ROWS * chunks_per_row; idx += blockDim.x) {
       const int row = idx / chunks_per_row, ch = idx - row * chunks_per_row;
       const int sw = JFMT == 0 ? (ch ^ (row & 7)) : (ch ^ (row & 15));
       unsigned char* dst = Jl + (size_t)row * jrow + sw * cb;
-      const unsigned char* src = Jg + (size_t)row * jrow + ch * cb;
+      const unsigned char* src = Jg + (size_t)row * jrow_g + ch * cb;
       if (JFMT == 0) *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(src);
       else if (JFMT == 1) *reinterpret_cast<uint2*>(dst) = *reinterpret_cast<const uint2*>(src);
       else *reinterpret_cast<uint32_t*>(dst) = *reinterpret_cast<const uint32_t*>(src);
