@@ -570,15 +570,32 @@ __global__ __launch_bounds__(P == PREC_FP64 ? 512 : 1024) void anneal_sparse(Ann
 // where there is room, iterations unrolled by two), no selects for padding spins or the noise's sign,
 // and slots for the degree rather than the next power of two. Per iteration: N = 2000, R = 1024,
 // degree 3 1.98 -> 1.71 us; degree 3, N = 2000, R = 100 0.93 -> 0.61 and N = 301, R = 64 0.73 -> 0.38;
-// degree 6, N = 1000, R = 512 0.99 -> 0.85; degree 10, N = 1537, R = 256 2.20 -> 1.22.
+// degree 6, N = 1000, R = 512 0.99 -> 0.85, N = 2000, R = 1024 2.8 -> 2.6; degree 8, N = 2000, R = 4096 11.0 -> 10.5;
+// degree 10, N = 1537, R = 256 2.20 -> 1.22. Where two workgroups of 512 threads share a CU the registers must
+// leave four waves per SIMD (128): with 129 or 130, degree 6, N = 2000, R = 4096 took 11.4 instead of 8.7 and
+// degree 8 13.2; with one register spilled inside the loop, degree 8, N = 300, R = 64 1.20 instead of 0.62.
 // ------------------------------------------------------------------------------------------
 template <typename T, int RB>
 struct alignas(sizeof(T) * RB) RepVec {
   T v[RB];
 };
 
+// Waves per SIMD that the registers must leave room for: four, two workgroups of 512 threads, wherever a register
+// or two decide it and none is spilled for it.
 template <int P, int RB, int DM, int QP>
-__global__ __launch_bounds__(512) void anneal_sparse_rq(AnnealArgs a, const int* __restrict__ ell_col,
+constexpr int rq_min_waves() {
+  return P != PREC_FP64 && QP == 1 && (RB <= 2 ? DM <= 6 : DM == 3) ? 4 : 2;
+}
+
+// Iterations unrolled by two, which takes registers: not where they would leave a SIMD fewer waves than the rolled
+// loop (FP32, 8 or 10 slots, two or four replicas) nor where it gained nothing (FP64, 8 slots).
+template <int P, int RB, int DM, int QP>
+constexpr bool rq_unrolled() {
+  return QP == 1 && (P == PREC_FP64 ? DM != 8 : RB == 1 || (DM != 8 && DM != 10));
+}
+
+template <int P, int RB, int DM, int QP, bool UNROLL = rq_unrolled<P, RB, DM, QP>()>
+__global__ __launch_bounds__(512, (rq_min_waves<P, RB, DM, QP>())) void anneal_sparse_rq(AnnealArgs a, const int* __restrict__ ell_col,
                                                        const void* __restrict__ ell_val, int D) {
   using acc_t = typename Traits<P>::acc_t;
   using V = RepVec<acc_t, RB>;
@@ -684,7 +701,7 @@ __global__ __launch_bounds__(512) void anneal_sparse_rq(AnnealArgs a, const int*
     }
     __syncthreads();
   };
-  if constexpr (QP == 1) {
+  if constexpr (UNROLL) {
     int t = a.t_begin;
     for (; t < a.t_end; t += 2) {
       step(std::integral_constant<int, 0>{}, t);
@@ -1580,7 +1597,7 @@ size_t sparse_lds_bytes(int prec, int N, int RB) {
 // 16 (a slot beyond D costs a gather and an FMA per spin all the same), QP quads per thread (1 up to
 // 512 quads, 2 up to 1024), with QP * (D rounded up to 4, 8 or 16) * (value words + 1) <= 32. FP64
 // keeps RB <= 2, and RB = 2 only for DM <= 4, QP = 1: its epilogue, unrolled over the replicas, would
-// spill otherwise.
+// spill otherwise (with 4 slots it spills six registers: N = 2000, R = 1024 17.4 us before, 16.8 with them).
 template <int P, int RB>
 static const void* rq_fn_d(int DM, int QP) {
   if (QP == 1) {
@@ -1672,6 +1689,10 @@ static int sparse_rq_pick(int prec, int N, int D, int R, SparseRq* o) {
     if (res4 < 16L * cus && g2 >= 2 * cus && per_cu(2) >= 2) RB = 2;
   }
   o->fn = rq_fn(prec, RB, DM, QP);
+  // one replica, 8 slots: unrolled it has 129 registers, so one workgroup of more than four waves on a CU. Where
+  // the grid asks for more, the rolled loop (degree 7, us per iteration, N = 1500, R = 400 2.18, rolled 1.83).
+  if (prec != PREC_FP64 && RB == 1 && DM == 8 && QP == 1 && R > cus)
+    o->fn = (const void*)anneal_sparse_rq<PREC_FP32, 1, 8, 1, false>;
   o->RB = RB;
   o->threads = threads;
   o->lds = lds_of(RB);

@@ -1,0 +1,62 @@
+"""Vector registers of the built kernels, from the metadata of the code objects in the library: kernels that
+are bound by how many waves a SIMD holds stay within the 128 registers (or another bound) that their launch
+rule counts on, without spills."""
+import os
+import re
+import struct
+
+import msgpack
+import pytest
+
+from paper_1806_08422_amd import build
+
+
+@pytest.fixture(scope="module")
+def kernels():
+    """name -> (vector registers, spilled registers) of every gfx950 kernel in libnmfa.so."""
+    if not os.path.exists(build.LIB):
+        build.build()
+    with open(build.LIB, "rb") as f:
+        blob = f.read()
+    out = {}
+    for m in re.finditer(b"__CLANG_OFFLOAD_BUNDLE__", blob):
+        n, = struct.unpack_from("<Q", blob, m.start() + 24)
+        q = m.start() + 32
+        for _ in range(n):
+            off, size, length = struct.unpack_from("<QQQ", blob, q)
+            target = blob[q + 24:q + 24 + length]
+            q += 24 + length
+            if b"gfx950" in target:
+                out.update(_metadata(blob[m.start() + off:m.start() + off + size]))
+    assert out
+    return out
+
+
+def _metadata(elf):
+    shoff, = struct.unpack_from("<Q", elf, 0x28)
+    shsize, shnum = struct.unpack_from("<HH", elf, 0x3A)
+    for i in range(shnum):
+        if struct.unpack_from("<I", elf, shoff + i * shsize + 4)[0] != 7:  # SHT_NOTE
+            continue
+        o, = struct.unpack_from("<Q", elf, shoff + i * shsize + 24)
+        name, desc, _ = struct.unpack_from("<III", elf, o)
+        o += 12 + (name + 3) // 4 * 4
+        doc = msgpack.unpackb(elf[o:o + desc], strict_map_key=False)
+        return {k[".name"]: (k[".vgpr_count"], k[".vgpr_spill_count"]) for k in doc["amdhsa.kernels"]}
+    return {}
+
+
+def _sparse(kernels, P, RB, DM, QP, unroll):
+    name = f"anneal_sparse_rqILi{P}ELi{RB}ELi{DM}ELi{QP}ELb{int(unroll)}E"
+    found = [v for k, v in kernels.items() if name in k]
+    assert len(found) == 1, name
+    return found[0]
+
+
+# FP32 (P = 1), one quad per thread: a workgroup of 512 threads is two waves per SIMD, and two of them share a CU
+@pytest.mark.parametrize("RB,DM,unroll", [
+    (1, 4, True), (1, 6, True), (1, 8, False), (1, 10, True), (2, 3, True), (2, 4, True), (2, 6, True), (2, 8, False),
+    (2, 10, False), (4, 3, True)])
+def test_sparse_kernel_leaves_four_waves(kernels, RB, DM, unroll):
+    vgprs, spills = _sparse(kernels, 1, RB, DM, 1, unroll)
+    assert vgprs <= 128 and spills == 0
