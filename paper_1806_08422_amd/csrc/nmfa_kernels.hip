@@ -778,23 +778,9 @@ template <int P, bool J8>
 static hipError_t launch_small_t(const AnnealArgs& a, hipStream_t st) {
   const int waves = a.Mp / 16;
   const size_t lds = (size_t)2 * 16 * a.lds_stride * sizeof(typename Traits<P>::op_t);
-  const int blocks = (a.R + 15) / 16;
   hipError_t e = hipErrorInvalidValue;
-  // FP64: while every wave of a workgroup can have a SIMD to itself, a tile's waves share its rows,
-  // each running the whole matrix product (the matrix cores are idle) and the libm epilogue of its
-  // rows only. us per iteration with 16 replicas per workgroup: N = 20, R = 256 2.6 with one wave per tile,
-  // 1.5 with two; N = 16 2.4 with one, 1.4 with two, 1.2 with four. Two waves on a SIMD gain nothing (N =
-  // 20, four waves per tile: 2.15; N = 33, two: 2.9 against 2.7), nor do several workgroups per CU (N =
-  // 20, R = 16384).
-  const int cus = device_cus();
-  const int split = P != PREC_FP64 || blocks > cus ? 1 : 4 / waves;
-  // While all its workgroups find a CU each, a workgroup takes 8 or (FP64) 4 replicas (LS = 2 or 4): the
-  // other columns of its product repeat them, and the lanes of the copies take over rows. us per iteration
-  // with LS = 1, 2, 4: FP64 N = 62, R = 1000 2.84, 1.72, 1.46, N = 100, R = 1000 5.67, 3.85, 3.41, N = 62,
-  // R = 2000 2.79, 1.79, 2.60, N = 20, R = 256 (two waves per tile) 1.15, 0.97; BF16 N = 173, R = 64 0.68,
-  // 0.60, 0.60, N = 256, R = 1024 0.92, 0.81, 0.85; FP32 N = 50, R = 1024 0.58, 0.49, 0.53. Two workgroups
-  // on a CU lose: BF16 N = 250, R = 4096 0.97, 1.63, FP32 N = 100, R = 4096 1.30, 2.19.
-  const int ls = P == PREC_FP64 && split == 1 && 4 * a.R <= 16 * cus ? 4 : (2 * a.R <= 16 * cus ? 2 : 1);
+  const SmallSplit sp = small_split(P == PREC_FP64, waves, a.R, device_cus());
+  const int split = sp.split, ls = sp.ls;
   small_dispatch<P>(small_nk<P>(a.Kp), [&](auto nk) {
     constexpr int NK = decltype(nk)::value;
     auto launch = [&](auto split_c, auto ls_c, auto pre_c) {

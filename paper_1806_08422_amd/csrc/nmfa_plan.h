@@ -52,4 +52,30 @@ inline StepPick step_pick(int jfmt, int N, int R, int cus) {
   return p;
 }
 
+// How the persistent small-N kernel shares its work among waves and lanes: `split` waves per 16-row tile, and
+// 16 / ls replicas per workgroup, whose product holds each of them in ls columns.
+struct SmallSplit {
+  int split, ls;
+};
+
+// waves: row tiles of the instance (a wave each). FP64: while every wave of a workgroup can have a SIMD to
+// itself, a tile's waves share its rows, each running the whole matrix product (the matrix cores are idle) and
+// the libm epilogue of its rows only. us per iteration with 16 replicas per workgroup: N = 20, R = 256 2.6 with
+// one wave per tile, 1.5 with two; N = 16 2.4 with one, 1.4 with two, 1.2 with four. Two waves on a SIMD gain
+// nothing (N = 20, four waves per tile: 2.15; N = 33, two: 2.9 against 2.7), nor do several workgroups per CU (N
+// = 20, R = 16384).
+// While all its workgroups find a CU each, a workgroup takes 8 or (FP64) 4 replicas (ls = 2 or 4): the other
+// columns of its product repeat them, and the lanes of the copies take over rows. us per iteration with ls =
+// 1, 2, 4: FP64 N = 62, R = 1000 2.84, 1.72, 1.46, N = 100, R = 1000 5.67, 3.85, 3.41, N = 62, R = 2000 2.79,
+// 1.79, 2.60, N = 20, R = 256 (two waves per tile) 1.15, 0.97; BF16 N = 173, R = 64 0.68, 0.60, 0.60, N = 256, R =
+// 1024 0.92, 0.81, 0.85; FP32 N = 50, R = 1024 0.58, 0.49, 0.53. Two workgroups on a CU lose: BF16 N = 250, R =
+// 4096 0.97, 1.63, FP32 N = 100, R = 4096 1.30, 2.19.
+inline SmallSplit small_split(bool fp64, int waves, int R, int cus) {
+  SmallSplit s{1, 1};
+  if (fp64 && (R + 15) / 16 <= cus && waves <= 2) s.split = 4 / waves;
+  if (fp64 && s.split == 1 && 4 * R <= 16 * cus) s.ls = 4;
+  else if (2 * R <= 16 * cus) s.ls = 2;
+  return s;
+}
+
 }  // namespace nmfa

@@ -30,3 +30,18 @@ def step(tmp_path_factory):
     (0, 8192, 64, 0), (0, 8192, 256, 2), (0, 2000, 1024, 2)])
 def test_step_tile(step, jfmt, n, R, tile):
     assert step(jfmt, n, R) == [str(tile)]
+
+
+@pytest.fixture(scope="module")
+def small(tmp_path_factory):
+    return _run(tmp_path_factory, 'SmallSplit s = small_split(arg(1), arg(2), arg(3), 256); '
+                                  'printf("%d %d", s.split, s.ls); (void)argc;')
+
+
+# waves of a workgroup (n / 16, rounded up), replicas -> waves per tile, columns per replica
+@pytest.mark.parametrize("fp64,waves,R,want", [
+    (1, 1, 64, (4, 2)), (1, 2, 256, (2, 2)), (1, 2, 5000, (1, 1)), (1, 3, 1024, (1, 4)), (1, 4, 1025, (1, 2)),
+    (1, 5, 64, (1, 4)), (1, 7, 1000, (1, 4)), (1, 7, 1024, (1, 4)), (1, 7, 1025, (1, 2)), (1, 7, 2049, (1, 1)),
+    (0, 1, 64, (1, 2)), (0, 7, 2048, (1, 2)), (0, 16, 2049, (1, 1))])
+def test_small_split(small, fp64, waves, R, want):
+    assert small(fp64, waves, R) == [str(x) for x in want]
