@@ -50,7 +50,7 @@ size_t small_noise_bytes();
 hipError_t launch_small_noise(const AnnealArgs& a, void* z, hipStream_t st);
 // jobs: device array of AnnealArgs (one per job); tasks: device array of (job, replica block).
 hipError_t launch_anneal_small_batched(int prec, const AnnealArgs* jobs, const int2* tasks, int n_tasks,
-                                       int max_Mp, size_t lds, hipStream_t st);
+                                       int max_Mp, int max_Kp, size_t lds, hipStream_t st);
 // jfmt: format of J in global memory and LDS: 0 = BF16, 1 = FP8 E4M3, 2 = FP4 E2M1
 hipError_t launch_anneal_xcd(int jfmt, const AnnealArgs& a, const XcdArgs& x, int grid, hipStream_t st);
 // Register-resident-J variant (FP4 J), Kp = xrj_kp(n): BF16 spins with 256 rows per workgroup and

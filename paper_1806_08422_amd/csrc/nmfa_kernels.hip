@@ -420,13 +420,24 @@ __host__ __device__ __forceinline__ bool small_dispatch(int nk, F&& f) {
   return false;
 }
 
-// One launch for replica blocks of many jobs: tasks[b] = (job index, replica block).
-template <int P, bool J8>
-__global__ __launch_bounds__(small_threads<P>()) void anneal_small_batched(const AnnealArgs* __restrict__ jobs,
+// One launch for replica blocks of many jobs: tasks[b] = (job index, replica block). NKMAX: the most operand
+// reads of any of the jobs, which sets the registers, so the workgroups that a CU holds. 16 requests of 4096
+// replicas, 2000 iterations, ms with J in LDS (46 registers, 8 waves per SIMD whatever the size) / one kernel for
+// all sizes (109 to 125 registers) / one per size: BF16 N = 80 14.0 / 15.0 / 12.8, N = 256 58 / 39 / 39; FP32 N = 80 30.1 /
+// 33.2 / 29.0, N = 100 41.3 / 43.5 / 40.6. Up to 80 spins the FP32 workgroups are five waves, four of which fit a CU
+// only if each SIMD has room for one more than five: 31.3 with room for five.
+template <int P>
+constexpr int batched_min_waves(int NK) {
+  return P == PREC_FP32 && NK == 5 ? 6 : 1;
+}
+template <int P, bool J8, int NKMAX>
+__global__ __launch_bounds__(small_threads<P>(), batched_min_waves<P>(NKMAX)) void anneal_small_batched(const AnnealArgs* __restrict__ jobs,
                                                              const int2* __restrict__ tasks) {
   const int2 tk = tasks[blockIdx.x];
   const AnnealArgs a = jobs[tk.x];
-  small_dispatch<P>(small_nk<P>(a.Kp), [&](auto nk) { anneal_small_body<P, J8, decltype(nk)::value>(a, tk.y); });
+  small_dispatch<P>(small_nk<P>(a.Kp), [&](auto nk) {
+    if constexpr (decltype(nk)::value <= NKMAX) anneal_small_body<P, J8, decltype(nk)::value>(a, tk.y);
+  });
 }
 
 // ------------------------------------------------------------------------------------------
@@ -851,21 +862,26 @@ hipError_t launch_anneal_small(int prec, const AnnealArgs& a, hipStream_t st) {
 
 template <int P, bool J8>
 static hipError_t launch_small_batched_t(const AnnealArgs* jobs, const int2* tasks, int n_tasks, int max_Mp,
-                                         size_t lds, hipStream_t st) {
-  hipError_t e = hipFuncSetAttribute((const void*)anneal_small_batched<P, J8>,
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((anneal_small_batched<P, J8>), dim3(n_tasks), dim3(64 * (max_Mp / 16)), lds, st, jobs, tasks);
-  return hipGetLastError();
+                                         int max_Kp, size_t lds, hipStream_t st) {
+  hipError_t e = hipErrorInvalidValue;
+  small_dispatch<P>(small_nk<P>(max_Kp), [&](auto nk) {
+    constexpr int NK = decltype(nk)::value;
+    e = hipFuncSetAttribute((const void*)anneal_small_batched<P, J8, NK>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)lds);
+    if (e != hipSuccess) return;
+    hipLaunchKernelGGL((anneal_small_batched<P, J8, NK>), dim3(n_tasks), dim3(64 * (max_Mp / 16)), lds, st, jobs, tasks);
+    e = hipGetLastError();
+  });
+  return e;
 }
 
 hipError_t launch_anneal_small_batched(int prec, const AnnealArgs* jobs, const int2* tasks, int n_tasks, int max_Mp,
-                                       size_t lds, hipStream_t st) {
+                                       int max_Kp, size_t lds, hipStream_t st) {
   switch (prec) {
-    case PREC_FP64: return launch_small_batched_t<PREC_FP64, false>(jobs, tasks, n_tasks, max_Mp, lds, st);
-    case PREC_FP32: return launch_small_batched_t<PREC_FP32, false>(jobs, tasks, n_tasks, max_Mp, lds, st);
-    case PREC_BF16: return launch_small_batched_t<PREC_BF16, false>(jobs, tasks, n_tasks, max_Mp, lds, st);
-    case PREC_FP8J_BF16S: return launch_small_batched_t<PREC_BF16, true>(jobs, tasks, n_tasks, max_Mp, lds, st);
+    case PREC_FP64: return launch_small_batched_t<PREC_FP64, false>(jobs, tasks, n_tasks, max_Mp, max_Kp, lds, st);
+    case PREC_FP32: return launch_small_batched_t<PREC_FP32, false>(jobs, tasks, n_tasks, max_Mp, max_Kp, lds, st);
+    case PREC_BF16: return launch_small_batched_t<PREC_BF16, false>(jobs, tasks, n_tasks, max_Mp, max_Kp, lds, st);
+    case PREC_FP8J_BF16S: return launch_small_batched_t<PREC_BF16, true>(jobs, tasks, n_tasks, max_Mp, max_Kp, lds, st);
   }
   return hipErrorInvalidValue;
 }

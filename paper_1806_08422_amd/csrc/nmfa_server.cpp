@@ -397,7 +397,7 @@ void enqueue_round(nmfa_server* s, Round& r) {
   };
 
   // requests on the persistent small-N path: one batched launch
-  int max_Mp = 0;
+  int max_Mp = 0, max_Kp = 0;
   size_t lds = 0;
   std::vector<std::pair<Job*, int>> batched;
   for (size_t k = 0; k < jobs.size(); ++k) {
@@ -412,6 +412,7 @@ void enqueue_round(nmfa_server* s, Round& r) {
     r.h_args.push_back(a);
     for (int b = 0; b < (j->R + 15) / 16; ++b) r.h_tasks.push_back(make_int2(job_index, b));
     max_Mp = std::max(max_Mp, j->ctx->Mp);
+    max_Kp = std::max(max_Kp, j->ctx->Kp);
     lds = std::max(lds, small_run_lds_bytes(j->ctx->prec, j->ctx->lds_stride));
     batched.emplace_back(j, te[k]);
   }
@@ -422,7 +423,7 @@ void enqueue_round(nmfa_server* s, Round& r) {
                        s->stream) == hipSuccess &&
         hipMemcpyAsync(r.d_tasks, r.h_tasks.data(), sizeof(int2) * r.h_tasks.size(), hipMemcpyHostToDevice,
                        s->stream) == hipSuccess &&
-        launch_anneal_small_batched(s->p.precision, r.d_jobs, r.d_tasks, (int)r.h_tasks.size(), max_Mp, lds,
+        launch_anneal_small_batched(s->p.precision, r.d_jobs, r.d_tasks, (int)r.h_tasks.size(), max_Mp, max_Kp, lds,
                                     s->stream) == hipSuccess;
     if (ok) {
       ++s->st.batched_launches;

@@ -60,3 +60,14 @@ def _sparse(kernels, P, RB, DM, QP, unroll):
 def test_sparse_kernel_leaves_four_waves(kernels, RB, DM, unroll):
     vgprs, spills = _sparse(kernels, 1, RB, DM, 1, unroll)
     assert vgprs <= 128 and spills == 0
+
+
+# the batched small-N kernel: registers of the largest job of a launch, not of the largest there is (operand
+# reads NK: BF16 N = 32 NK, FP32 N = 16 NK), so that a CU holds at least as many waves per SIMD as given
+@pytest.mark.parametrize("P,j8,nk,waves", [(2, 0, 1, 8), (2, 0, 3, 6), (2, 0, 4, 5), (2, 1, 3, 6), (1, 0, 2, 6), (1, 0, 5, 6),
+                                           (1, 0, 7, 5), (0, 0, 4, 3)])
+def test_batched_kernel_registers(kernels, P, j8, nk, waves):
+    name = f"anneal_small_batchedILi{P}ELb{j8}ELi{nk}E"
+    found = [v for k, v in kernels.items() if name in k]
+    assert len(found) == 1, name
+    assert -(-found[0][0] // 8) * 8 <= 512 // waves
