@@ -139,6 +139,19 @@ __device__ XcdSlot xcd_register(const XcdArgs& x, int tid) {
   return r;
 }
 
+// Device-scope release and acquire by one thread for its workgroup, and each complete before it goes on: the
+// compiler waits for nothing behind the write-back or the invalidation of a fence where it knows of no other
+// memory operation in flight, and the arrival then passes the write-back (with the L2 full of another kernel's
+// dirty lines one run in twelve read old spins), as other waves' loads might pass the invalidation.
+__device__ __forceinline__ void release_agent() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+__device__ __forceinline__ void acquire_agent() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
 // Group barrier after the new spins are stored, in two halves so that work which does not
 // depend on the other workgroups can run in between. Arrive: this workgroup's stores are
 // complete (and released to the device when the group spans XCDs); one thread adds to the
@@ -147,7 +160,7 @@ __device__ __forceinline__ void xcd_group_arrive(unsigned* bar, bool xcd_mode, i
   __builtin_amdgcn_s_waitcnt(0);  // this wave's stores of the new spins are complete
   __syncthreads();
   if (tid == 0) {
-    if (!xcd_mode) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    if (!xcd_mode) release_agent();
     __hip_atomic_fetch_add(bar, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
@@ -167,7 +180,7 @@ __device__ __forceinline__ bool xcd_group_wait(const XcdArgs& x, unsigned* bar, 
         break;
       }
     }
-    if (!xcd_mode) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    if (!xcd_mode) acquire_agent();
   }
   __syncthreads();
   return ld_dev(&ctl[CTL_ABORT]) != 0;
@@ -194,7 +207,7 @@ __device__ __forceinline__ bool xrj_group_wait(const XcdArgs& x, unsigned* bar, 
         }
       }
     }
-    if (!xcd_mode) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    if (!xcd_mode) acquire_agent();
     *abort_word = ab;
   }
   __syncthreads();

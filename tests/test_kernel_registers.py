@@ -1,6 +1,10 @@
-"""Vector registers of the built kernels, from the metadata of the code objects in the library: kernels that
-are bound by how many waves a SIMD holds stay within the 128 registers (or another bound) that their launch
-rule counts on, without spills."""
+"""The built kernels, from the code objects in the library.
+
+* Vector registers: kernels that are bound by how many waves a SIMD holds stay within the 128 registers (or
+  another bound) that their launch rule counts on, without spills.
+* Cache write-backs and invalidations of the group kernels' exchange between XCDs: each is waited for before the
+  next memory operation (the compiler's fence alone does not wait where it knows of nothing else in flight).
+"""
 import os
 import re
 import struct
@@ -12,13 +16,13 @@ from paper_1806_08422_amd import build
 
 
 @pytest.fixture(scope="module")
-def kernels():
-    """name -> (vector registers, spilled registers) of every gfx950 kernel in libnmfa.so."""
+def code_objects():
+    """The gfx950 code objects (ELF images) of libnmfa.so."""
     if not os.path.exists(build.LIB):
         build.build()
     with open(build.LIB, "rb") as f:
         blob = f.read()
-    out = {}
+    out = []
     for m in re.finditer(b"__CLANG_OFFLOAD_BUNDLE__", blob):
         n, = struct.unpack_from("<Q", blob, m.start() + 24)
         q = m.start() + 32
@@ -27,8 +31,17 @@ def kernels():
             target = blob[q + 24:q + 24 + length]
             q += 24 + length
             if b"gfx950" in target:
-                out.update(_metadata(blob[m.start() + off:m.start() + off + size]))
+                out.append(blob[m.start() + off:m.start() + off + size])
     assert out
+    return out
+
+
+@pytest.fixture(scope="module")
+def kernels(code_objects):
+    """name -> (vector registers, spilled registers) of every kernel."""
+    out = {}
+    for elf in code_objects:
+        out.update(_metadata(elf))
     return out
 
 
@@ -71,3 +84,14 @@ def test_batched_kernel_registers(kernels, P, j8, nk, waves):
     found = [v for k, v in kernels.items() if name in k]
     assert len(found) == 1, name
     assert -(-found[0][0] // 8) * 8 <= 512 // waves
+
+
+def test_cache_operations_are_waited_for(code_objects):
+    wait = struct.pack("<I", 0xBF8C0F70)  # s_waitcnt vmcnt(0)
+    found = 0
+    for op in (b"\x00\x80\xa0\xe0\x00\x00\x00\x00", b"\x00\x80\xa4\xe0\x00\x00\x00\x00"):  # buffer_wbl2 / buffer_inv sc1
+        for elf in code_objects:
+            for m in re.finditer(re.escape(op), elf):
+                assert elf[m.end():m.end() + 4] == wait
+                found += 1
+    assert found >= 40  # both in every group kernel
