@@ -130,6 +130,11 @@ int nmfa_create(int32_t n, const double *J, const double *h, const nmfa_params *
  * same R and t_f has run eagerly (that call allocates the run buffers and uploads the schedule;
  * a recorded call enqueues kernels and event records only); replaying the graph repeats the
  * recorded call exactly, seed included.
+ * Contexts may run at the same time on streams and threads of their own. The group kernels (paths 2-5) hold
+ * one CU per workgroup until all of theirs run, so the library gives such runs their parts of the chip and lets a
+ * run that does not fit wait, on the device, for those of other streams; a recorded run takes the fewest workgroups,
+ * which runs of other contexts leave free as long as its context lives. Two processes on one GPU do not know of
+ * each other: group kernels of both at the same time may end in NMFA_EDEVICE.
  * Errors: EINVAL (R < 1, t_f < 1, t_f other than n_T_explicit when explicit temperatures
  * were given), ENOMEM, EDEVICE. */
 int nmfa_anneal(nmfa_ctx *c, int32_t R, int32_t t_f, uint64_t seed, void *hip_stream);

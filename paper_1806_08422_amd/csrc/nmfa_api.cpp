@@ -8,6 +8,8 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <map>
+#include <mutex>
 #include <string>
 #include <thread>
 #include <vector>
@@ -16,6 +18,7 @@
 #include "nmfa_ctx.h"
 #include "nmfa_internal.h"
 #include "nmfa_plan.h"
+#include "nmfa_share.h"
 
 using namespace nmfa;
 
@@ -181,6 +184,8 @@ struct CouplingCodes {
 // Context
 // ------------------------------------------------------------------------------------------
 
+static void share_context(nmfa_ctx* c, int by);
+
 static void free_run_buffers(nmfa_ctx* c) {
   (void)hipFree(c->d_state);
   (void)hipFree(c->d_spins);
@@ -224,6 +229,7 @@ extern "C" void nmfa_destroy(nmfa_ctx* c) {
   (void)hipSetDevice(c->device);
   if (c->stream) (void)hipStreamSynchronize(c->stream);
   else (void)hipDeviceSynchronize();
+  share_context(c, -1);
   free_run_buffers(c);
   (void)hipFree(c->d_J);
   (void)hipFree(c->d_inv);
@@ -669,6 +675,7 @@ extern "C" int nmfa_create(int32_t n, const double* J, const double* h, const nm
     CREATE_TRY(hipMalloc(&c->d_ctl, (size_t)xcd_ctl_words() * 4));
     CREATE_TRY(hipMemset(c->d_ctl, 0, (size_t)xcd_ctl_words() * 4));
   }
+  share_context(c, 1);
 #undef CREATE_TRY
   *out = c;
   return NMFA_OK;
@@ -845,7 +852,7 @@ extern "C" int nmfa_anneal_range(nmfa_ctx* c, int32_t R, int32_t t_f, int32_t t_
 // for device-scope fences, most with the smallest tile (N = 2000, R = 100: 2.6 -> 7.0, 3.6 -> 5.3,
 // 4.9 -> 6.7 and 7.3 -> 8.8 us). Two workgroups per CU gained nothing (128 x 16, R = 512: 7.0 us for
 // one launch of 512 workgroups, 2 x 3.5 for two of 256), so width counts one per CU.
-bool ctx_group_plan(const nmfa_ctx* c, int32_t R, int width, GroupPlan* out) {
+bool ctx_group_plan(const nmfa_ctx* c, int32_t R, int width, GroupPlan* out, bool narrow) {
   if (c->path != 2) return false;
   int cus = width;  // the per-iteration kernel's launches need not be resident: they may take every CU
   (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device);
@@ -862,16 +869,15 @@ bool ctx_group_plan(const nmfa_ctx* c, int32_t R, int width, GroupPlan* out) {
     const int P = tile == TILE_LDS ? (c->n + rows - 1) / rows : c->Mp / rows, G = (R + rg - 1) / rg;
     const double t = a + b * (tile == TILE_LDS ? c->lds_Kp : c->Kp) / 1024.0;
     const int local = width / (8 * P) * 8, fenced = width / P;
-    for (const int per : {local, fenced}) {
+    for (const int per : {narrow ? 0 : local, fenced}) {
       if (per < 1) continue;
       const double us = (double)((G + per - 1) / per) * (per == local ? t : t + fences);
       if (any && us >= out->us) continue;
-      *out = GroupPlan{tile, P, rg, G, per, us};
+      *out = GroupPlan{tile, P, rg, G, per, us, !narrow};
       any = true;
     }
-    return P;
   };
-  if (c->xvar != 0)
+  if (c->xvar != 0 && !narrow)
     for (int tile : {2, 1, 0})
       if (xrs_applies(fmt, tile, c->Kp))
         consider(tile, xrs_rows(tile), xrs_group_replicas(tile), kTime[kind][tile][0], kTime[kind][tile][1],
@@ -880,7 +886,7 @@ bool ctx_group_plan(const nmfa_ctx* c, int32_t R, int width, GroupPlan* out) {
   if (c->lds_Kp > 0) consider(TILE_LDS, xcd_rows(), xcd_group_replicas(), 2.0, lds_b, 10.0);
   if (c->xvar == 1) consider(TILE_LARGE, xrj_rows(0), xrj_group_replicas(0), 2.1, 2.6, 0.8);
   if (c->xvar == 2) consider(TILE_LARGE, xrj_rows(1), xrj_group_replicas(1), 2.6, 1.2, 0.8);
-  if (c->xvar == 3 && !(c->flags & NMFA_FLAG_FORCE_XCD)) {
+  if (c->xvar == 3 && !(c->flags & NMFA_FLAG_FORCE_XCD) && !(narrow && any)) {
     const double us = 1.1 * step_pick(c->jfmt, c->n, R, cus).us;  // below n = 2100 its estimate is a little low
     if (!any || us < out->us) {
       *out = GroupPlan{TILE_STEP, 1, 1, 0, 1, us};
@@ -889,7 +895,7 @@ bool ctx_group_plan(const nmfa_ctx* c, int32_t R, int width, GroupPlan* out) {
   }
   if (!any) {  // not even one group fits in width: one group per launch
     width = 1 << 20;
-    if (c->xvar == 0) consider(TILE_LDS, xcd_rows(), xcd_group_replicas(), 2.0, 5.6, 1.0);
+    if (c->xvar == 0 || c->xvar == 3) consider(TILE_LDS, xcd_rows(), xcd_group_replicas(), 2.0, 5.6, 1.0);
     else consider(TILE_LARGE, xrj_rows(c->xvar == 2), xrj_group_replicas(c->xvar == 2), 2.1, 2.6, 0.8);
     out->per_launch = 1;
     out->us = 1e9;
@@ -913,6 +919,49 @@ static int small_noise_ahead(nmfa_ctx* c, const AnnealArgs& a, hipStream_t st) {
   return 0;
 }
 
+// The shared CUs of every device, and events to mark the ends of group launches with. Lives until the process
+// ends; the events are freed with the last group-kernel context of their device.
+struct DeviceShare {
+  std::mutex mu;
+  ChipShare share;
+  std::vector<hipEvent_t> pool;
+  int contexts = 0;
+};
+static DeviceShare& device_share(int device) {
+  static std::mutex mu;
+  static auto* all = new std::map<int, DeviceShare>();
+  std::lock_guard<std::mutex> lk(mu);
+  return (*all)[device];
+}
+
+// Calls that another thread's stream capture would forbid are allowed to this one: they touch no captured stream.
+struct RelaxedCapture {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
+static void share_forget(DeviceShare& d) {
+  RelaxedCapture relaxed;
+  d.share.reap([](void* ev) { return hipEventQuery((hipEvent_t)ev) == hipSuccess; },
+               [&](void* ev) { d.pool.push_back((hipEvent_t)ev); });
+  (void)hipGetLastError();  // hipErrorNotReady
+}
+
+// A context that may run group kernels comes (1) or goes (-1).
+static void share_context(nmfa_ctx* c, int by) {
+  if (c->path != 2 || c->shares == (by > 0)) return;
+  c->shares = by > 0;
+  DeviceShare& d = device_share(c->device);
+  std::lock_guard<std::mutex> lk(d.mu);
+  d.share.unreserve(c);
+  d.contexts += by;
+  if (d.contexts > 0 || by > 0) return;
+  share_forget(d);  // all complete: a context waits for its work before it goes
+  for (hipEvent_t ev : d.pool) (void)hipEventDestroy(ev);
+  d.pool.clear();
+}
+
 // All iterations of a run on the group kernel of plan gp, launches of at most width workgroups one after the other.
 static int launch_groups(nmfa_ctx* c, AnnealArgs a, const GroupPlan& gp, int width, hipStream_t st) {
   const int Rg = gp.rg, G = gp.G, P = gp.P, per_launch = gp.per_launch;
@@ -922,11 +971,7 @@ static int launch_groups(nmfa_ctx* c, AnnealArgs a, const GroupPlan& gp, int wid
   if (gp.tile == TILE_LDS) a.Kp = c->lds_Kp;
   c->launches = 0;
   for (int gb = 0; gb < G; gb += per_launch) {
-    const int ng = std::min(per_launch, G - gb);
-    // workgroups are dispatched round robin over the eight XCDs: a multiple of 8 P of them, where
-    // that many fit, gives every XCD a multiple of P, so that every group exchanges through one L2
-    const int even = (ng + 7) / 8 * 8 * P;
-    const int grid = even <= width ? even : ng * P;
+    const int ng = std::min(per_launch, G - gb), grid = gp.workgroups(ng, width);
     if (gb > 0 || a.t_begin > 1)  // fresh registration and barrier counters; abort and mode persist
       HIP_TRY(launch_zero_words(reinterpret_cast<uint32_t*>(c->d_ctl), 0, 17, 64, (size_t)xcd_ctl_words(), st));
     XcdArgs x{};
@@ -971,6 +1016,68 @@ static int launch_steps(nmfa_ctx* c, AnnealArgs a, hipStream_t st) {
   return NMFA_OK;
 }
 
+// A run of a group-kernel context. Launches of other streams may hold CUs (ChipShare): the run takes its part of the
+// chip, a CU count by the streams that share it or all that they leave, where the streams together get at least
+// as much done as with the whole chip in turn (N = 2000, R = 100: 2.4 us per iteration on 256 CUs, 3.4 on 128), and
+// else the whole of it. Either way it waits for those that it does not fit beside. Replays of a recorded run cannot
+// be made to wait: it is recorded with the fewest workgroups, and other contexts leave it these.
+static int launch_shared(nmfa_ctx* c, const AnnealArgs& a, int max_workgroups, hipStream_t st) {
+  int cus = 0;
+  HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device));
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cap) != hipSuccess) (void)hipGetLastError();
+  const bool captured = cap != hipStreamCaptureStatusNone;
+  DeviceShare& d = device_share(c->device);
+  std::lock_guard<std::mutex> lk(d.mu);
+  GroupPlan gp;
+  int width = cus, most = cus;
+  if (captured) {
+    ctx_group_plan(c, a.R, width, &gp, true);
+  } else {
+    share_forget(d);
+    // 32 CUs hold a group of every tile
+    most = std::max(std::min(cus, 32), cus - d.share.reserved_by_others(c));
+    width = max_workgroups > 0 ? std::min(max_workgroups, most) : most;
+    ctx_group_plan(c, a.R, width, &gp);
+    int held = 0;
+    const int others = d.share.others(st, &held);
+    if (max_workgroups <= 0 && others > 0 && gp.tile != TILE_STEP) {
+      const int part = std::max(std::min(cus, 32), std::max(most / (others + 1), most - held) / 8 * 8);
+      GroupPlan pp;
+      if (part < width && ctx_group_plan(c, a.R, part, &pp) && pp.us <= 0.95 * (others + 1) * gp.us) {
+        gp = pp;
+        width = part;
+      }
+    }
+  }
+  c->stepped = gp.tile == TILE_STEP;
+  if (c->stepped) return launch_steps(c, a, st);
+  const int held = ChipShare::rounded(gp.workgroups(std::min(gp.per_launch, gp.G), width));
+  if (captured) {
+    d.share.reserve(c, held);
+    return launch_groups(c, a, gp, width, st);
+  }
+  hipEvent_t ev = nullptr;
+  if (d.pool.empty()) {
+    RelaxedCapture relaxed;
+    HIP_TRY(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+  } else {
+    ev = d.pool.back();
+    d.pool.pop_back();
+  }
+  int rc = NMFA_OK;
+  for (void* w : d.share.waits(st, held, most))
+    if (hipStreamWaitEvent(st, (hipEvent_t)w, 0) != hipSuccess) rc = NMFA_EDEVICE;
+  if (rc == NMFA_OK) rc = launch_groups(c, a, gp, width, st);
+  else (void)fail(rc, "nmfa_anneal: hipStreamWaitEvent failed");
+  // also after a failure, which may have left launches behind
+  if (hipEventRecord(ev, st) == hipSuccess)
+    d.share.add(st, held, ev, [&](void* e) { d.pool.push_back((hipEvent_t)e); });
+  else
+    (void)hipEventDestroy(ev);
+  return rc;
+}
+
 int ctx_launch_run(nmfa_ctx* c, int32_t R, int32_t t_f, int32_t t_begin, int32_t t_end, uint64_t seed,
                    hipStream_t st, bool finish, int max_workgroups) {
   AnnealArgs a{};
@@ -999,20 +1106,12 @@ int ctx_launch_run(nmfa_ctx* c, int32_t R, int32_t t_f, int32_t t_begin, int32_t
     c->launches = 1;
     HIP_TRY(hipEventRecord(c->evm, st));
   } else {
-    GroupPlan gp;
-    int width = 0;
-    if (c->path == 2) {
-      HIP_TRY(hipDeviceGetAttribute(&width, hipDeviceAttributeMultiprocessorCount, c->device));
-      if (max_workgroups > 0) width = std::min(width, max_workgroups);
-      ctx_group_plan(c, R, width, &gp);
-      c->stepped = gp.tile == TILE_STEP;
-      // A new run clears the whole control block; a continued one (and every launch after the
-      // first) only the registration and barrier counters, so that an abort in an earlier chunk of
-      // the run stays raised, ends the later ones at once, and is reported when the run is read.
-      if (t_begin == 1)
-        HIP_TRY(launch_zero_words(reinterpret_cast<uint32_t*>(c->d_ctl), 0, (size_t)xcd_ctl_words(), 0, 0, st));
-    }
-    rc = c->path == 2 && !c->stepped ? launch_groups(c, a, gp, width, st) : launch_steps(c, a, st);
+    // A new run clears the whole control block; a continued one (and every launch after the
+    // first) only the registration and barrier counters, so that an abort in an earlier chunk of
+    // the run stays raised, ends the later ones at once, and is reported when the run is read.
+    if (c->path == 2 && t_begin == 1)
+      HIP_TRY(launch_zero_words(reinterpret_cast<uint32_t*>(c->d_ctl), 0, (size_t)xcd_ctl_words(), 0, 0, st));
+    rc = c->path == 2 ? launch_shared(c, a, max_workgroups, st) : launch_steps(c, a, st);
     if (rc != NMFA_OK) return rc;
   }
   if (!finish) {

@@ -26,6 +26,7 @@ struct nmfa_ctx {
                              // per-iteration kernel)
   int lds_Kp = 0;            // xvar 0 and 3: k length of the LDS-J kernel, 0 where its J does not fit
   bool stepped = false;      // path 2: the last anneal ran the per-iteration kernel
+  bool shares = false;       // path 2: counted among the contexts that share the device's CUs
   unsigned* d_ctl = nullptr; // path 2: control block
   bool ctl_pending = false;  // path 2: abort/mode flags not yet read back
   int exchange_mode = 0;     // path 2: 1 = XCD-local, 2 = device-scope fences
@@ -102,11 +103,20 @@ struct GroupPlan {
   int G = 1;           // groups
   int per_launch = 1;  // groups per launch
   double us = 0;       // estimated time of one iteration of all groups
+  bool spare = true;   // launches may hold workgroups beyond their groups' (see workgroups)
+  // Workgroups of a launch of ng groups: they are dispatched round robin over the eight XCDs, so a multiple of
+  // 8 P, where that many fit in width, gives every XCD a multiple of P, and every group exchanges through one L2.
+  int workgroups(int ng, int width) const {
+    const int even = (ng + 7) / 8 * 8 * P;
+    return spare && even <= width ? even : ng * P;
+  }
 };
-bool ctx_group_plan(const nmfa_ctx* c, int32_t R, int width, GroupPlan* out);
+// narrow: the kernel that puts the fewest workgroups on a replica, without spare ones.
+bool ctx_group_plan(const nmfa_ctx* c, int32_t R, int width, GroupPlan* out, bool narrow = false);
 // Enqueue iterations t_begin..t_end on the context's kernel path; with finish, also the energies.
 // max_workgroups > 0 caps the workgroups of one group-kernel launch (more launches, one after the
-// other on st, cover the remaining groups); results do not depend on it.
+// other on st, cover the remaining groups); without it they share the chip with those of other streams.
+// Results do not depend on it.
 int ctx_launch_run(nmfa_ctx* c, int32_t R, int32_t t_f, int32_t t_begin, int32_t t_end, uint64_t seed,
                    hipStream_t st, bool finish, int max_workgroups = 0);
 // Energies (E_int zero unless exact) and spins of a run whose energies were enqueued by

@@ -30,6 +30,9 @@ enum : int {
 constexpr int AUX_SC1 = 16;
 
 constexpr unsigned SPIN_LIMIT = 1u << 22;  // about a second of polling
+// The workgroups of a launch wait longer for each other to start: other kernels' workgroups, each of which
+// ends by itself, may hold CUs for as long as their runs take.
+constexpr unsigned START_LIMIT = 16 * SPIN_LIMIT;
 
 __device__ __forceinline__ unsigned ld_dev(const unsigned* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -106,7 +109,7 @@ __device__ XcdSlot xcd_register(const XcdArgs& x, int tid) {
     atomicAdd(&ctl[CTL_TOTAL], 1u);
     unsigned spins = 0;
     while (ld_dev(&ctl[CTL_TOTAL]) < gridDim.x) {
-      if (++spins > SPIN_LIMIT) {
+      if (++spins > START_LIMIT) {
         atomicExch(&ctl[CTL_ABORT], 1u);
         break;
       }

@@ -454,7 +454,8 @@ void enqueue_round(nmfa_server* s, Round& r) {
         (void)hipStreamWaitEvent(st, s->ev_wide, 0);
       }
     }
-    if (ctx_launch_run(j->ctx, j->R, j->t_f, j->t_sched + 1, te[k], j->seed, st, false, group_cap[k]) != NMFA_OK) {
+    if (ctx_launch_run(j->ctx, j->R, j->t_f, j->t_sched + 1, te[k], j->seed, st, false,
+                       group && group_cap[k] == 0 ? s->cus : group_cap[k]) != NMFA_OK) {
       fail_job(j);
       continue;
     }
