@@ -152,9 +152,11 @@ struct Epilogue<PREC_BF16> : EpilogueF32<PREC_BF16> {};
 // waves per SIMD make no difference); FP32: the chain of 16x16x4 products (32 cycles each) beside it.
 // Against J in LDS, a rolled k loop and buffer addresses multiplied out in every iteration, per
 // iteration: BF16 N = 100, R = 16384 1.94 -> 1.73 us, N = 173, R = 64 1.09 -> 0.60, N = 256, R = 1024
-// 1.55 -> 0.81; FP32 N = 100, R = 4096 1.42 -> 1.35; FP64 N = 20, R = 256 2.73 -> 0.88
-// (with the noise drawn ahead, PRE: launch_small_noise). Scheduling the
-// FP32 noise between the products (1.41) or drawing it after them in every second wave gained nothing.
+// 1.55 -> 0.81; FP32 N = 112, R = 4096 1.43 -> 1.21; FP64 N = 20, R = 256 2.73 -> 0.88
+// (with the noise drawn ahead, PRE: launch_small_noise). FP32 draws the noise after it has issued the products, a
+// serial chain of 32 cycles each, which leaves the registers of their operands free as well: drawn before them, N
+// = 48, R = 8192 took 0.86 us (0.81 with J in LDS) instead of 0.76, N = 80, R = 32768 7.2 (6.8) instead of 6.2, N =
+// 112, R = 4096 1.31 (1.43) instead of 1.21.
 // ------------------------------------------------------------------------------------------
 template <int P, bool J8, int NK, int SPLIT = 1, bool PRE = false, int LS = 1>
 __device__ __forceinline__ void anneal_small_body(const AnnealArgs& a, const int rblock) {
@@ -274,7 +276,7 @@ __device__ __forceinline__ void anneal_small_body(const AnnealArgs& a, const int
 #pragma unroll
       for (int v = 0; v < NV; ++v) z[v] = zt[v];
       zr[SLOT] = read_z(t + NPRE);
-    } else {
+    } else if constexpr (P != PREC_FP32) {
       draw(z, t);
     }
     acc4_t acc;
@@ -286,6 +288,10 @@ __device__ __forceinline__ void anneal_small_body(const AnnealArgs& a, const int
       const frag_t* bf = reinterpret_cast<const frag_t*>(&bv[m]);
 #pragma unroll
       for (int u = 0; u < VEC; ++u) acc = Tr::mfma(af[u], bf[u], acc);
+    }
+    if constexpr (P == PREC_FP32) {  // under the chain of products, whose operands' registers are free by then
+      __builtin_amdgcn_sched_barrier(0);
+      draw(z, t);
     }
     acc_t fld[NV];
     if constexpr (SUB == 1) {
@@ -355,14 +361,16 @@ __host__ __device__ constexpr int small_nk(int Kp) {
   return Kp * (int)sizeof(typename Traits<P>::op_t) / 64;
 }
 
-// Largest workgroup (Mp / 16 waves) and the waves per SIMD that the registers must leave room for
+// Largest workgroup (Mp / 16 waves) and the waves per SIMD that the registers must leave room for (FP32, 6 reads:
+// with 82 registers instead of 80 only two workgroups of six waves were on a CU, N = 96, R = 12000 4.0 us
+// instead of 3.0)
 template <int P>
 constexpr int small_threads() {
   return P == PREC_FP64 ? 512 : (P == PREC_FP32 ? 768 : 1024);
 }
 template <int P>
 constexpr int small_min_waves(int NK) {
-  return P == PREC_FP64 ? 2 : (P == PREC_FP32 || NK > 4 ? 4 : 5);
+  return P == PREC_FP64 ? 2 : (P == PREC_FP32 ? (NK == 6 ? 6 : 4) : (NK > 4 ? 4 : 5));
 }
 
 template <int P, bool J8, int NK, int SPLIT, bool PRE, int LS>
@@ -422,16 +430,11 @@ __host__ __device__ __forceinline__ bool small_dispatch(int nk, F&& f) {
 
 // One launch for replica blocks of many jobs: tasks[b] = (job index, replica block). NKMAX: the most operand
 // reads of any of the jobs, which sets the registers, so the workgroups that a CU holds. 16 requests of 4096
-// replicas, 2000 iterations, ms with J in LDS (46 registers, 8 waves per SIMD whatever the size) / one kernel for
-// all sizes (109 to 125 registers) / one per size: BF16 N = 80 14.0 / 15.0 / 12.8, N = 256 58 / 39 / 39; FP32 N = 80 30.1 /
-// 33.2 / 29.0, N = 100 41.3 / 43.5 / 40.6. Up to 80 spins the FP32 workgroups are five waves, four of which fit a CU
-// only if each SIMD has room for one more than five: 31.3 with room for five.
-template <int P>
-constexpr int batched_min_waves(int NK) {
-  return P == PREC_FP32 && NK == 5 ? 6 : 1;
-}
+// replicas, ms with J in LDS (46 registers, 8 waves per SIMD whatever the size) / one kernel for all sizes (109 to
+// 125 registers) / one per size: BF16, 2000 iterations, N = 80 14.0 / 15.0 / 12.8, N = 256 58 / 39 / 39; FP32, 4000
+// iterations, N = 80 58 / 65 / 51, N = 100 81 / 85 / 73.
 template <int P, bool J8, int NKMAX>
-__global__ __launch_bounds__(small_threads<P>(), batched_min_waves<P>(NKMAX)) void anneal_small_batched(const AnnealArgs* __restrict__ jobs,
+__global__ __launch_bounds__(small_threads<P>()) void anneal_small_batched(const AnnealArgs* __restrict__ jobs,
                                                              const int2* __restrict__ tasks) {
   const int2 tk = tasks[blockIdx.x];
   const AnnealArgs a = jobs[tk.x];

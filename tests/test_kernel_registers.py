@@ -86,6 +86,13 @@ def test_batched_kernel_registers(kernels, P, j8, nk, waves):
     assert -(-found[0][0] // 8) * 8 <= 512 // waves
 
 
+# the small-N kernel in FP32: 80 registers for six waves per SIMD up to 96 spins (16 per operand read)
+@pytest.mark.parametrize("nk", [3, 5, 6])
+def test_small_fp32_registers(kernels, nk):
+    found = [v for k, v in kernels.items() if f"anneal_smallILi1ELb0ELi{nk}ELi1ELb0ELi1E" in k]
+    assert len(found) == 1 and found[0][0] <= 80
+
+
 def test_cache_operations_are_waited_for(code_objects):
     wait = struct.pack("<I", 0xBF8C0F70)  # s_waitcnt vmcnt(0)
     found = 0
