@@ -904,6 +904,14 @@ bool ctx_group_plan(const nmfa_ctx* c, int32_t R, int width, GroupPlan* out, boo
   return true;
 }
 
+// Calls that the capture of another stream, in its default mode, would forbid and be ended by are allowed while this
+// lives: they touch no captured stream.
+struct RelaxedCapture {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
 // Iterations of a small-N run whose noise is drawn ahead by a launch of its own, 0 where the annealing kernel
 // draws it: also for a recorded run (the trajectory counts its iterations from the launch's first) and where
 // the buffer is not there and cannot be allocated, as while a stream is captured.
@@ -911,6 +919,7 @@ static int small_noise_ahead(nmfa_ctx* c, const AnnealArgs& a, hipStream_t st) {
   const int ahead = a.traj ? 0 : small_noise_iters(c->prec, a.Mp, a.R, a.t_end - a.t_begin + 1);
   if (ahead == 0 || c->d_z) return ahead;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  RelaxedCapture relaxed;
   if (hipStreamIsCapturing(st, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
       hipMalloc(&c->d_z, small_noise_bytes()) == hipSuccess)
     return ahead;
@@ -933,13 +942,6 @@ static DeviceShare& device_share(int device) {
   std::lock_guard<std::mutex> lk(mu);
   return (*all)[device];
 }
-
-// Calls that another thread's stream capture would forbid are allowed to this one: they touch no captured stream.
-struct RelaxedCapture {
-  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-  RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
-  ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
-};
 
 static void share_forget(DeviceShare& d) {
   RelaxedCapture relaxed;
