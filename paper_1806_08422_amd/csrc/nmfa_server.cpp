@@ -84,12 +84,13 @@ struct Job {
 // Upper bound of the device memory one request needs on any kernel path (J operand copy, exact
 // energy copy, normalisers, schedule, state, spins, energies and the spin operand buffers).
 size_t job_bytes(int n, int R, int t_f, bool j_integral) {
-  const size_t Kp = std::max<size_t>(512, round_up_sz(n, 256)), Mp = round_up_sz(n, 128);  // either XCD layout
+  const size_t Kp = std::max<size_t>(512, round_up_sz(n, 256)), Mp = Kp;  // the largest layout of any kernel
   const size_t Rp = round_up_sz(R, 128);
   size_t b = Mp * Kp * 2;                          // J operand (BF16 or smaller)
   b += (size_t)n * n * (j_integral ? 1 : 8);       // J for exact energies
   b += 2 * Mp * 4 + (size_t)t_f * 4 + (size_t)n * 8;
   b += (size_t)R * n * 4 + (size_t)R * n + (size_t)R * 16;
+  if (!j_integral) b += energy_f64_part(n) * R * 8;  // partial sums of the energies
   b += 2 * Rp * Kp * 2;                            // spin operand double buffer
   b += 96 * 1024;                                  // control block and alignment slack
   return b;
