@@ -473,6 +473,7 @@ extern "C" int nmfa_create(int32_t n, const double* J, const double* h, const nm
   } else if ((p->flags & NMFA_FLAG_FORCE_XCD) && x_ok) {
     c->path = 2;
   } else if ((p->flags & NMFA_FLAG_FORCE_XCD)) {
+    nmfa_destroy(c);
     return fail(NMFA_EINVAL, "nmfa_create: the XCD-group kernel needs BF16 / FP8-J precision, n <= 2048 and "
                              "couplings that fit its LDS");
   } else if (small_fits) {
