@@ -54,12 +54,14 @@ def tts99(t_sample_s: float, p: float) -> float:
 
 
 def kernel_source_sha(kernel_file: str) -> str:
-    """sha256 over a kernel source file followed by the shared device header (Philox, Box-Muller,
-    tanh), the sources a committed counter summary was taken from."""
+    """sha256 over a kernel source file followed by the headers with device code that it includes (the
+    group kernels' barrier and registration; Philox, Box-Muller, tanh), the sources a committed counter
+    summary was taken from."""
     import hashlib
 
     h = hashlib.sha256()
-    for f in (kernel_file, "nmfa_device.h"):
+    group = ("nmfa_group.h",) if kernel_file == "nmfa_xcd.hip" else ()
+    for f in (kernel_file, *group, "nmfa_device.h"):
         with open(os.path.join(ROOT, "paper_1806_08422_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()

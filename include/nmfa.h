@@ -196,14 +196,15 @@ int nmfa_set_state(nmfa_ctx *c, int32_t R, const double *in);
 int nmfa_trajectory(nmfa_ctx *c, double *out);
 
 /* Information about a context: writes n, the precision and the kernel path (0 = persistent
- * small-N kernel with J in LDS; 1 = per-iteration kernel; 2 = persistent XCD-group kernel
+ * small-N kernel, J in registers; 1 = per-iteration kernel; 2 = persistent XCD-group kernel
  * (J rows in registers as FP8 or BF16, n <= 2048, or in LDS) whose groups exchanged spins through
  * one XCD's L2 (where J is neither FP4-exact nor forced onto this kernel, large replica counts run
- * the per-iteration kernel instead, and path is 1 after such an anneal); 3 = the same with device-scope fences, used when a group's workgroups were not all
- * placed on one XCD; 4 and 5 = the XCD-group kernel with J rows held in registers as FP4
- * (FP4-exact couplings, n <= 2048), exchange as for 2 and 3; 6 = the sparse kernel, J as nonzeros per row (chosen for n > 256 when every
- * row has at most min(64, n/8) couplings and either the register variant below applies or no
- * XCD-group kernel does, or with NMFA_FLAG_FORCE_SPARSE); 7 = the sparse kernel with each
+ * the per-iteration kernel instead, and path is 1 after such an anneal); 3 = the same with
+ * device-scope fences, used when a group's workgroups were not all placed on one XCD; 4 and 5 = the
+ * XCD-group kernel with J rows held in registers as FP4 (FP4-exact couplings, n <= 2048), exchange as
+ * for 2 and 3; 6 = the sparse kernel, J as nonzeros per row (chosen for n > 256 when every row has at
+ * most min(64, n/8) couplings and either the register variant below applies, or J is not FP4-exact
+ * and does not fit the LDS-J kernel, or with NMFA_FLAG_FORCE_SPARSE); 7 = the sparse kernel with each
  * thread's rows of J held in registers (at most 16 couplings per row, n <= 4096, fewer
  * couplings per row above n = 2048).
  * Paths 2/3, 4/5 and 6/7 are only told apart after an anneal has completed (the call
@@ -226,7 +227,9 @@ int nmfa_j_format(nmfa_ctx *c, int32_t *fmt);
 /* Device time of the last anneal in milliseconds, from HIP events recorded on the anneal's own
  * stream: *anneal_ms covers the annealing kernel launches only (Algorithm 1's iterations),
  * *total_ms also the readout and the energy evaluation; *launches is the number of annealing
- * kernel launches (1 for the persistent kernels, one per iteration for the per-iteration path).
+ * kernel launches: one per iteration on the per-iteration path; 1 on the persistent ones, or more
+ * where the replicas exceed what one launch of the group kernels holds, and for small FP64 runs
+ * whose noise is drawn ahead, one per stretch of iterations that its buffer holds.
  * Any output pointer may be NULL. Synchronises. Errors: ESTATE, EDEVICE. */
 int nmfa_last_timing(nmfa_ctx *c, double *anneal_ms, double *total_ms, int32_t *launches);
 

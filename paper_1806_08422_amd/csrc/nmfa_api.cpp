@@ -449,8 +449,10 @@ extern "C" int nmfa_create(int32_t n, const double* J, const double* h, const nm
   if (!sp_rb && sparse_lds_bytes(sp_prec, n, 1) <= (size_t)device_max_lds()) sp_rb = 1;
   const bool sp_ok = deg_max <= 64 && sp_rb > 0;
   // chosen by itself where the register-ELL kernel serves it (2-4x faster than the dense kernels
-  // at n = 2000, degree 3-16), or where no persistent dense kernel applies; the generic ELL
-  // kernel, which reads J from global memory every iteration, is slower than the XCD kernel
+  // at n = 2000, degree 3-16), or where neither the FP4 register-J nor the LDS-J kernel applies; the
+  // generic ELL kernel, which reads J from global memory every iteration, is slower than these. (Couplings
+  // that need BF16, 1024 < n <= 2048, 17 to 64 per row: the small register-J tiles would serve them too;
+  // which is faster has not been measured.)
   const bool sp_rq = sp_ok && sparse_rq_applies(sp_prec, n, std::max(deg_max, 1));
   const bool sp_auto = sp_ok && n > 256 && 8 * std::max(deg_max, 1) <= n && (sp_rq || !x_ok);
   if (fp8s) {
@@ -1361,7 +1363,8 @@ extern "C" int nmfa_noise_words(uint64_t seed, int32_t t, int32_t r0, int32_t n_
   const size_t cnt = (size_t)n_rep * n_quads * 4;
   uint32_t* d = nullptr;
   HIP_TRY(hipMalloc(&d, cnt * 4));
-  hipError_t e = launch_noise_words((uint32_t)seed, (uint32_t)(seed >> 32), (uint32_t)t, (uint32_t)r0, n_rep, n_quads, d, 0);
+  hipError_t e =
+      launch_noise_words((uint32_t)seed, (uint32_t)(seed >> 32), (uint32_t)t, (uint32_t)r0, n_rep, n_quads, d, 0);
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (e == hipSuccess) e = hipMemcpy(out, d, cnt * 4, hipMemcpyDeviceToHost);
   (void)hipFree(d);

@@ -202,7 +202,7 @@ __global__ __launch_bounds__(256) void energy_pairs_i8(const int8_t* __restrict_
 #pragma unroll
   for (int ct = 0; ct < 4; ++ct) {
     const int r = rep0 + wr + 16 * ct + c;
-    long long part = 0;  // other values than +-1 are taken as the integers they are: a row's product may need 36 bits
+    long long part = 0;  // other values than +-1 are taken as the integers they are: a product may need 36 bits
 #pragma unroll
     for (int rt = 0; rt < 4; ++rt) {
       const int row = m0 + wm + 16 * rt + 4 * g4;
@@ -439,12 +439,12 @@ hipError_t launch_energy_f64(const double* J64, const double* h, int exact, cons
   // 64 replicas per block where such blocks cover the chip, else 16 (the sums are the same)
   if ((long)nb * ((R + 63) / 64) >= 256) {
     const int by = (R + 63) / 64;
-    hipLaunchKernelGGL(energy_f64<4>, grid_of(nb, by + field_rows(h, R, nb)), dim3(256), 0, st, J64, spins, N, R, by, part,
-                       h, exact, E, E_int, E);
+    hipLaunchKernelGGL(energy_f64<4>, grid_of(nb, by + field_rows(h, R, nb)), dim3(256), 0, st, J64, spins, N, R, by,
+                       part, h, exact, E, E_int, E);
   } else {
     const int by = (R + 15) / 16;
-    hipLaunchKernelGGL(energy_f64<1>, grid_of(nb, by + field_rows(h, R, nb)), dim3(256), 0, st, J64, spins, N, R, by, part,
-                       h, exact, E, E_int, E);
+    hipLaunchKernelGGL(energy_f64<1>, grid_of(nb, by + field_rows(h, R, nb)), dim3(256), 0, st, J64, spins, N, R, by,
+                       part, h, exact, E, E_int, E);
   }
   hipLaunchKernelGGL(energy_f64_finish, dim3((R + 127) / 128), dim3(128), 0, st, (const double*)part, nb,
                      h ? (const double*)E : nullptr, exact, R, E_int, E);
@@ -465,7 +465,8 @@ hipError_t launch_energy_i8(const int8_t* J8p, int Np, const double* h, int h_in
   hipLaunchKernelGGL(pad_spins_kernel, dim3(pb), dim3(256), 0, st, spins, N, R, Sp, Np, Rp, E2);
   long long* fld = reinterpret_cast<long long*>(E);  // the field terms wait in E
   const size_t lds = (size_t)EP_NS * EP_STAGE;
-  hipError_t e = hipFuncSetAttribute((const void*)energy_pairs_i8, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipError_t e =
+      hipFuncSetAttribute((const void*)energy_pairs_i8, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
   const int gx = (Np + EP_T - 1) / EP_T, by = (R + EP_T - 1) / EP_T;
   hipLaunchKernelGGL(energy_pairs_i8, grid_of(gx, by + field_rows(h, R, gx)), dim3(256), lds, st, J8p,

@@ -59,8 +59,8 @@ hipError_t launch_anneal_xrj(const AnnealArgs& a, const XcdArgs& x, int grid, hi
 // The same decomposition with FP8 E4M3 spin operands (FP4 x FP8 scaled MFMA); S holds bytes.
 hipError_t launch_anneal_xrj8(const AnnealArgs& a, const XcdArgs& x, int grid, hipStream_t st);
 // Small tiles of the register-J kernel, J of format jfmt in rows of Kp = xrj_kp(n) couplings and BF16
-// spins (XRS_FP8S: FP4 J and FP8 spins): 64 x 16, 128 x 16 and 128 x 32 (tiles 0, 1, 2; rows x replicas per workgroup). grid:
-// workgroups launched (>= x.groups * x.P).
+// spins (XRS_FP8S: FP4 J and FP8 spins): 64 x 16, 128 x 16 and 128 x 32 (tiles 0, 1, 2; rows x replicas
+// per workgroup). grid: workgroups launched (>= x.groups * x.P).
 constexpr int XRS_FP8S = 3;
 hipError_t launch_anneal_xrs(int jfmt, int tile, const AnnealArgs& a, const XcdArgs& x, int grid, hipStream_t st);
 int xrs_rows(int tile);

@@ -139,24 +139,24 @@ struct Epilogue<PREC_BF16> : EpilogueF32<PREC_BF16> {};
 
 // ------------------------------------------------------------------------------------------
 // anneal_small<P, J8, NK, SPLIT, PRE, LS>: see the file header. Wave w owns rows [16w, 16w+16) (FP64 with
-// SPLIT > 1: SPLIT waves share a tile's rows, see the launcher); grid = ceil(R / 16) workgroups,
+// SPLIT > 1: SPLIT waves share a tile's rows, see small_split); grid = ceil(R / 16) workgroups,
 // workgroup b owns replicas [16b, 16b+16) (LS > 1: 16 / LS of them, each in LS columns of the product
-// whose lanes share the replica's rows; while a CU is free for every workgroup, see the launcher). Each lane keeps its part of J in registers (NK reads of 16
-// bytes; J8: FP8 E4M3 in memory, widened to BF16). LDS: Ss[2][16][js] (op_t), js = padded row stride in
-// elements. The iterations are unrolled by two, so that the buffers' addresses are constants.
-// The body is shared with anneal_small_batched, where one launch carries replica blocks of many
-// jobs (serving): a workgroup may then have more waves than its job has row tiles, and the extra
-// waves only take part in the barriers.
-// What bounds it: the vector instructions, about 120 per wave and iteration, most of them the noise
-// (BF16, N = 100, R = 16384: 28 waves per CU, 593 cycles per wave and iteration; five or seven
-// waves per SIMD make no difference); FP32: the chain of 16x16x4 products (32 cycles each) beside it.
-// Against J in LDS, a rolled k loop and buffer addresses multiplied out in every iteration, per
-// iteration: BF16 N = 100, R = 16384 1.94 -> 1.73 us, N = 173, R = 64 1.09 -> 0.60, N = 256, R = 1024
-// 1.55 -> 0.81; FP32 N = 112, R = 4096 1.43 -> 1.21; FP64 N = 20, R = 256 2.73 -> 0.88
-// (with the noise drawn ahead, PRE: launch_small_noise). FP32 draws the noise after it has issued the products, a
-// serial chain of 32 cycles each, which leaves the registers of their operands free as well: drawn before them, N
-// = 48, R = 8192 took 0.86 us (0.81 with J in LDS) instead of 0.76, N = 80, R = 32768 7.2 (6.8) instead of 6.2, N =
-// 112, R = 4096 1.31 (1.43) instead of 1.21.
+// whose lanes share the replica's rows; while a CU is free for every workgroup, see small_split). Each
+// lane keeps its part of J in registers (NK reads of 16 bytes; J8: FP8 E4M3 in memory, widened to BF16).
+// LDS: Ss[2][16][js] (op_t), js = padded row stride in elements. The iterations are unrolled by two, so
+// that the buffers' addresses are constants. The body is shared with anneal_small_batched, where one
+// launch carries replica blocks of many jobs (serving): a workgroup may then have more waves than its
+// job has row tiles, and the extra waves only take part in the barriers. What bounds it: the vector
+// instructions, about 120 per wave and iteration, most of them the noise (BF16, N = 100, R = 16384: 28
+// waves per CU, 593 cycles per wave and iteration; five or seven waves per SIMD make no difference);
+// FP32: the chain of 16x16x4 products (32 cycles each) beside it. Against J in LDS, a rolled k loop and
+// buffer addresses multiplied out in every iteration, per iteration: BF16 N = 100, R = 16384 1.94 ->
+// 1.73 us, N = 173, R = 64 1.09 -> 0.60, N = 256, R = 1024 1.55 -> 0.81; FP32 N = 112, R = 4096 1.43 ->
+// 1.21; FP64 N = 20, R = 256 2.73 -> 0.88 (with the noise drawn ahead, PRE: launch_small_noise). FP32
+// draws the noise after it has issued the products, a serial chain of 32 cycles each, which leaves the
+// registers of their operands free as well: drawn before them, N = 48, R = 8192 took 0.86 us (0.81 with
+// J in LDS) instead of 0.76, N = 80, R = 32768 7.2 (6.8) instead of 6.2, N = 112, R = 4096 1.31 (1.43)
+// instead of 1.21.
 // ------------------------------------------------------------------------------------------
 template <int P, bool J8, int NK, int SPLIT = 1, bool PRE = false, int LS = 1>
 __device__ __forceinline__ void anneal_small_body(const AnnealArgs& a, const int rblock) {
@@ -609,8 +609,8 @@ constexpr bool rq_unrolled() {
 }
 
 template <int P, int RB, int DM, int QP, bool UNROLL = rq_unrolled<P, RB, DM, QP>()>
-__global__ __launch_bounds__(512, (rq_min_waves<P, RB, DM, QP>())) void anneal_sparse_rq(AnnealArgs a, const int* __restrict__ ell_col,
-                                                       const void* __restrict__ ell_val, int D) {
+__global__ __launch_bounds__(512, (rq_min_waves<P, RB, DM, QP>())) void anneal_sparse_rq(
+    AnnealArgs a, const int* __restrict__ ell_col, const void* __restrict__ ell_val, int D) {
   using acc_t = typename Traits<P>::acc_t;
   using V = RepVec<acc_t, RB>;
   extern __shared__ __align__(16) unsigned char smem_sp[];
@@ -872,7 +872,8 @@ static hipError_t launch_small_batched_t(const AnnealArgs* jobs, const int2* tas
     e = hipFuncSetAttribute((const void*)anneal_small_batched<P, J8, NK>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)lds);
     if (e != hipSuccess) return;
-    hipLaunchKernelGGL((anneal_small_batched<P, J8, NK>), dim3(n_tasks), dim3(64 * (max_Mp / 16)), lds, st, jobs, tasks);
+    hipLaunchKernelGGL((anneal_small_batched<P, J8, NK>), dim3(n_tasks), dim3(64 * (max_Mp / 16)), lds, st, jobs,
+                       tasks);
     e = hipGetLastError();
   });
   return e;
@@ -1291,8 +1292,8 @@ __global__ __launch_bounds__(512, 1) void anneal_step_tiled(AnnealArgs a, const 
 // The grid covers the N rows; rows of the last tile beyond N are written as zeros, and the columns of S
 // past them, which the last block of k multiplies by zero couplings, are finite: the zeros they were
 // allocated with, or what a group kernel kept there. (With rows and k padded to a multiple of 256, FP64,
-// us per iteration: N = 120, R = 64 8.9 against 7.4; N = 300, R = 256 13.5, 10.7; N = 777, R = 256 21.9, 18.7; N = 1100, R = 200 33.4, 23.3. FP32, N =
-// 1100, R = 200 19.7, 14.4.)
+// us per iteration: N = 120, R = 64 8.9 against 7.4; N = 300, R = 256 13.5, 10.7; N = 777, R = 256 21.9,
+// 18.7; N = 1100, R = 200 33.4, 23.3. FP32, N = 1100, R = 200 19.7, 14.4.)
 // Needs Mp % 256 == 0, Kp = Mp, and S buffers of roundup(R, 64) rows (padding rows finite).
 // ------------------------------------------------------------------------------------------
 template <int P, int JFMT, int RT, int CT, int WM, int WR, int WPC = 1>
@@ -1517,8 +1518,8 @@ __device__ __forceinline__ void step_tiled_f_body(const AnnealArgs& a, const voi
 }
 
 template <int P, int JFMT, int RT, int CT, int WM, int WR, int WPC>
-__global__ __launch_bounds__(64 * WM * WR, WM * WR * WPC / 4) void anneal_step_tiled_f(AnnealArgs a, const void* __restrict__ S_cur,
-                                                                       void* __restrict__ S_next, int t) {
+__global__ __launch_bounds__(64 * WM * WR, WM * WR * WPC / 4) void anneal_step_tiled_f(
+    AnnealArgs a, const void* __restrict__ S_cur, void* __restrict__ S_next, int t) {
   step_tiled_f_body<P, JFMT, RT, CT, WM, WR, WPC>(a, S_cur, S_next, t);
 }
 
@@ -1541,7 +1542,8 @@ static hipError_t launch_step_f(const AnnealArgs& a, const void* S_cur, void* S_
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
   const dim3 grid = tile_grid((a.N + T::TM - 1) / T::TM, (a.R + T::TR - 1) / T::TR);
-  hipLaunchKernelGGL((anneal_step_tiled_f<P, JFMT, RT, CT, WM, WR, WPC>), grid, dim3(64 * T::W), lds, st, a, S_cur, S_next, t);
+  hipLaunchKernelGGL((anneal_step_tiled_f<P, JFMT, RT, CT, WM, WR, WPC>), grid, dim3(64 * T::W), lds, st, a, S_cur,
+                     S_next, t);
   return hipGetLastError();
 }
 
@@ -1638,7 +1640,8 @@ static const void* rq_fn(int prec, int RB, int DM, int QP) {
   if (prec == PREC_FP64) {
     if (RB == 2) {
       if (QP != 1 || DM > 4) return nullptr;
-      return DM == 3 ? (const void*)anneal_sparse_rq<PREC_FP64, 2, 3, 1> : (const void*)anneal_sparse_rq<PREC_FP64, 2, 4, 1>;
+      return DM == 3 ? (const void*)anneal_sparse_rq<PREC_FP64, 2, 3, 1>
+                     : (const void*)anneal_sparse_rq<PREC_FP64, 2, 4, 1>;
     }
     return RB == 1 ? rq_fn_d<PREC_FP64, 1>(DM, QP) : nullptr;
   }

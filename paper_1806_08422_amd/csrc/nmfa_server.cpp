@@ -549,7 +549,8 @@ void scheduler(nmfa_server* s) {
     {
       std::unique_lock<std::mutex> lk(s->mu);
       if (!busy) s->cv_work.wait(lk, [&] { return s->stop || !s->active.empty() || s->want_free; });
-      if (s->stop && s->queue.empty() && s->active.empty() && !busy) break;  // the admission thread retires what it still sets up
+      // (the admission thread retires what it still sets up)
+      if (s->stop && s->queue.empty() && s->active.empty() && !busy) break;
     }
     // round k+1 is enqueued before round k is waited for, so that the device has the next round
     // queued while the host collects results

@@ -1028,8 +1028,9 @@ int xcd_pick_buffers(size_t room) {
 
 // Every workgroup of a launch must be resident at once (they wait for each other). One
 // workgroup fills a CU's LDS, so that holds when the grid does not exceed what the occupancy
-// calculator allows; a launch that cannot become resident (a GPU shared with long-running work)
-// ends in the bounded registration wait with an error rather than hanging. An ordinary launch is
+// calculator allows and no other launch that waits in the same way holds CUs (the callers see to that
+// within a process); a launch that cannot become resident (a GPU shared with such launches of another
+// process) ends in the bounded registration wait with an error rather than hanging. An ordinary launch is
 // used rather than the cooperative-launch API, under which the ROCm profiler cannot trace the
 // process.
 hipError_t launch_group_resident(const void* fn, int grid, int block, size_t lds, const AnnealArgs& a,

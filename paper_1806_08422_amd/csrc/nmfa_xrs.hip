@@ -41,9 +41,10 @@ typedef int i32x8 __attribute__((ext_vector_type(8)));
 
 // JFMT: format of J in memory (0 BF16, 1 FP8 E4M3, 2 FP4 E2M1), spins in BF16; XRS_FP8S: FP4 J and FP8
 // E4M3 spins, both taken by the matrix instruction as they are stored (a chunk of 256 bytes per replica
-// is 256 k then, else 128). The first NB chunks of J are held in registers as BF16, widened once at the start; with FP4 J the others stay in FP4 and are widened at
-// every use. NB is what the registers of one wave per SIMD have room for beside about 110 (one
-// column tile) or 150 (two) others; a tile whose FP8 or BF16 J does not fit is not built.
+// is 256 k then, else 128). The first NB chunks of J are held in registers as BF16, widened once at the
+// start; with FP4 J the others stay in FP4 and are widened at every use. NB is what the registers of
+// one wave per SIMD have room for beside about 110 (one column tile) or 150 (two) others; a tile whose
+// FP8 or BF16 J does not fit is not built.
 template <int JFMT, int RT, int CT, int NCH>
 struct XrsCfg {
   static constexpr int ROWS = 64 * RT;         // rows of J per workgroup (16 RT per wave)
@@ -125,7 +126,8 @@ __device__ __forceinline__ void xrs_body(const AnnealArgs& a, const XcdArgs& x) 
         for (int st = 0; st < NST; ++st) {
           uint32_t m[MW];
 #pragma unroll
-          for (int q = 0; q < MW; ++q) m[q] = *reinterpret_cast<const uint32_t*>(p + 64 * MW * ch + 16 * MW * st + 4 * q);
+          for (int q = 0; q < MW; ++q)
+            m[q] = *reinterpret_cast<const uint32_t*>(p + 64 * MW * ch + 16 * MW * st + 4 * q);
           if (i < NB) {
             jb[i < NB ? i : 0][st][rt] = xrs_widen<JFMT>(m);
           } else {

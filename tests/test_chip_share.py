@@ -58,7 +58,8 @@ int main(int, char** argv) {
     L l{width, last[st], {}, false, false};
     if (obey) for (void* e : s.waits(key(st), width, cus)) l.waits.push_back(ev_launch[(size_t)e - 1]);
     size_t ev;
-    if (pool.empty()) { ev = ev_launch.size(); ev_launch.push_back(0); ++events; } else { ev = pool.back(); pool.pop_back(); }
+    if (pool.empty()) { ev = ev_launch.size(); ev_launch.push_back(0); ++events; }
+    else { ev = pool.back(); pool.pop_back(); }
     ev_launch[ev] = (int)all.size();
     s.add(key(st), width, (void*)(ev + 1), release);
     last[st] = (int)all.size();

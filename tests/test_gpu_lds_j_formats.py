@@ -10,8 +10,8 @@ import pytest
 
 import instances
 import oracle
-from contraction_cases import (ONE_STEP_ALPHA, ONE_STEP_T, ONE_STEP_T_AT, ONE_STEP_TF, ONE_STEP_TOL, bf16_grid_couplings,
-                               grid_states, signed_fields)
+from contraction_cases import (ONE_STEP_ALPHA, ONE_STEP_T, ONE_STEP_T_AT, ONE_STEP_TF, ONE_STEP_TOL,
+                               bf16_grid_couplings, grid_states, signed_fields)
 
 pytestmark = pytest.mark.gpu
 
@@ -33,7 +33,8 @@ def _couplings(fmt, n):
     return 5.0 * instances.sk(n, 11).J if fmt == "fp8_e4m3" else bf16_grid_couplings(n, 12)
 
 
-@pytest.mark.parametrize("fmt,n,R", [("fp8_e4m3", 400, 300), ("fp8_e4m3", 1290, 130), ("bf16", 400, 300), ("bf16", 321, 1)])
+@pytest.mark.parametrize("fmt,n,R", [
+    ("fp8_e4m3", 400, 300), ("fp8_e4m3", 1290, 130), ("bf16", 400, 300), ("bf16", 321, 1)])
 def test_one_step(nmfa, fmt, n, R):
     J, h, s0 = _couplings(fmt, n), signed_fields(n, 0.5, 13), grid_states(R, n, 14)
     T = np.full(ONE_STEP_TF, ONE_STEP_T)

@@ -77,8 +77,8 @@ def test_sparse_kernel_leaves_four_waves(kernels, RB, DM, unroll):
 
 # the batched small-N kernel: registers of the largest job of a launch, not of the largest there is (operand
 # reads NK: BF16 N = 32 NK, FP32 N = 16 NK), so that a CU holds at least as many waves per SIMD as given
-@pytest.mark.parametrize("P,j8,nk,waves", [(2, 0, 1, 8), (2, 0, 3, 6), (2, 0, 4, 5), (2, 1, 3, 6), (1, 0, 2, 6), (1, 0, 5, 6),
-                                           (1, 0, 7, 5), (0, 0, 4, 3)])
+@pytest.mark.parametrize("P,j8,nk,waves", [
+    (2, 0, 1, 8), (2, 0, 3, 6), (2, 0, 4, 5), (2, 1, 3, 6), (1, 0, 2, 6), (1, 0, 5, 6), (1, 0, 7, 5), (0, 0, 4, 3)])
 def test_batched_kernel_registers(kernels, P, j8, nk, waves):
     name = f"anneal_small_batchedILi{P}ELb{j8}ELi{nk}E"
     found = [v for k, v in kernels.items() if name in k]
@@ -96,7 +96,8 @@ def test_small_fp32_registers(kernels, nk):
 def test_cache_operations_are_waited_for(code_objects):
     wait = struct.pack("<I", 0xBF8C0F70)  # s_waitcnt vmcnt(0)
     found = 0
-    for op in (b"\x00\x80\xa0\xe0\x00\x00\x00\x00", b"\x00\x80\xa4\xe0\x00\x00\x00\x00"):  # buffer_wbl2 / buffer_inv sc1
+    # buffer_wbl2 sc1, buffer_inv sc1
+    for op in (b"\x00\x80\xa0\xe0\x00\x00\x00\x00", b"\x00\x80\xa4\xe0\x00\x00\x00\x00"):
         for elf in code_objects:
             for m in re.finditer(re.escape(op), elf):
                 assert elf[m.end():m.end() + 4] == wait

@@ -24,8 +24,8 @@ def step(tmp_path_factory):
 
 # 64x32 alone, 64x32, 128, 256x64, 256x128
 @pytest.mark.parametrize("jfmt,n,R,tile", [
-    (2, 1300, 3072, 4), (2, 2100, 2048, 4), (2, 2600, 4096, 4), (2, 3100, 1536, 4), (1, 600, 4096, 4), (1, 2600, 4096, 4),
-    (0, 2000, 1536, 4), (0, 2000, 2048, 4), (0, 2600, 1536, 4), (0, 5500, 1536, 4), (0, 8192, 1280, 4),
+    (2, 1300, 3072, 4), (2, 2100, 2048, 4), (2, 2600, 4096, 4), (2, 3100, 1536, 4), (1, 600, 4096, 4),
+    (1, 2600, 4096, 4), (0, 2000, 1536, 4), (0, 2000, 2048, 4), (0, 2600, 1536, 4), (0, 5500, 1536, 4), (0, 8192, 1280, 4),
     (2, 8192, 1024, 4), (2, 8192, 512, 3), (2, 2100, 64, 1), (2, 2100, 1024, 2), (1, 2000, 1536, 3), (0, 2100, 64, 0),
     (0, 8192, 64, 0), (0, 8192, 256, 2), (0, 2000, 1024, 2)])
 def test_step_tile(step, jfmt, n, R, tile):
