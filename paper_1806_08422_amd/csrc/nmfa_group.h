@@ -142,17 +142,17 @@ __device__ XcdSlot xcd_register(const XcdArgs& x, int tid) {
   return r;
 }
 
-// Device-scope release and acquire by one thread for its workgroup, and each complete before it goes on: the
-// compiler waits for nothing behind the write-back or the invalidation of a fence where it knows of no other
-// memory operation in flight, and the arrival then passes the write-back (with the L2 full of another kernel's
-// dirty lines one run in twelve read old spins), as other waves' loads might pass the invalidation.
+// Device-scope release (of stores that are complete) and acquire by one thread for its workgroup, each complete
+// before it goes on. Written out: behind the write-back or the invalidation of a fence the compiler waits for
+// nothing where it knows of no other memory operation in flight. The arrival then passes the write-back (with the
+// L2 full of another kernel's dirty lines one run in twelve read old spins), as other waves' loads might pass the
+// invalidation. (A fence with a wait behind it changes the schedule of the whole loop: 37.25 ms per headline
+// anneal instead of 37.1.)
 __device__ __forceinline__ void release_agent() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  asm volatile("buffer_wbl2 sc1\n\ts_waitcnt vmcnt(0)" ::: "memory");
 }
 __device__ __forceinline__ void acquire_agent() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  asm volatile("s_waitcnt vmcnt(0)\n\tbuffer_inv sc1\n\ts_waitcnt vmcnt(0)" ::: "memory");
 }
 
 // Group barrier after the new spins are stored, in two halves so that work which does not
