@@ -1063,9 +1063,9 @@ static int launch_shared(nmfa_ctx* c, const AnnealArgs& a, int max_workgroups, h
     return launch_groups(c, a, gp, width, st);
   }
   hipEvent_t ev = nullptr;
-  if (d.pool.empty()) {
+  if (d.pool.empty()) {  // only order matters, no data: the event needs no time stamp and no cache write-back
     RelaxedCapture relaxed;
-    HIP_TRY(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+    HIP_TRY(hipEventCreateWithFlags(&ev, hipEventDisableTiming | hipEventDisableSystemFence));
   } else {
     ev = d.pool.back();
     d.pool.pop_back();
